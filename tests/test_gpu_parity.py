@@ -159,6 +159,32 @@ def test_prefill_scores_random_shapes(sqa, case):
                 assert rel_err(got2[b, h], O.prefill_scores(Qn[b, h * g:(h + 1) * g], Kn[b, h])) < TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("P", [129, 191, 193, 320])
+def test_prefill_scores_by_query_head_and_by_kv_head(sqa, dtype, D, P):
+    """The column sums of a small call are taken per query head and added up afterwards; with a workspace of two
+    floats per query row (no room for those) per KV head.  Both against the oracle, around the edges of the 64-row
+    tiles, with one key whose logits are -inf (it counts nothing)."""
+    g, Hkv, B = 4, 2, 2
+    wl = W.scaled(W.WORKLOADS["tiny"], L=1, Hq=Hkv * g, Hkv=Hkv, D=D, B=B, P=P, dtype=dtype)
+    K, _ = W.prompt_kv(wl, 0, DEV)
+    Q = W.prompt_q(wl, 0, DEV)
+    K[:, :, 5, 0], Q[..., 0] = -float("inf"), Q[..., 0].abs() + 0.5
+    whole = sqa.prefill_scores(Q, K)
+    small = torch.empty_like(whole)
+    ws = torch.empty(B * Hkv * g * P * 8, dtype=torch.uint8, device=DEV)
+    rc = sqa._lib.sqa_prefill_scores(Q.data_ptr(), K.data_ptr(), 0 if dtype == "f32" else 1, B, Hkv * g, Hkv, P, D,
+                                     small.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    Qn, Kn = np64(Q), np64(K)
+    Kn[:, :, 5, 0] = -1e6                             # (the oracle's logits stay finite; exp gives 0 all the same)
+    for got in (whole.cpu().numpy().astype(np.float64), small.cpu().numpy().astype(np.float64)):
+        for b in range(B):
+            for h in range(Hkv):
+                ref = O.prefill_scores(Qn[b, h * g:(h + 1) * g], Kn[b, h])
+                assert ref[5] == 0.0 and rel_err(got[b, h], ref) < TOL[dtype]
+
+
 def _wide_range_qk(case, P, Hq, Hkv, D):
     """Queries and keys that share one direction u; the keys' component along u sets the logit level."""
     r = torch.Generator().manual_seed({"steps_up": 11, "late_peak": 12, "steps_down": 13}[case])
