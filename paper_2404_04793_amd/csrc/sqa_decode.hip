@@ -29,6 +29,7 @@
 // leaves most lanes idle on such a unit and ends in a merge that costs as much
 // as the streaming; one wave walks it 16 rows at a time with nothing to merge.
 #include "sqa_common.h"
+#include <cstring>
 
 namespace sqa {
 
@@ -91,11 +92,32 @@ __device__ __forceinline__ float ld_agent(const float* p) {
 __device__ __forceinline__ void st_agent(unsigned long long* p, unsigned long long v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+__device__ __forceinline__ unsigned long long ld_agent(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 __device__ __forceinline__ void st_agent(unsigned short* p, unsigned short v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ unsigned short ld_agent(const unsigned short* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// element i of an array whose base is the same in all lanes: a global access (the pointers come from a table in
+// memory, where the compiler can only take them for generic ones) with a 32-bit offset, one register instead of two
+typedef __attribute__((address_space(1))) char g_char_t;
+typedef __attribute__((address_space(1))) float g_float_t;
+typedef __attribute__((address_space(1))) int32_t g_int_t;
+__device__ __forceinline__ float ld_f(const float* base, int i) {
+  return *(const g_float_t*)((const g_char_t*)base + (uint32_t)i * 4u);
+}
+__device__ __forceinline__ void st_f(float* base, int i, float v) {
+  *(g_float_t*)((g_char_t*)base + (uint32_t)i * 4u) = v;
+}
+__device__ __forceinline__ int32_t ld_i(const int32_t* base, int i) {
+  return *(const g_int_t*)((const g_char_t*)base + (uint32_t)i * 4u);
+}
+__device__ __forceinline__ float ld_agent_at(const float* base, int i) {
+  return __hip_atomic_load((const g_float_t*)((const g_char_t*)base + (uint32_t)i * 4u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // block-wide reductions; every thread gets the result
@@ -224,6 +246,7 @@ typedef __attribute__((address_space(3))) v4s_t* lds_v4s_ptr;
 constexpr int kWpuMaxSlots = 256;                 // one wave per unit: for units of at most this many slots
 constexpr int kSoloMaxTokens = 512;               // calls with few workgroups: an unsplit unit's tail (scores, decision) is left
                                                   // to wave 0 alone up to this length
+constexpr int kMaxSplit = 128;                    // work items per unit (their statistics are merged in the LDS of the waves' accumulators)
 constexpr int kLogitPad = 33;                     // a unit's H2O scratch region: G x (slots + kLogitPad) floats: the logit of the
                                                   // new token as one more slot, or whole 32-token tiles of bf16 probabilities
                                                   // plus a reference per tile and head
@@ -765,24 +788,53 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
     if (tid == 0) s_ctl[0] = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (s_ctl[0] != nsplit - 1) return;
-    for (int g = wave * RPI + r; g < G; g += kDecWaves * RPI) {
+    // The merge: every record's statistics in one round trip, weights from LDS, then the accumulators, two values
+    // per thread and eight records in flight.  (One lane group per head that walked the records one by one paid a
+    // round trip for each: 10.2 us for a unit in 13 pieces, 14 in 26; now 2.3 and 3.)
+    static_assert(2 * kMaxSplit * G <= (MF ? kDecWaves * kStageBytesPerWave / 4 : kDecWaves * G * D), "records' statistics fit in LDS");
+    float* const rec_m = acc_lds;                 // [nsplit][G] m_k, then the weights; nsplit <= kMaxSplit
+    float* const rec_l = acc_lds + kMaxSplit * G;
+    for (int i = tid; i < nsplit * G; i += kDecThreads) {
+      const unsigned long long ml = ld_agent(reinterpret_cast<const unsigned long long*>(part + (int64_t)i * PREC + D));
+      rec_m[i] = __uint_as_float((uint32_t)ml);
+      rec_l[i] = __uint_as_float((uint32_t)(ml >> 32));
+    }
+    __syncthreads();
+    if (tid < G) {
       float mx = -INFINITY;
-      for (int k = 0; k < nsplit; ++k) mx = fmaxf(mx, ld_agent(&part[((int64_t)k * G + g) * PREC + D]));
-      float lt = 0.f, o[EPL];
-#pragma unroll
-      for (int e = 0; e < EPL; ++e) o[e] = 0.f;
+      for (int k = 0; k < nsplit; ++k) mx = fmaxf(mx, rec_m[k * G + tid]);
+      float lt = 0.f;
       for (int k = 0; k < nsplit; ++k) {          // fixed order
-        const float* rec_p = part + ((int64_t)k * G + g) * PREC;
-        const float f = fast_exp2(ld_agent(&rec_p[D]) - mx);   // some chunk is non-empty: mx is finite
-        lt += ld_agent(&rec_p[D + 1]) * f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) o[e] += ld_agent(&rec_p[c * EPL + e]) * f;
+        const float f = fast_exp2(rec_m[k * G + tid] - mx);       // some chunk is non-empty: mx is finite
+        lt += rec_l[k * G + tid] * f;
+        rec_m[k * G + tid] = f;
       }
-      const float inv = 1.f / lt;
+      s_m[0][tid] = mx; s_l[0][tid] = 1.f / lt;
+    }
+    __syncthreads();
+    for (int e = 2 * tid; e < G * D; e += 2 * kDecThreads) {
+      const int g = e / D;
+      float o0 = 0.f, o1 = 0.f;
+      for (int k0 = 0; k0 < nsplit; k0 += 8) {
+        unsigned long long v[8];
 #pragma unroll
-      for (int e = 0; e < EPL; ++e) o[e] *= inv;
-      RowMath<T>::store(outp + (int64_t)g * ROWB + c * 16, o);
-      if (c == 0) { s_m[0][g] = mx; s_l[0][g] = inv; }
+        for (int k = 0; k < 8; ++k)
+          v[k] = ld_agent(reinterpret_cast<const unsigned long long*>(part + ((int64_t)min(k0 + k, nsplit - 1) * G + g) * PREC + e % D));
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (k0 + k < nsplit) {                  // fixed order
+            const float f = rec_m[(k0 + k) * G + g];
+            o0 += __uint_as_float((uint32_t)v[k]) * f;
+            o1 += __uint_as_float((uint32_t)(v[k] >> 32)) * f;
+          }
+      }
+      const float inv = s_l[0][g];
+      o0 *= inv; o1 *= inv;
+      if constexpr (sizeof(T) == 2) {
+        *reinterpret_cast<uint32_t*>(outp + (int64_t)e * 2) = f32_to_bf16_bits(o0) | (f32_to_bf16_bits(o1) << 16);
+      } else {
+        *reinterpret_cast<float2*>(outp + (int64_t)e * 4) = make_float2(o0, o1);
+      }
     }
     if (tid == 0) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next launch
   }
@@ -828,54 +880,127 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
         if (!solo) __syncthreads();               // (a wave on its own reads back what it wrote itself: LDS keeps a wave's order)
       }
     }
+    // Every thread keeps its lowest heavy score and that slot, so that the decision needs no second walk.
     float mn = INFINITY;
-    constexpr int SB = 4;                         // scores requested together: one round trip per SB tokens
-    for (int i0 = tq; i0 < n; i0 += SB * nthr) {
-      float cur[SB];
-#pragma unroll
-      for (int k = 0; k < SB; ++k) {
-        const int i = i0 + k * nthr;
-        cur[k] = (k == 0 && i0 == tq) ? sc_pre : sc[min(i, rmax)];   // each thread's first score came with the start
+    int mn_slot = -1;
+    bool mn_tie = false;
+    auto put = [&](int i, float old, float p) {   // the new score of slot i
+      const float nv = (i == slot_new ? 0.f : (i == moved_to ? leaver_score : old)) + p;
+      if (i < hh) {
+        if (nv < mn) { mn = nv; mn_slot = i; mn_tie = false; }
+        else if (nv == mn) mn_tie = true;
       }
+      if (i == leaver_slot) s_ctlf[wq][0] = nv;
+      return nv;
+    };
+    if constexpr (MF) {
+      // a thread takes 4 consecutive tokens: one 8-byte access per head
+      typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
+      typedef __attribute__((address_space(1))) f4u_t g_f4u_t;
+      for (int qi = tq; 4 * qi < n; qi += nthr) {
+        const int i = 4 * qi, tile = qi >> 3;
+        const bool whole = i + 3 <= rmax && !(virt && (slot_new >> 2) == qi);
+        float cur[4];
+        if (whole) {
+          const f4u_t c4 = *(const g_f4u_t*)((const g_char_t*)sc + (uint32_t)i * 4u);
+          cur[0] = c4.x; cur[1] = c4.y; cur[2] = c4.z; cur[3] = c4.w;
+        } else {
 #pragma unroll
-      for (int k = 0; k < SB; ++k) {
-        const int i = i0 + k * nthr;
-        if (i < n) {
-          float p = 0.f;
+          for (int k = 0; k < 4; ++k) cur[k] = ld_f(sc, min(i + k, rmax));
+        }
+        const bool in_lds = tile < lds_tiles;
+        unsigned long long ev[G];
+        if (in_lds) {
 #pragma unroll
-          for (int g = 0; g < G; ++g) {
-            if constexpr (MF) {
-              const int at = ((i >> 5) * G + g) * 32 + (i & 31);
-              const bool in_lds = (i >> 5) < lds_tiles;
-              const unsigned short eb = in_lds ? e16_l[at] : (handover ? ld_agent(&e16[at]) : e16[at]);
-              const float e = __uint_as_float((uint32_t)eb << 16);
-              p += e * (use_fac ? fac[(i >> 5) * G + g]
-                                : fast_exp2((in_lds ? tref_l[(i >> 5) * G + g] : ld_agent(&tref[(i >> 5) * G + g])) - s_m[wq][g]) * s_l[wq][g]);
-            } else {
-              const float lg = glogit ? ld_agent(&glogit[(int64_t)g * lpitch + i]) : s_lg[g * lp + i];
-              p += fast_exp2(lg - fm[g]) * fi[g];
+          for (int g = 0; g < G; ++g) ev[g] = *reinterpret_cast<const unsigned long long*>(e16_l + (tile * G + g) * 32 + (i & 31));
+        } else {
+          const unsigned long long* src = reinterpret_cast<const unsigned long long*>(e16 + (int64_t)tile * G * 32 + (i & 31));
+#pragma unroll
+          for (int g = 0; g < G; ++g) ev[g] = handover ? ld_agent(src + g * 8) : src[g * 8];
+        }
+        float p[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          float f;
+          if (use_fac) f = fac[tile * G + g];
+          else f = fast_exp2((in_lds ? tref_l[tile * G + g] : ld_agent(&tref[tile * G + g])) - s_m[wq][g]) * s_l[wq][g];
+          const uint32_t lo = (uint32_t)ev[g], hi = (uint32_t)(ev[g] >> 32);
+          p[0] += bf16_lo(lo) * f; p[1] += bf16_hi(lo) * f;
+          p[2] += bf16_lo(hi) * f; p[3] += bf16_hi(hi) * f;
+        }
+        float nv[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (i + k < n) nv[k] = put(i + k, cur[k], p[k]);
+        if (whole) {
+          *(g_f4u_t*)((g_char_t*)sc + (uint32_t)i * 4u) = f4u_t{nv[0], nv[1], nv[2], nv[3]};
+        } else {
+#pragma unroll
+          for (int k = 0; k < 4; ++k)
+            if (i + k < n) {
+              if (virt && i + k == slot_new) s_ctlf[wq][1] = nv[k];   // stored in step 4, once its slot is free
+              else st_f(sc, i + k, nv[k]);
             }
+        }
+      }
+    } else {
+      constexpr int SB = 4;          // tokens whose scores (and logits) are requested together: one round trip
+      for (int i0 = tq; i0 < n; i0 += SB * nthr) {
+        float cur[SB], lg[SB][G];
+#pragma unroll
+        for (int k = 0; k < SB; ++k)
+          cur[k] = (k == 0 && i0 == tq) ? sc_pre : ld_f(sc, min(i0 + k * nthr, rmax));   // each thread's first score came with the start
+        if (glogit) {
+#pragma unroll
+          for (int k = 0; k < SB; ++k)
+#pragma unroll
+            for (int g = 0; g < G; ++g) lg[k][g] = ld_agent_at(glogit + (int64_t)g * lpitch, min(i0 + k * nthr, n - 1));
+        } else {
+#pragma unroll
+          for (int k = 0; k < SB; ++k)
+#pragma unroll
+            for (int g = 0; g < G; ++g) lg[k][g] = s_lg[g * lp + min(i0 + k * nthr, n - 1)];
+        }
+#pragma unroll
+        for (int k = 0; k < SB; ++k) {
+          const int i = i0 + k * nthr;
+          if (i < n) {
+            float p = 0.f;
+#pragma unroll
+            for (int g = 0; g < G; ++g) p += fast_exp2(lg[k][g] - fm[g]) * fi[g];
+            const float nv = put(i, cur[k], p);
+            if (virt && i == slot_new) s_ctlf[wq][1] = nv;   // stored in step 4, once its slot is free
+            else st_f(sc, i, nv);
           }
-          const float old = i == slot_new ? 0.f : (i == moved_to ? leaver_score : cur[k]);
-          const float nv = old + p;
-          if (virt && i == slot_new) s_ctlf[wq][1] = nv;   // stored in step 4, once its slot is free
-          else sc[i] = nv;
-          if (i < hh) mn = fminf(mn, nv);
-          if (i == leaver_slot) s_ctlf[wq][0] = nv;
         }
       }
     }
     if (decide) {
-      mn = block_min(mn, s_red, solo);            // (the barrier inside also orders the s_ctlf writes)
+      const float low = block_min(mn, s_red, solo);   // (the barrier inside also orders the s_ctlf writes)
       // positions as they will be after step 4: the moved token brings its own
-      const int v = pick_victim(sc, posu, hh, mn, s_ctlf[wq][0], moved_to, leaver_pos, s_red64, solo, tq);
+      int v = -1;
+      if (!(s_ctlf[wq][0] <= low)) {
+        // equal scores -> the highest position: among threads by the maximum below; a thread that met its lowest
+        // score twice (bit 63 of its key) has the heavy scores walked again
+        unsigned long long key = 0ull;
+        if (mn == low && (mn_slot >= 0 || mn_tie)) {
+          if (mn_tie) {
+            key = 1ull << 63;
+          } else {
+            const int ps = mn_slot == moved_to ? leaver_pos : ld_i(posu, mn_slot);
+            key = ((unsigned long long)(uint32_t)(ps + 1) << 32) | (uint32_t)mn_slot;
+          }
+        }
+        key = block_max64(key, s_red64, solo);
+        v = (key >> 63) ? pick_victim(sc, posu, hh, low, s_ctlf[wq][0], moved_to, leaver_pos, s_red64, solo, tq) : (int)(uint32_t)key;
+      }
       if (ae) {
         // Apply it now.  Each score is rewritten by the thread that wrote it
-        // above (slot i belongs to thread i mod nthr), so the two writes to one
+        // above (slot i, or group of 4 slots i, belongs to thread i mod nthr), so the two writes to one
         // address are ordered by that thread's program order.
         victim = v;
-        if (victim >= 0 && tq == victim % nthr) sc[victim] = s_ctlf[wq][0];
-        if (tq == slot_wr % nthr) sc[slot_wr] = s_ctlf[wq][1];
+        if (victim >= 0 && tq == (MF ? victim >> 2 : victim) % nthr) sc[victim] = s_ctlf[wq][0];
+        if (tq == (MF ? slot_wr >> 2 : slot_wr) % nthr) sc[slot_wr] = s_ctlf[wq][1];
       } else {
         next_hint = v;
       }
@@ -948,6 +1073,7 @@ struct DecodePlan {
   uint16_t nsplit[SQA_MAX_LAYERS];
   uint32_t chunk[SQA_MAX_LAYERS];
   uint32_t unit_off[SQA_MAX_LAYERS], part_off[SQA_MAX_LAYERS], logit_off[SQA_MAX_LAYERS];
+  uint8_t order[SQA_MAX_LAYERS];                   // layers in descending budget (stable): long units start first
   uint64_t blocks;
   size_t cnt_bytes, part_bytes, logit_bytes;       // arrival counters, partial records, H2O logits / probabilities
   size_t off_table, off_cnt, off_part, off_logit, bytes;   // where they lie in a caller's workspace
@@ -956,13 +1082,16 @@ struct DecodePlan {
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Units are split only when the call would otherwise leave CUs idle: the target work item is the call's
-// tokens divided by the number of CUs (at least 256 slots, and at most what lets a unit's step logits fit
+// tokens divided by the number of CUs (at least min_item slots, and at most what lets a unit's step logits fit
 // in LDS -- kMaxUnsplit slots x heads; not for the matrix-core variant, which keeps what H2O needs in the
 // workspace), and a unit is cut into equal chunks only if it is more than a quarter longer than that.
 // One workgroup per CU already streams at 80 % of what the chip reaches, so what splitting buys is balance,
 // and the hand-over between a unit's workgroups costs more than a small imbalance: with 256 equal units (a
-// layer of the Llama-2-7B shape at batch 8 launched on its own) whole units take 53 us, halves 60 us,
-// quarters 62 us; all layers at batch 2 take 71 us whole and 81 us cut in three.
+// layer of the Llama-2-7B shape at batch 8 launched on its own) whole units take 56 us, halves 67 us; 320 units
+// 67 us whole, 82 in halves; all layers at batch 2 81 us with the long units whole, 87 cut in three.
+// Where the longest units have to be cut anyway, the pieces are made for 2 or 3 items per CU if the items of one
+// per CU come out unevenly (the busiest of 256 CUs with over 9/8 of its share): 96 units of 2271 slots 41 us in 3
+// pieces (288 items), 34.5 in 5; 130 units of 8192 with 286 of 557, 4 query heads over 1, 167 us and 140.
 constexpr int64_t kMinItems = 256;
 constexpr int64_t kWideTailMaxBlocks = 512;       // calls with at most this many workgroups: see DecodeArgs::wide_tail
 // Matrix-core variant under H2O: LDS a workgroup may use for a unit's per-head probabilities so that three
@@ -973,22 +1102,63 @@ constexpr int kMaxUnsplit = 8192;
 // units (one wave walks a unit 16 rows at a time, so the call needs many units to keep the chip's wave
 // slots filled; the matrix-core variant walks it one 32-token tile at a time).
 constexpr int64_t kWpuMinUnits = 4096;
+// The shortest work item: 4 waves take 128 slots of the matrix-core variant in one 32-token tile each, and 256 slots
+// there cost hardly more; the other kernels walk 16 to 128 rows at a time.  (fp32, D = 128, 8 query heads over 1, two
+// layers of 1500 and 146 slots: 35 us with 256, 25 with 128; 16 over 2, bf16, 4743 slots: 27.5 and 29.8.)
+static int min_item(bool matrix_cores) { return matrix_cores ? 256 : 128; }
+// coarse: the fewest pieces (and the least scratch).
 // scratch_probs: the H2O step's per-token, per-head values live in the workspace for every unit, split or
 // not (the matrix-core variant: they never need LDS, so nothing limits an unsplit unit's length).
 static sqa_status plan_decode(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv, int D, bool h2o,
-                              bool allow_wpu, bool scratch_probs, DecodePlan* p) {
+                              bool allow_wpu, bool scratch_probs, int min_item, bool coarse, DecodePlan* p) {
   const int64_t units = (int64_t)B * Hkv;
   const int g = Hq / Hkv;
   const bool paged = layers[0].block_table != nullptr;
   int64_t tokens = 0;
+  uint8_t* const order = p->order;
+  for (int i = 0; i < n_layers; ++i) {
+    int j = i - 1;
+    while (j >= 0 && layers[order[j]].budget < layers[i].budget) { order[j + 1] = order[j]; --j; }
+    order[j + 1] = (uint8_t)i;
+  }
   for (int i = 0; i < n_layers; ++i) {
     if (layers[i].capacity < 1) return SQA_ERR_CAPACITY;
     if (layers[i].budget < 1) return SQA_ERR_BUDGET;
     tokens += units * (layers[i].budget < layers[i].capacity ? layers[i].budget : layers[i].capacity);
   }
-  int64_t target = tokens / kMinItems;
-  target = target < 256 ? 256 : target;
-  if (h2o && !scratch_probs && target > kMaxUnsplit / g) target = kMaxUnsplit / g;
+  // longest work item a unit is cut for, given how many items the call's tokens are worth
+  auto item_slots = [&](int64_t items) {
+    int64_t t = tokens / items;
+    t = t < min_item ? min_item : t;
+    return h2o && !scratch_probs && t > kMaxUnsplit / g ? (int64_t)(kMaxUnsplit / g) : t;
+  };
+  auto cut = [&](int i, int64_t target, int64_t* ns_out, int64_t* ch_out) {
+    // + 1: under attend-then-evict a full unit attends budget + 1 tokens
+    const int nmax = (layers[i].budget < layers[i].capacity ? layers[i].budget : layers[i].capacity) + 1;
+    int64_t ns = (4 * (int64_t)nmax + 5 * target - 1) / (5 * target);   // ceil(nmax / (1.25 target))
+    ns = ns < 1 ? 1 : (ns > kMaxSplit ? kMaxSplit : ns);
+    int64_t ch = ((nmax + ns - 1) / ns + 63) / 64 * 64;
+    if (h2o && !scratch_probs && ns == 1 && ch * g > kMaxUnsplit) { ns = 2; ch = ((nmax + 1) / 2 + 63) / 64 * 64; }
+    *ns_out = (nmax + ch - 1) / ch;
+    *ch_out = ch;
+  };
+  int64_t target = item_slots(kMinItems);
+  int64_t longest_ns, longest_ch;
+  cut(order[0], target, &longest_ns, &longest_ch);
+  for (int64_t items = kMinItems, best = INT64_MAX; longest_ns > 1 && items <= (coarse ? 1 : 3) * kMinItems; items += kMinItems) {
+    const int64_t t = item_slots(items);
+    int64_t n = 0, shortest = INT64_MAX, load = 0;         // slots the busiest CU streams if it gets every 256th item
+    for (int k = 0; k < n_layers; ++k) {
+      int64_t ns, ch;
+      cut(order[k], t, &ns, &ch);
+      n += units * ns;
+      shortest = ch < shortest ? ch : shortest;
+      const int64_t x = (n + kMinItems - 1) / kMinItems * shortest;
+      load = x > load ? x : load;
+    }
+    if (load <= best) { best = load; target = t; }
+    if (8 * load * kMinItems <= 9 * tokens || t == min_item) break;
+  }
   uint64_t blocks = 0, n_units = 0, n_part = 0, n_logit = 0;
   p->tbl_entries = 0;
   if (paged) {
@@ -1003,14 +1173,9 @@ static sqa_status plan_decode(const sqa_layer_cache* layers, int n_layers, int B
   p->lds_chunk = scratch_probs ? 0 : 64;           // (no LDS logits at all when they live in the workspace)
   p->lds_chunk_w = scratch_probs ? 0 : 64;
   for (int i = 0; i < n_layers; ++i) {
-    // + 1: under attend-then-evict a full unit attends budget + 1 tokens
     const int nmax = (layers[i].budget < layers[i].capacity ? layers[i].budget : layers[i].capacity) + 1;
-    int64_t ns = (4 * (int64_t)nmax + 5 * target - 1) / (5 * target);   // ceil(nmax / (1.25 target))
-    ns = ns < 1 ? 1 : ns;
-    int64_t ch = ((nmax + ns - 1) / ns + 63) / 64 * 64;
-    if (h2o && !scratch_probs && ns == 1 && ch * g > kMaxUnsplit) { ns = 2; ch = ((nmax + 1) / 2 + 63) / 64 * 64; }
-    ns = (nmax + ch - 1) / ch;
-    if (ns > 65535) return SQA_ERR_CAPACITY;
+    int64_t ns, ch;
+    cut(i, target, &ns, &ch);
     p->nsplit[i] = (uint16_t)ns;
     p->chunk[i] = (uint32_t)ch;
     p->wpu[i] = allow_wpu && ns == 1 && nmax <= kWpuMaxSlots && units * n_layers >= kWpuMinUnits;
@@ -1070,13 +1235,12 @@ extern "C" size_t sqa_decode_workspace_bytes(const sqa_layer_cache* layers, int 
   // shape allows it)
   const bool h2o = policy == SQA_H2O;
   size_t bytes = 0;
-  for (int wpu = 0; wpu < 2; ++wpu) {              // (a call may or may not give short units a wave each)
-    if (sqa::plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, wpu != 0, false, &p) != SQA_OK) return 0;
+  const bool mf = D == 128 && Hq / Hkv >= sqa::kMfmaMinGroup;
+  for (int k = 0; k < 6; ++k) {                    // (a call may or may not give short units a wave each, or run on the matrix cores)
+    const bool wpu = (k & 1) != 0, probs = k >= 4;
+    if ((k >= 2 && !mf) || (probs && !h2o)) continue;
+    if (sqa::plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, wpu, probs, sqa::min_item(k >= 2), false, &p) != SQA_OK) return 0;
     bytes = p.bytes > bytes ? p.bytes : bytes;
-    if (h2o && D == 128 && Hq / Hkv >= sqa::kMfmaMinGroup) {
-      if (sqa::plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, wpu != 0, true, &p) != SQA_OK) return 0;
-      bytes = p.bytes > bytes ? p.bytes : bytes;
-    }
   }
   return bytes;
 }
@@ -1142,10 +1306,10 @@ struct DecodeScratch {
 // The launch plan of a call and the dynamic LDS its workgroups need (host arithmetic only).
 static bool uses_mfma(sqa_dtype dt, int D, int g) { return dt == SQA_BF16 && D == 128 && g >= kMfmaMinGroup; }
 static sqa_status plan_call(sqa_dtype dt, int B, int Hq, int Hkv, int D, bool h2o, const sqa_layer_cache* layers,
-                            int n_layers, DecodePlan* plan, size_t* lds_out) {
+                            int n_layers, bool coarse, DecodePlan* plan, size_t* lds_out) {
   const int g = Hq / Hkv;
   const bool mfma = uses_mfma(dt, D, g);
-  const sqa_status ps = plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, true, h2o && mfma, plan);
+  const sqa_status ps = plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, true, h2o && mfma, coarse ? 256 : min_item(mfma), coarse, plan);
   if (ps != SQA_OK) return ps;
   const size_t lds_shared = (size_t)g * plan->lds_chunk, lds_waves = (size_t)kDecWaves * g * plan->lds_chunk_w;
   const size_t lds = (h2o ? (lds_shared > lds_waves ? lds_shared : lds_waves) * sizeof(float) : 0) +
@@ -1160,7 +1324,7 @@ static sqa_status plan_call(sqa_dtype dt, int B, int Hq, int Hkv, int D, bool h2
 static sqa_status decode_prepare(const void* q, const void* k_new, const void* v_new, sqa_dtype dt,
                                  int B, int Hq, int Hkv, int D, int32_t new_pos, sqa_policy policy, int n_sink,
                                  const sqa_layer_cache* layers, int n_layers, const void* out,
-                                 const sqa_batch_opts* opts, decode_fn* fn_out, DecodePlan* plan, size_t* lds_out) {
+                                 const sqa_batch_opts* opts, bool coarse, decode_fn* fn_out, DecodePlan* plan, size_t* lds_out) {
   if (!q || !k_new || !v_new || !layers || !out) return SQA_ERR_NULL;
   if (opts && opts->order != SQA_EVICT_THEN_ATTEND && opts->order != SQA_ATTEND_THEN_EVICT) return SQA_ERR_POLICY;
   if (dt != SQA_F32 && dt != SQA_BF16) return SQA_ERR_DTYPE;
@@ -1187,7 +1351,7 @@ static sqa_status decode_prepare(const void* q, const void* k_new, const void* v
                   (int64_t)c.blocks_per_unit * SQA_BLOCK_SLOTS < (c.budget < c.capacity ? c.budget : c.capacity)))
       return SQA_ERR_SHAPE;
   }
-  const sqa_status ps = plan_call(dt, B, Hq, Hkv, D, h2o, layers, n_layers, plan, lds_out);
+  const sqa_status ps = plan_call(dt, B, Hq, Hkv, D, h2o, layers, n_layers, coarse, plan, lds_out);
   if (ps != SQA_OK) return ps;
   *fn_out = pick(dt, D, g, h2o, paged);
   return SQA_OK;
@@ -1213,14 +1377,7 @@ static sqa_status decode_launch(decode_fn fn, const DecodePlan& plan, size_t lds
   a.lds_chunk = plan.lds_chunk;
   a.lds_chunk_w = plan.lds_chunk_w;
   a.scale_log2 = (float)(1.4426950408889634 / sqrt((double)D));
-  // long units first: layers in descending budget (stable)
-  for (int i = 0; i < n_layers; ++i) a.order[i] = (uint8_t)i;
-  for (int i = 1; i < n_layers; ++i) {
-    const uint8_t x = a.order[i];
-    int j = i - 1;
-    while (j >= 0 && layers[a.order[j]].budget < layers[x].budget) { a.order[j + 1] = a.order[j]; --j; }
-    a.order[j + 1] = x;
-  }
+  memcpy(a.order, plan.order, (size_t)n_layers);
   uint64_t run = 0;
   for (int i = 0; i < n_layers; ++i) {
     const int l = a.order[i];
@@ -1260,7 +1417,7 @@ extern "C" sqa_status sqa_decode_plan(const sqa_layer_cache* layers, int n_layer
   if (!pick(dt, D, Hq / Hkv, h2o, layers[0].block_table != nullptr)) return SQA_ERR_SHAPE;
   DecodePlan plan;
   size_t lds = 0;
-  const sqa_status ps = plan_call(dt, B, Hq, Hkv, D, h2o, layers, n_layers, &plan, &lds);
+  const sqa_status ps = plan_call(dt, B, Hq, Hkv, D, h2o, layers, n_layers, false, &plan, &lds);
   if (ps != SQA_OK) return ps;
   info->workgroups = (int64_t)plan.blocks;
   info->workspace_bytes = (int64_t)plan.bytes;
@@ -1290,10 +1447,14 @@ extern "C" sqa_status sqa_decode_step_ex(const void* q, const void* k_new, const
   DecodePlan plan;
   size_t lds = 0;
   const sqa_status ps = decode_prepare(q, k_new, v_new, dt, B, Hq, Hkv, D, new_pos, policy, n_sink, layers, n_layers, out,
-                                       opts, &fn, &plan, &lds);
+                                       opts, false, &fn, &plan, &lds);
   if (ps != SQA_OK) return ps;
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return SQA_ERR_SHAPE;
-  if (ws_bytes < plan.bytes) return SQA_ERR_CAPACITY;
+  if (ws_bytes < plan.bytes) {                     // (units cut into fewer pieces need less)
+    const sqa_status cs = plan_call(dt, B, Hq, Hkv, D, policy == SQA_H2O, layers, n_layers, true, &plan, &lds);
+    if (cs != SQA_OK) return cs;
+    if (ws_bytes < plan.bytes) return SQA_ERR_CAPACITY;
+  }
   char* ws = static_cast<char*>(workspace);
   DecodeScratch sc;
   sc.status = reinterpret_cast<int32_t*>(ws);
@@ -1363,11 +1524,17 @@ extern "C" sqa_status sqa_decode_step_static(const void* q, const void* k_new, c
   DecodePlan plan;
   size_t lds = 0;
   const sqa_status ps = decode_prepare(q, k_new, v_new, dt, B, Hq, Hkv, D, new_pos, policy, n_sink, layers, n_layers, out,
-                                       opts, &fn, &plan, &lds);
+                                       opts, false, &fn, &plan, &lds);
   if (ps != SQA_OK) return ps;
-  // beyond the array's fixed size: refused, nothing is enqueued (use sqa_decode_step with a workspace)
+  // beyond the array's fixed size even with units cut into fewer pieces: refused, nothing is enqueued (use
+  // sqa_decode_step with a workspace)
+  auto too_large = [&] { return plan.cnt_bytes > kStaticCntBytes || align256(plan.part_bytes) + plan.logit_bytes > kStaticDataBytes; };
+  if (too_large()) {
+    const sqa_status cs = plan_call(dt, B, Hq, Hkv, D, policy == SQA_H2O, layers, n_layers, true, &plan, &lds);
+    if (cs != SQA_OK) return cs;
+    if (too_large()) return SQA_ERR_CAPACITY;
+  }
   const size_t part_bytes = align256(plan.part_bytes);
-  if (plan.cnt_bytes > kStaticCntBytes || part_bytes + plan.logit_bytes > kStaticDataBytes) return SQA_ERR_CAPACITY;
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* base = nullptr;
   const sqa_status bs = static_scratch_base(st, &base);

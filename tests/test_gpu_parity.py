@@ -13,7 +13,7 @@ from oracle import sqa_oracle as O
 from oracle import pipeline as OP
 from paper_2404_04793_amd import workloads as W
 from tests.harness import (TOL, check_scores_after_run, check_step_scores, clustering_margin, export_state, import_state,
-                           near_tie_swap, np64, rel_err, round_scores_f32, uses_matrix_cores)
+                           near_tie_swap, np64, oracle_view, rel_err, round_scores_f32, uses_matrix_cores)
 
 pytestmark = pytest.mark.gpu
 
@@ -793,6 +793,47 @@ def test_units_longer_than_any_lds_list(sqa, policy, P, b):
     assert sqa.read_device_status(ws) == 0
     n = len(c2["pos"])
     assert sqa.kept_idx_sorted(caches, 0)[0, 0, :n].cpu().tolist() == c2["pos"].tolist()
+
+
+@pytest.mark.parametrize("order", ["evict_then_attend", "attend_then_evict"])
+@pytest.mark.parametrize("dtype,D,g,b", [("f32", 64, 1, 1409), ("f32", 128, 8, 700), ("bf16", 128, 1, 3001), ("bf16", 64, 2, 1290),
+                                         ("bf16", 128, 4, 2750), ("bf16", 128, 8, 4100)])
+@pytest.mark.parametrize("flat", [False, True], ids=["", "ties"])
+def test_a_unit_in_many_pieces(sqa, dtype, D, g, b, order, flat):
+    """One unit cut into 4 to 18 pieces (numbers that are and are not multiples of 8, a last piece of few slots):
+    outputs, scores and the tokens kept over several steps.  flat: equal keys and scores, so that every heavy
+    hitter ties for the lowest score and the highest position has to go."""
+    S, P = 3, b + 40
+    gen = torch.Generator(device="cpu").manual_seed(b)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    mk = lambda *shape: torch.randn(*shape, generator=gen).to(dt).to(DEV)
+    K, V = mk(1, 1, P, D), mk(1, 1, P, D)
+    sc = torch.rand(1, 1, P, generator=gen) + 0.5
+    if flat:
+        K.zero_()
+        sc.fill_(1.0)
+        sc[0, 0, P - (b - b // 2):] = 2.0            # the recent window: its leaver outlives the worst heavy hitter
+    sc = sc.to(DEV)
+    caches = _mk_caches(sqa, [b], [b], 1, 1, D, dtype)
+    sqa.prefill_compress(K, V, sc, "h2o", 4, caches, 0)
+    plan = sqa.decode_plan([b], [b], 1, g, 1, D, dtype, "h2o")
+    assert plan["layers"][0]["workgroups_per_unit"] >= 4
+    ws, less = sqa.decode_workspace(caches, g, "h2o"), torch.zeros(plan["workspace_bytes"] - 256, dtype=torch.uint8, device=DEV)
+    mf = uses_matrix_cores(dtype, D, g)
+    for t in range(S):
+        q, k, v = mk(1, 1, g, D), mk(1, 1, 1, D), mk(1, 1, 1, D)
+        if flat:
+            k.zero_()
+        before = export_state(caches, 0, 0, 0)
+        out = torch.empty_like(q)
+        # (in between with less scratch than the cut above needs: fewer pieces, unless there are none fewer)
+        w = less if t == 1 and not mf else ws
+        sqa.decode_step(q, k, v, P + t, "h2o", 4, caches, out, w, opts=sqa.batch_opts(order=order))
+        want, c2 = O.decode_step(oracle_view(before), np64(q)[0, 0], np64(k)[0, 0, 0], np64(v)[0, 0, 0], P + t, b, "h2o", 4, order=order)
+        got = export_state(caches, 0, 0, 0)
+        assert got["pos"].tolist() == c2["pos"].tolist(), t
+        assert rel_err(np64(out)[0, 0], want) < TOL[dtype]
+        check_step_scores(got, before, c2, mf, (t,))
 
 
 def test_decode_is_deterministic_and_per_layer_calls_agree(sqa):
