@@ -1,5 +1,7 @@
 // Prefill compression (Algorithm 1 steps 12 + 16-17 applied to the prompt) and
-// the sorted kept-index view.  One workgroup per (sequence, KV head) unit:
+// the sorted kept-index view.  One workgroup per (sequence, KV head) unit, or
+// several that each copy a part of its rows where the units are too few to fill
+// the chip (every one of them makes the selection for itself):
 //   select  sliding / streaming: index arithmetic on the position;
 //           H2O: the floor(b/2) largest accumulated scores among the non-recent
 //           tokens by an LDS radix select (4 passes of 8 bits over the fp32 bit
@@ -11,11 +13,17 @@
 // HBM traffic per unit: P scores (H2O) + read and write of the kept rows.
 #include "sqa_common.h"
 #include <algorithm>
+#include <type_traits>
 
 namespace sqa {
 
 constexpr int kCmpThreads = 256;
 constexpr int kCmpWaves = kCmpThreads / SQA_WAVE;
+constexpr int kCmpRows = 4;             // rows of K and of V that a thread has in flight
+constexpr int64_t kCmpFill = 384;         // workgroups that a call with few units is cut into
+constexpr int64_t kCmpCUs = 256;
+constexpr int64_t kCmpMany = 16384;           // units of a launch from which on the variant for many is used
+constexpr int64_t kCmpMaxParts = 256;         // workgroups per unit
 constexpr int kKeysInLdsMax = 16384;     // scores staged in LDS up to this many candidates
 
 __device__ __forceinline__ uint32_t score_key(float s) {
@@ -67,17 +75,25 @@ struct CompressBatch {
   const int32_t* budget_seq;    // [n_layers][B]
   int32_t* status;
   int B, Hkv;
+  uint32_t parts[kCmpBatch];    // workgroups per unit
   uint8_t layer[kCmpBatch];     // which layer of the call a slot of this launch holds (row of budget_seq)
 };
 static_assert(SQA_MAX_LAYERS <= 256, "CompressBatch::layer holds a layer index in 8 bits");
 
-template <typename T, int D>
+// MANY: so many units that what counts is how little each one does (one workgroup per unit, two rows in flight per
+// thread); otherwise a unit may be shared out, four rows are in flight, and many candidates are listed in runs.
+template <typename T, int D, bool MANY>
 __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
     const CompressBatch batch, int P /*prompt rows per unit in memory*/, int policy, int n_sink, int lds_words /*dynamic LDS of the launch, in 32-bit words*/) {
-  const sqa_layer_cache L = batch.L[blockIdx.y];
-  const T* __restrict__ K = static_cast<const T*>(batch.K[blockIdx.y]);
-  const T* __restrict__ V = static_cast<const T*>(batch.V[blockIdx.y]);
-  const float* __restrict__ scores = batch.scores[blockIdx.y];
+  const int li = blockIdx.y;              // slot of this launch: a layer
+  const uint32_t parts = MANY ? 1u : batch.parts[li];
+  int part = 0, u = blockIdx.x;
+  if (parts > 1) { part = (int)(blockIdx.x % parts); u = (int)(blockIdx.x / parts); }
+  if (!MANY && u >= batch.B * batch.Hkv) return;           // (the grid is made for the layer with the most parts)
+  const sqa_layer_cache L = batch.L[li];
+  const T* __restrict__ K = static_cast<const T*>(batch.K[li]);
+  const T* __restrict__ V = static_cast<const T*>(batch.V[li]);
+  const float* __restrict__ scores = batch.scores[li];
   constexpr int ROWB = D * (int)sizeof(T);
   constexpr int LPR = ROWB / 16;
   extern __shared__ uint32_t s_mem[];
@@ -86,7 +102,6 @@ __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
   __shared__ uint32_t s_sel[2];           // threshold key, how many equal keys to take
 
   const int tid = threadIdx.x;
-  const int u = blockIdx.x;
   const int bidx = u / batch.Hkv;
   const int64_t uoff = L.unit_offset ? L.unit_offset[u] : (int64_t)u * L.capacity;   // the unit's first slot
   const int cap = L.unit_offset ? (int)(L.unit_offset[u + 1] - uoff) : L.capacity;
@@ -94,11 +109,11 @@ __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
   int b = L.budget;
   if (batch.prompt_len || batch.budget_seq) {
     if (batch.prompt_len) P = batch.prompt_len[bidx];
-    if (batch.budget_seq) b = batch.budget_seq[(int64_t)batch.layer[blockIdx.y] * batch.B + bidx];
+    if (batch.budget_seq) b = batch.budget_seq[(int64_t)batch.layer[li] * batch.B + bidx];
     const int min_budget = policy == SQA_H2O ? 2 : (policy == SQA_STREAMING ? n_sink + 1 : 1);
     const bool bad_len = P < 0 || P > P_pad, bad_budget = b < min_budget || b > L.budget;
     if (bad_len || bad_budget) {                           // leave the unit empty and say why
-      if (tid == 0) {
+      if (tid == 0 && part == 0) {
         *reinterpret_cast<int4*>(L.unit_state + (int64_t)u * SQA_ST_WORDS) = make_int4(0, 0, -2, 0);
         if (batch.status) *batch.status = bad_len ? SQA_ERR_SHAPE : SQA_ERR_BUDGET;
       }
@@ -113,7 +128,7 @@ __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
     const int nblk = (min(n_keep, cap) + SQA_BLOCK_SLOTS - 1) / SQA_BLOCK_SLOTS;
     for (int i = tid; i < nblk; i += kCmpThreads) bad |= (unsigned)tbl[i] >= (unsigned)L.n_blocks;
     if (__syncthreads_or(bad)) {                           // a block number outside the pools: touch nothing
-      if (tid == 0) {
+      if (tid == 0 && part == 0) {
         *reinterpret_cast<int4*>(L.unit_state + (int64_t)u * SQA_ST_WORDS) = make_int4(0, 0, -2, 0);
         if (batch.status) *batch.status = SQA_ERR_SHAPE;
       }
@@ -121,7 +136,7 @@ __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
     }
   }
   if (n_keep > cap) {                                      // packed units: this one was given too few slots
-    if (tid == 0) {
+    if (tid == 0 && part == 0) {
       *reinterpret_cast<int4*>(L.unit_state + (int64_t)u * SQA_ST_WORDS) = make_int4(0, 0, -2, 0);
       if (batch.status) *batch.status = SQA_ERR_CAPACITY;
     }
@@ -180,8 +195,26 @@ __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
     thr = prefix; take_eq = (uint32_t)k;
   }
 
-  // keep flags of the candidates -> their order among the chosen, in position order, 256 positions at a time
-  if (hh > 0) {
+  // keep flags of the candidates -> their order among the chosen, in position order
+  if (!MANY && hh > 0 && keys_in_lds && M > 4 * kCmpThreads) {
+    // Every thread takes a run of positions (an odd number of them: no bank conflicts): counts, prefix
+    // sums over the threads, then the list.  (256 positions at a time, each with two counts over the workgroup, took half of
+    // the selection: 24 barriers for 1500 candidates.)
+    int run = (M + kCmpThreads - 1) / kCmpThreads;
+    run |= 1;
+    const int lo = min(tid * run, M), hi = min(lo + run, M);
+    int above = 0, equal = 0;
+    for (int i = lo; i < hi; ++i) { const uint32_t key = s_keys[i]; above += key > thr; equal += key == thr; }
+    const int eq_before = block_incl_sum(equal, s_wave_tot) - equal;
+    int slot = block_incl_sum(above, s_wave_tot) - above + min(eq_before, (int)take_eq);
+    int eq_rank = eq_before;
+    for (int i = lo; i < hi; ++i) {
+      const uint32_t key = s_keys[i];
+      if (key > thr || (key == thr && eq_rank++ < (int)take_eq)) s_idx[slot++] = i;
+    }
+    __syncthreads();
+  } else if (hh > 0) {
+    // Few candidates, or more than are staged (their scores are then read in order): 256 positions at a time.
     int eq_seen = 0, kept_seen = 0;
     for (int base = 0; base < M; base += kCmpThreads) {
       const int i = base + tid;
@@ -211,30 +244,38 @@ __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
   auto row_of = [&](int j) -> int64_t { return tbl ? (int64_t)tbl[j / SQA_BLOCK_SLOTS] * SQA_BLOCK_SLOTS + j % SQA_BLOCK_SLOTS : (int64_t)j; };
   const int grp = tid / LPR, c = tid % LPR;
   constexpr int GROUPS = kCmpThreads / LPR;
-  for (int j = grp; j < n_keep; j += 2 * GROUPS) {
-    const int j2 = j + GROUPS;
-    const int src = source(j);
-    const int src2 = j2 < n_keep ? source(j2) : src;
-    const uint4 k1 = ld16(reinterpret_cast<const char*>(Ku) + (int64_t)src * ROWB + c * 16);
-    const uint4 v1 = ld16(reinterpret_cast<const char*>(Vu) + (int64_t)src * ROWB + c * 16);
-    const uint4 k2 = ld16(reinterpret_cast<const char*>(Ku) + (int64_t)src2 * ROWB + c * 16);
-    const uint4 v2 = ld16(reinterpret_cast<const char*>(Vu) + (int64_t)src2 * ROWB + c * 16);
-    const int64_t d1 = row_of(j);
-    st16(Kc + d1 * ROWB + c * 16, k1);
-    st16(Vc + d1 * ROWB + c * 16, v1);
-    if (j2 < n_keep) {
-      const int64_t d2 = row_of(j2);
-      st16(Kc + d2 * ROWB + c * 16, k2);
-      st16(Vc + d2 * ROWB + c * 16, v2);
+  // this workgroup's share of the slots
+  const int share = parts > 1 ? (n_keep + (int)parts - 1) / (int)parts : n_keep;
+  const int j_lo = MANY ? 0 : min(part * share, n_keep), j_hi = MANY ? n_keep : min(j_lo + share, n_keep);
+  // R rows of K and of V in flight per thread (beyond the end: the first once more, not stored)
+  auto copy_rows = [&](int j, auto rows_tag) {
+    constexpr int R = decltype(rows_tag)::value;
+    uint4 kr[R], vr[R];
+#pragma unroll
+    for (int x = 0; x < R; ++x) {
+      const int64_t src = source(j + x * GROUPS < j_hi ? j + x * GROUPS : j);
+      kr[x] = ld16(reinterpret_cast<const char*>(Ku) + src * ROWB + c * 16);
+      vr[x] = ld16(reinterpret_cast<const char*>(Vu) + src * ROWB + c * 16);
     }
-  }
+#pragma unroll
+    for (int x = 0; x < R; ++x)
+      if (j + x * GROUPS < j_hi) {
+        const int64_t dst = row_of(j + x * GROUPS);
+        st16(Kc + dst * ROWB + c * 16, kr[x]);
+        st16(Vc + dst * ROWB + c * 16, vr[x]);
+      }
+  };
+  int j = j_lo + grp;
+  if constexpr (!MANY)
+    for (; j + (kCmpRows - 1) * GROUPS < j_hi; j += kCmpRows * GROUPS) copy_rows(j, std::integral_constant<int, kCmpRows>{});
+  for (; j < j_hi; j += 2 * GROUPS) copy_rows(j, std::integral_constant<int, 2>{});   // (short units: fewer rows asked for in vain)
   int32_t* posu = L.pos + uoff;
-  for (int j = tid; j < n_keep; j += kCmpThreads) {
-    const int src = source(j);
-    posu[j] = src;
-    if (L.score_acc) L.score_acc[uoff + j] = sc ? sc[src] : 0.f;
+  for (int i = j_lo + tid; i < j_hi; i += kCmpThreads) {
+    const int src = source(i);
+    posu[i] = src;
+    if (L.score_acc) L.score_acc[uoff + i] = sc ? sc[src] : 0.f;
   }
-  if (tid == 0) *reinterpret_cast<int4*>(L.unit_state + (int64_t)u * SQA_ST_WORDS) = make_int4(n_keep, 0, -2, 0);
+  if (tid == 0 && part == 0) *reinterpret_cast<int4*>(L.unit_state + (int64_t)u * SQA_ST_WORDS) = make_int4(n_keep, 0, -2, 0);
 }
 
 // out[rank of pos[i]] = pos[i]; -1 beyond len.  Rank by counting (a test view, O(n^2)).
@@ -264,14 +305,38 @@ __global__ __launch_bounds__(kCmpThreads) void kept_idx_sorted_kernel(sqa_layer_
 }
 
 template <typename T, int D>
-static hipError_t launch_compress(const CompressBatch& batch, int n, int P, int policy, int n_sink,
+static hipError_t launch_compress(CompressBatch& batch, int n, int P, int policy, int n_sink,
                                    unsigned units, size_t lds, hipStream_t st) {
-  auto fn = prefill_compress_kernel<T, D>;
+  // A unit's rows are shared out among workgroups where one per unit leaves CUs idle (fewer units than CUs) or busy for
+  // long after the others (fewer than two per CU, and the longest has more than 1.5 times a CU's share of the rows):
+  // as many pieces as bring the launch to 384 equal workgroups, of at least one trip of the copy loop each.  One
+  // sequence joining with 8 heads, 26 layers of 301 and 6 of 1777 rows, 73 -> 35 us (51 with 256 workgroups, 35 with
+  // 512); 8 layers, 16 units each, up to 3439 of 8192 rows, 149 -> 80.  256 units of 2048 rows: 111 whole, 113 in two.
+  constexpr int64_t trip = kCmpRows * (kCmpThreads / (D * (int)sizeof(T) / 16));
+  int64_t rows = 0, longest = 0;
+  for (int i = 0; i < n; ++i) {
+    const int64_t keep = P < batch.L[i].budget ? P : batch.L[i].budget;
+    rows += (int64_t)units * keep;
+    longest = keep > longest ? keep : longest;
+  }
+  const int64_t share = rows / kCmpFill > trip ? rows / kCmpFill : trip;
+  const bool shared_out = (int64_t)units * n < kCmpCUs || ((int64_t)units * n < 2 * kCmpCUs && 2 * longest * kCmpCUs > 3 * rows);
+  uint32_t most = 1;
+  for (int i = 0; i < n; ++i) {
+    const int64_t keep = P < batch.L[i].budget ? P : batch.L[i].budget;
+    int64_t parts = shared_out ? (keep + share - 1) / share : 1;
+    parts = parts < kCmpMaxParts ? parts : kCmpMaxParts;
+    batch.parts[i] = (uint32_t)parts;
+    most = batch.parts[i] > most ? batch.parts[i] : most;
+  }
+  // (224 sequences of 512 tokens, 35 rows kept in most layers: 1 % slower with the other variant; 22 layers of 160 units
+  // 371 us with this one, 360 with the other)
+  auto fn = (int64_t)units * n >= kCmpMany ? prefill_compress_kernel<T, D, true> : prefill_compress_kernel<T, D, false>;
   if (lds > 48 * 1024) {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(fn), lds);
     if (e != hipSuccess) return e;
   }
-  fn<<<dim3(units, n), kCmpThreads, lds, st>>>(batch, P, policy, n_sink, (int)(lds / sizeof(uint32_t)));
+  fn<<<dim3(units * most, n), kCmpThreads, lds, st>>>(batch, P, policy, n_sink, (int)(lds / sizeof(uint32_t)));
   return hipGetLastError();
 }
 

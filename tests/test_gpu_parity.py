@@ -260,6 +260,41 @@ def test_prefill_compress(sqa, policy, dtype, B, Hkv, P, D, b, blocked):
                 assert np.array_equal(got["score"], want["score"])
 
 
+@pytest.mark.parametrize("blocked", [False, True], ids=["dense", "blocked"])
+@pytest.mark.parametrize("dtype,D,P,budgets", [("bf16", 128, 1400, [100, 1287, 1399]), ("f32", 64, 2305, [641, 2304, 3000]),
+                                               ("f32", 128, 1100, [33, 64, 65]), ("bf16", 64, 17000, [1031, 6]),
+                                               # 300 units: between one and two per CU, shared out for the long layer only
+                                               ("bf16", 128, 400, [8] * 49 + [390])])
+def test_prefill_compress_units_shared_out(sqa, dtype, D, P, budgets, blocked):
+    """Few units, so that several workgroups copy a unit's rows (shares with and without remainders, more workgroups
+    than a share needs), and more than 1024 candidates with many equal scores (each thread lists a run of
+    positions), below and above the number whose scores are staged; sequences of different length and budget."""
+    B, Hkv = (2, 2) if len(budgets) < 10 else (3, 2)
+    n = len(budgets)
+    gen = torch.Generator(device="cpu").manual_seed(P)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    plen = [P, P - P // 3, 1][:B]
+    bseq = [[b, max(2, b // 2), 2][:B] for b in budgets]
+    Ks = [torch.randn(B, Hkv, P, D, generator=gen).to(dt).to(DEV) for _ in range(n)]
+    Vs = [torch.randn(B, Hkv, P, D, generator=gen).to(dt).to(DEV) for _ in range(n)]
+    Ss = [(torch.randint(0, 40, (B, Hkv, P), generator=gen).float() / 16).to(DEV) for _ in range(n)]
+    i32 = lambda x: torch.tensor(x, dtype=torch.int32, device=DEV)
+    status, pl, bs = i32([0]), i32(plen), i32(bseq)
+    for opts in (None, sqa.batch_opts(prompt_len=pl, budget_seq=bs, status=status)):
+        caches = _mk_caches(sqa, budgets, [min(P, b) for b in budgets], B, Hkv, D, dtype, blocked=blocked)
+        sqa.prefill_compress_layers(Ks, Vs, Ss, "h2o", 4, caches, opts=opts)
+        for l in (range(n) if n < 10 else (0, 48, 49)):
+            for b in range(B):
+                p, bud = (P, budgets[l]) if opts is None else (plen[b], bseq[l][b])
+                for h in range(Hkv):
+                    want = O.prefill_compress(np64(Ks[l])[b, h, :p], np64(Vs[l])[b, h, :p], np64(Ss[l])[b, h, :p], bud, "h2o", 4)
+                    got = export_state(caches, l, b, h)
+                    assert got["pos"].tolist() == want["pos"].tolist(), (l, b, h)
+                    assert all(np.array_equal(got[f], want[f]) for f in ("K", "V", "score")), (l, b, h)
+                    assert caches.state[l][b, h].tolist() == [len(want["pos"]), 0, -2, 0]
+    assert int(status) == 0
+
+
 def test_prefill_compress_layers_matches_single_layer_calls(sqa):
     """One launch over 35 layers with different budgets (two batches of kernel arguments) == 35 calls."""
     B, Hkv, P, D, L = 2, 2, 300, 128, 35
