@@ -57,6 +57,10 @@ __device__ __forceinline__ void st16(void* p, uint4 v) {
   *(g_v4u_t*)(p) = v4u_t{v.x, v.y, v.z, v.w};
 }
 
+__device__ __forceinline__ void st16_nt(void* p, uint4 v) {
+  __builtin_nontemporal_store(v4u_t{v.x, v.y, v.z, v.w}, (g_v4u_t*)(p));
+}
+
 template <typename T> __device__ __forceinline__ T wave_sum(T v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, SQA_WAVE);

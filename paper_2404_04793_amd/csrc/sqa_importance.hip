@@ -59,8 +59,8 @@ template <> struct Residual<bf16_t> {
   }
 };
 
-// FUSE = false: h_out is read.  FUSE = true: `other` is attn_out and h_out is written.
-template <typename T, bool FUSE>
+// FUSE = false: h_out is read.  FUSE = true: `other` is attn_out and h_out is written (NT: non-temporally).
+template <typename T, bool FUSE, bool NT = false>
 __global__ __launch_bounds__(kImpThreads) void importance_partial_kernel(
     const T* h_in, const T* other, T* h_out_w /*may be h_in or other*/, int64_t n_tokens, int hidden,
     const int32_t* __restrict__ seq_start /*[gridDim.z + 1] or NULL*/,
@@ -85,6 +85,7 @@ __global__ __launch_bounds__(kImpThreads) void importance_partial_kernel(
     row_lo = row_lo < 0 ? 0 : row_lo;
     row_hi = row_hi > n_tokens ? n_tokens : row_hi;
   }
+  auto put = [](char* p, const uint4& v) { if constexpr (NT) st16_nt(p, v); else st16(p, v); };
   double wave_cos = 0.0;
   for (int64_t row = row_lo + (int64_t)blockIdx.x * kImpWaves + wave; row < row_hi; row += stride) {
     const char* a = A + row * row_bytes;
@@ -104,8 +105,8 @@ __global__ __launch_bounds__(kImpThreads) void importance_partial_kernel(
       if (FUSE) {
         b0 = Residual<T>::add(a0, b0); b1 = Residual<T>::add(a1, b1);
         b2 = Residual<T>::add(a2, b2); b3 = Residual<T>::add(a3, b3);
-        st16(w + (int64_t)c * 16, b0); st16(w + (int64_t)(c + SQA_WAVE) * 16, b1);
-        st16(w + (int64_t)(c + 2 * SQA_WAVE) * 16, b2); st16(w + (int64_t)(c + 3 * SQA_WAVE) * 16, b3);
+        put(w + (int64_t)c * 16, b0); put(w + (int64_t)(c + SQA_WAVE) * 16, b1);
+        put(w + (int64_t)(c + 2 * SQA_WAVE) * 16, b2); put(w + (int64_t)(c + 3 * SQA_WAVE) * 16, b3);
       }
       Dots<T>::acc(a0, b0, ab, aa, bb); Dots<T>::acc(a1, b1, ab, aa, bb);
       Dots<T>::acc(a2, b2, ab, aa, bb); Dots<T>::acc(a3, b3, ab, aa, bb);
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(kImpThreads) void importance_partial_kernel(
     for (; c < chunks; c += SQA_WAVE) {
       const uint4 a0 = ld16_nt(a + (int64_t)c * 16);
       uint4 b0 = ld16_nt(b + (int64_t)c * 16);
-      if (FUSE) { b0 = Residual<T>::add(a0, b0); st16(w + (int64_t)c * 16, b0); }
+      if (FUSE) { b0 = Residual<T>::add(a0, b0); put(w + (int64_t)c * 16, b0); }
       Dots<T>::acc(a0, b0, ab, aa, bb);
     }
     ab = wave_sum(ab); aa = wave_sum(aa); bb = wave_sum(bb);
@@ -130,15 +131,34 @@ __global__ __launch_bounds__(kImpThreads) void importance_partial_kernel(
   }
 }
 
-// one wave per (layer, sequence): blockIdx.x = layer * n_seq + sequence
-__global__ __launch_bounds__(SQA_WAVE) void importance_final_kernel(
+// one workgroup per (layer, sequence): blockIdx.x = layer * n_seq + sequence.  All of its partial sums are requested
+// at once and added in a fixed order (one wave that took 16 turns for 1024 of them: 5.8 us; 16384 rows of 4096 bf16
+// in one layer, both kernels: 45.9 -> 42.3 us, inside the residual add 71.5 -> 68.0).  64 threads for up to 256.
+__global__ __launch_bounds__(kImpThreads) void importance_final_kernel(
     const double* __restrict__ partial, int n_part, int64_t n_tokens, const int32_t* __restrict__ seq_start, int n_seq,
     float* __restrict__ cos_out) {
   const int item = blockIdx.x;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & (SQA_WAVE - 1);
+  constexpr int N = 4;                            // >= n_part / threads
+  double v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int at = threadIdx.x + i * blockDim.x;
+    v[i] = partial[(int64_t)item * n_part + min(at, n_part - 1)];
+    v[i] = at < n_part ? v[i] : 0.0;
+  }
   double s = 0.0;
-  for (int i = lane; i < n_part; i += SQA_WAVE) s += partial[(int64_t)item * n_part + i];
+#pragma unroll
+  for (int i = 0; i < N; ++i) s += v[i];
   s = wave_sum(s);
+  if (blockDim.x > SQA_WAVE) {
+    __shared__ double s_wave[kImpWaves];
+    if (lane == 0) s_wave[threadIdx.x / SQA_WAVE] = s;
+    __syncthreads();
+    s = 0.0;
+    for (int w = 0; w < kImpWaves; ++w) s += s_wave[w];
+  }
+  if (threadIdx.x != 0) return;
   int64_t rows = n_tokens;
   if (seq_start) {
     const int q = item % n_seq;
@@ -147,7 +167,7 @@ __global__ __launch_bounds__(SQA_WAVE) void importance_final_kernel(
     hi = hi > n_tokens ? n_tokens : hi;
     rows = hi - lo;
   }
-  if (lane == 0) cos_out[item] = rows > 0 ? (float)(s / (double)rows) : 0.f;
+  cos_out[item] = rows > 0 ? (float)(s / (double)rows) : 0.f;
 }
 
 static int imp_blocks(int64_t n_tokens) {
@@ -179,21 +199,28 @@ static sqa_status launch_importance(const void* h_in, const void* other, void* h
   const int nblk = imp_blocks(n_tokens);
   double* partial = static_cast<double*>(workspace);
   dim3 grid(nblk, n_layers, n_seq);
+  // h_out is stored non-temporally where it is larger than the 256 MB Infinity Cache: nothing of it would be found
+  // there again (16 layers of 4096 x 4096 bf16, 537 MB: 304 us, 285 so); below that plain stores are absorbed by the
+  // cache and found by the next kernel (16384 x 4096, 134 MB: 68 us, 74 so).
+  const bool nt = fuse && (int64_t)n_layers * n_tokens * hidden * (dt == SQA_F32 ? 4 : 2) >= ((int64_t)256 << 20);
   if (dt == SQA_F32) {
     const float* a = static_cast<const float*>(h_in);
     const float* b = static_cast<const float*>(other);
     float* w = static_cast<float*>(h_out_w);
-    if (fuse) importance_partial_kernel<float, true><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
+    if (nt) importance_partial_kernel<float, true, true><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
+    else if (fuse) importance_partial_kernel<float, true><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
     else importance_partial_kernel<float, false><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
   } else {
     const bf16_t* a = static_cast<const bf16_t*>(h_in);
     const bf16_t* b = static_cast<const bf16_t*>(other);
     bf16_t* w = static_cast<bf16_t*>(h_out_w);
-    if (fuse) importance_partial_kernel<bf16_t, true><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
+    if (nt) importance_partial_kernel<bf16_t, true, true><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
+    else if (fuse) importance_partial_kernel<bf16_t, true><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
     else importance_partial_kernel<bf16_t, false><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
   }
   SQA_HIP_CHECK(hipGetLastError());
-  importance_final_kernel<<<n_layers * n_seq, SQA_WAVE, 0, st>>>(partial, nblk, n_tokens, seq_start, n_seq, cos_out);
+  static_assert(kImpMaxBlocks <= 4 * kImpThreads, "partial sums per thread of the final kernel");
+  importance_final_kernel<<<n_layers * n_seq, nblk <= 4 * SQA_WAVE ? SQA_WAVE : kImpThreads, 0, st>>>(partial, nblk, n_tokens, seq_start, n_seq, cos_out);
   SQA_HIP_CHECK(hipGetLastError());
   return SQA_OK;
 }

@@ -77,6 +77,24 @@ def test_residual_add_importance(sqa, dtype, L, T, d, inplace):
         assert np.array_equal(alone.view(np.uint32), cos.astype(np.float32).view(np.uint32))
 
 
+@pytest.mark.parametrize("L,T,d", [(2, 1021, 64), (1, 1025, 128), (1, 4099, 64),      # 256, 257 and 1024 partial sums
+                                   (1, 32768, 4096), (2, 16383, 4096)])                # h_out of 256 MiB, and just below
+def test_residual_add_importance_store_forms(sqa, L, T, d):
+    """Stored sums bit for bit, and the same cosines as the probe of the stored values, around the number of partial
+    sums one wave adds up and around the size from which h_out is stored non-temporally."""
+    gen = torch.Generator(device=DEV).manual_seed(T)
+    a = torch.randn(L, T, d, device=DEV, generator=gen).bfloat16()
+    r = torch.randn(L, T, d, device=DEV, generator=gen).bfloat16()
+    h = torch.empty_like(a)
+    cos = sqa.residual_add_importance(a, r, h)
+    assert torch.equal(h, a + r)
+    assert torch.equal(cos, sqa.layer_importance(a, h))
+    x, y = a[:, :2000].double(), h[:, :2000].double()
+    part = sqa.layer_importance(a[:, :2000].contiguous(), h[:, :2000].contiguous()).double()
+    want = ((x * y).sum(-1) / (x.norm(dim=-1) * y.norm(dim=-1))).mean(-1)
+    assert float((part - want).abs().max()) < 1e-6       # fp32 products over at most 4096 elements, fp64 mean
+
+
 def test_tiny_budgets_from_gpu_cosines(sqa):
     wl = W.WORKLOADS["tiny"]
     hs = [W.hidden_states(wl, l, DEV) for l in range(wl.L)]
