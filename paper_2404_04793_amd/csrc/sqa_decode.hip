@@ -790,7 +790,7 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
     if (s_ctl[0] != nsplit - 1) return;
     // The merge: every record's statistics in one round trip, weights from LDS, then the accumulators, two values
     // per thread and eight records in flight.  (One lane group per head that walked the records one by one paid a
-    // round trip for each: 10.2 us for a unit in 13 pieces, 14 in 26; now 2.3 and 3.)
+    // round trip for each: 10.2 us for a unit in 13 pieces, 14 in 26; now 3.6 and 3.5.)
     static_assert(2 * kMaxSplit * G <= (MF ? kDecWaves * kStageBytesPerWave / 4 : kDecWaves * G * D), "records' statistics fit in LDS");
     float* const rec_m = acc_lds;                 // [nsplit][G] m_k, then the weights; nsplit <= kMaxSplit
     float* const rec_l = acc_lds + kMaxSplit * G;
@@ -880,7 +880,9 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
         if (!solo) __syncthreads();               // (a wave on its own reads back what it wrote itself: LDS keeps a wave's order)
       }
     }
-    // Every thread keeps its lowest heavy score and that slot, so that the decision needs no second walk.
+    // Every thread keeps its lowest heavy score and that slot, so that the decision needs no second walk.  What bounds
+    // this part is round trips: everything a trip needs is asked for before anything of it is used (4743 slots under 8
+    // heads, split: 19 us with loads inside the per-token branches, 8.5 so; 8192 slots, fp32: 21.5 and 13.5).
     float mn = INFINITY;
     int mn_slot = -1;
     bool mn_tie = false;
