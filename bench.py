@@ -32,11 +32,11 @@ HBM_PEAK_GBS = 8000.0
 # `traffic` is null and `traffic_source` says that the profile is out of date.
 MEASURED_TRAFFIC = {
     ("llama2_7b", "squeeze", "h2o", "all_layers", "dense"): {
-        "bytes": 820843.8 * 1024 * 2.0 + 19390.3 * 1024,
-        "source": "profiles/decode_importance_compress__llama2_7b.txt", "kernel_sha": "44c144312391cc67"},
+        "bytes": 820843.3 * 1024 * 2.0 + 19390.5 * 1024,
+        "source": "profiles/decode_importance_compress__llama2_7b.txt", "kernel_sha": "50701cad316c736c"},
     ("llama2_7b", "squeeze", "h2o", "all_layers", "blocked"): {
-        "bytes": 821419.7 * 1024 * 2.0 + 19387.9 * 1024,
-        "source": "profiles/decode_importance_compress__llama2_7b.txt", "kernel_sha": "44c144312391cc67"},
+        "bytes": 821419.7 * 1024 * 2.0 + 19388.1 * 1024,
+        "source": "profiles/decode_importance_compress__llama2_7b.txt", "kernel_sha": "50701cad316c736c"},
 }
 
 

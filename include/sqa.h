@@ -372,7 +372,8 @@ typedef struct sqa_decode_plan_info {
   int64_t workspace_bytes;  /* what the call uses of its workspace (<= sqa_decode_workspace_bytes)        */
   int32_t lds_bytes;        /* dynamic LDS per workgroup                                                  */
   int32_t matrix_cores;     /* 1: the MFMA variant runs (bf16, D = 128, 4 or 8 query heads per KV head)   */
-  int32_t wide_tail;        /* 1: so few workgroups that a long unit's score walk keeps all four waves    */
+  int32_t wide_tail;        /* 1: so few workgroups that a long unit's score walk keeps all four waves
+                               (0: only that of units over 768 tokens does, up to 2048 workgroups)        */
   int32_t table_entries;    /* blocked allocation: block numbers a workgroup stages in LDS (else 0)       */
 } sqa_decode_plan_info;
 typedef struct sqa_decode_layer_plan {

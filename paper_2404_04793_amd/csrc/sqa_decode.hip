@@ -68,7 +68,7 @@ struct DecodeArgs {
     uint32_t logit_off;   // first logit (floats)
   } lay[SQA_MAX_LAYERS];
   int lds_chunk_w;                     // row length of a wave's LDS logit buffer in one-wave-per-unit layers
-  int wide_tail;                       // the call has few workgroups: a long unit's tail keeps all four waves
+  int wide_tail;                       // an unsplit unit's tail keeps all four waves if it has more tokens than this (0: never)
   int lds_probs_w;                     // bytes of a wave's own LDS region for those probabilities in one-wave-per-unit layers
   int tbl_off;                         // blocked allocation: where in the dynamic LDS the unit's block numbers are staged (bytes)
 };
@@ -244,8 +244,12 @@ typedef short v4s_t __attribute__((ext_vector_type(4)));
 typedef short v8s_t __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) v4s_t* lds_v4s_ptr;
 constexpr int kWpuMaxSlots = 256;                 // one wave per unit: for units of at most this many slots
-constexpr int kSoloMaxTokens = 512;               // calls with few workgroups: an unsplit unit's tail (scores, decision) is left
-                                                  // to wave 0 alone up to this length
+// An unsplit unit's tail (scores, decision) is left to wave 0 alone, so that the registers of the other waves are free for
+// the next workgroup -- up to this length where there is hardly a next one (at most kWideTailMaxBlocks workgroups), up to
+// the other in calls of 2 to 8 workgroups per CU, whose long units otherwise end after everything else (Llama-2-7B shape at
+// batch 2, 32 layers in one call, 80.6 -> 75.2 us; 12 layers of 128 units of 300 to 1900 slots, D = 64, 55.8 -> 51.3; fp32,
+// 2 query heads over 1, up to 1500 slots, 99 -> 96).  Beyond: no better (batch 6) or worse (batch 8, 277 -> 283).
+constexpr int kSoloMaxTokens = 512, kSoloMaxTokensMid = 768;
 constexpr int kMaxSplit = 128;                    // work items per unit (their statistics are merged in the LDS of the waves' accumulators)
 constexpr int kLogitPad = 33;                     // a unit's H2O scratch region: G x (slots + kLogitPad) floats: the logit of the
                                                   // new token as one more slot, or whole 32-token tiles of bf16 probabilities
@@ -848,7 +852,7 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
   // (matrix-core H2O: the whole workgroup walks the unit's probabilities, unless each wave has a unit of its own)
   // (... except in a call with few workgroups, where nothing else would use the registers the other waves
   // free and a long unit's tail -- its scores are walked once more -- is on the critical path)
-  const bool solo = nsplit == 1 && (wpu || (!(MF && H2O) && !(a.wide_tail != 0 && n > kSoloMaxTokens)));
+  const bool solo = nsplit == 1 && (wpu || (!(MF && H2O) && !(a.wide_tail != 0 && n > a.wide_tail)));
   if (solo && !wpu && wave != 0) return;
   const int nthr = solo ? SQA_WAVE : kDecThreads;
   const int tq = solo ? lane : tid;               // this thread's place among the nthr threads still at work
@@ -1095,7 +1099,7 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // per CU come out unevenly (the busiest of 256 CUs with over 9/8 of its share): 96 units of 2271 slots 41 us in 3
 // pieces (288 items), 34.5 in 5; 130 units of 8192 with 286 of 557, 4 query heads over 1, 167 us and 140.
 constexpr int64_t kMinItems = 256;
-constexpr int64_t kWideTailMaxBlocks = 512;       // calls with at most this many workgroups: see DecodeArgs::wide_tail
+constexpr int64_t kWideTailMaxBlocks = 512, kWideTailMidBlocks = 2048;   // see kSoloMaxTokens
 // Matrix-core variant under H2O: LDS a workgroup may use for a unit's per-head probabilities so that three
 // workgroups still fit a CU (160 KiB / 3, less the four stage buffers and the small static arrays).
 constexpr int kLdsProbsMax = 18 * 1024;
@@ -1391,7 +1395,7 @@ static sqa_status decode_launch(decode_fn fn, const DecodePlan& plan, size_t lds
     a.lay[i].part_off = plan.part_off[i];
     a.lay[i].logit_off = plan.logit_off[i];
   }
-  a.wide_tail = plan.blocks <= (uint64_t)kWideTailMaxBlocks ? 1 : 0;
+  a.wide_tail = plan.blocks <= (uint64_t)kWideTailMaxBlocks ? kSoloMaxTokens : (plan.blocks <= (uint64_t)kWideTailMidBlocks ? kSoloMaxTokensMid : 0);
   a.lds_probs_w = plan.lds_probs_w;
   a.tbl_off = (int)(lds - (size_t)plan.tbl_entries * sizeof(int));
   if (layers_dev) {

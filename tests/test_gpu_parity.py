@@ -889,6 +889,35 @@ def test_a_unit_in_many_pieces(sqa, dtype, D, g, b, order, flat):
         check_step_scores(got, before, c2, mf, (t,))
 
 
+@pytest.mark.parametrize("order", ["evict_then_attend", "attend_then_evict"])
+@pytest.mark.parametrize("dtype,D,g,B,b", [("f32", 64, 1, 17, 769), ("f32", 64, 1, 17, 768), ("bf16", 128, 2, 20, 1030)])
+def test_long_whole_units_in_a_call_of_some_hundred_workgroups(sqa, dtype, D, g, B, b, order):
+    """544 and 640 whole units: the score walk of one over 768 tokens keeps all four waves, of a shorter one does not."""
+    Hkv, S, P = 32, 3, b + 20
+    gen = torch.Generator(device=DEV).manual_seed(b)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    mk = lambda *shape: torch.randn(*shape, generator=gen, device=DEV).to(dt)
+    K, V, sc = mk(B, Hkv, P, D), mk(B, Hkv, P, D), torch.rand(B, Hkv, P, generator=gen, device=DEV) + 0.5
+    caches = _mk_caches(sqa, [b], [b], B, Hkv, D, dtype)
+    sqa.prefill_compress(K, V, sc, "h2o", 4, caches, 0)
+    plan = sqa.decode_plan([b], [b], B, Hkv * g, Hkv, D, dtype, "h2o")
+    assert 512 < plan["workgroups"] <= 2048 and plan["layers"][0]["workgroups_per_unit"] == 1
+    ws = sqa.decode_workspace(caches, Hkv * g, "h2o")
+    for t in range(S):
+        q, k, v = mk(1, B, Hkv * g, D), mk(1, B, Hkv, D), mk(1, B, Hkv, D)
+        units = [(0, 0), (B // 2, 7), (B - 1, Hkv - 1)]
+        before = [export_state(caches, 0, x, h) for x, h in units]
+        out = torch.empty_like(q)
+        sqa.decode_step(q, k, v, P + t, "h2o", 4, caches, out, ws, opts=sqa.batch_opts(order=order))
+        for (x, h), c in zip(units, before):
+            want, c2 = O.decode_step(oracle_view(c), np64(q)[0, x, h * g:(h + 1) * g], np64(k)[0, x, h], np64(v)[0, x, h], P + t, b,
+                                     "h2o", 4, order=order)
+            got = export_state(caches, 0, x, h)
+            assert got["pos"].tolist() == c2["pos"].tolist(), (t, x, h)
+            assert rel_err(np64(out)[0, x, h * g:(h + 1) * g], want) < TOL[dtype]
+            check_step_scores(got, c, c2, False, (t, x, h))
+
+
 def test_decode_is_deterministic_and_per_layer_calls_agree(sqa):
     """Same inputs twice -> identical bytes; one call over all layers == one call per layer
     (with and without the device copy of the layer table)."""
