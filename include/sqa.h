@@ -231,7 +231,8 @@ sqa_status sqa_prefill_scores_ex(const void* Q, const void* K, sqa_dtype dt,
  * attention kernel that runs the prompt returns, per query row, the logarithm of its normaliser, and with it
  * the column sums need one pass over the logits instead of two (half the work of sqa_prefill_scores).
  *   row_lse : DEVICE float [B][Hq][P], row_lse[b][h][i] = ln sum_{j<=i} exp(Q_i.K_j / sqrt(D))
- *             (natural logarithm, logits already scaled by 1/sqrt(D), causal); rows of padding are not read
+ *             (natural logarithm, logits already scaled by 1/sqrt(D), causal); those of padding count
+ *             nothing.  May lie in the memory of scores_out, or of the workspace (not of both)
  * Everything else, the workspace included, as for sqa_prefill_scores_ex.  The values are trusted: a wrong
  * normaliser gives wrong scores, not an error. */
 sqa_status sqa_prefill_scores_lse(const void* Q, const void* K, const float* row_lse, sqa_dtype dt,

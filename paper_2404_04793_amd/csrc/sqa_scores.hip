@@ -454,6 +454,11 @@ __global__ __launch_bounds__(256) void sum_heads_kernel(const float* __restrict_
   scores[i] = t;
 }
 
+// the caller's normalisers, where they lie in memory that the call writes
+__global__ __launch_bounds__(256) void copy_lse_kernel(const float* __restrict__ lse, int64_t n, float* __restrict__ out) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) out[i] = lse[i];
+}
+
 typedef void (*score_fn)(const ScoreArgs);
 template <typename T, int D, int NB> score_fn pick_rowstats() {
   if constexpr (sizeof(T) == 2 && D == 128 && NB == 2) return score_rowstats_mfma_kernel;
@@ -529,12 +534,22 @@ static sqa_status prefill_scores_impl(const void* Q, const void* K, const float*
   a.inv = ws + rows;
   a.out = nullptr;
   float* part = lse ? ws : (ws_bytes >= rows * 3 * sizeof(float) ? ws + 2 * rows : nullptr);
+  // The normalisers are read while the sums are written.  A caller may give them in memory that it hands over for the
+  // scores (they are copied into the workspace first) or in the workspace itself (the partial sums then keep off them).
+  bool copy_lse = false;
+  if (lse) {
+    auto shares = [&](const float* p, size_t n) { return row_lse < p + n && p < row_lse + rows; };
+    copy_lse = shares(scores_out, (size_t)B * Hkv * P);
+    if (copy_lse) { a.ref = ws; part = ws + rows; }
+    else if (shares(ws, rows)) part = shares(ws + rows, rows) ? nullptr : ws + rows;
+  }
   // Pass 2 per query head where the KV heads alone give the chip too few workgroups (8 per CU), unless the call is
   // so small that the additional launch is what one sees.  64 query heads over 8, one sequence, 1024 tokens, bf16,
   // D = 64: 129 -> 42 us for both passes; the same at 4096 tokens, D = 128: 650 -> 362; 32 over 8, 69 tokens: 14 -> 17.
   const int own = dt == SQA_F32 ? kMT : 2 * kMT;
   if (Hq == Hkv || P <= 128 || (int64_t)((P + own - 1) / own) * B * Hkv >= 2048) part = nullptr;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (copy_lse) copy_lse_kernel<<<(unsigned)(rows / 256 + 1 < 4096 ? rows / 256 + 1 : 4096), 256, 0, st>>>(row_lse, (int64_t)rows, ws);
   if (dt == SQA_F32) {
     if (D == 64) return launch_scores<float, 64, 1>(a, lse, part, scores_out, st);
     return launch_scores<float, 128, 1>(a, lse, part, scores_out, st);

@@ -203,6 +203,40 @@ def test_prefill_scores_by_query_head_and_by_kv_head(sqa, dtype, D, P):
                 assert ref[5] == 0.0 and rel_err(got[b, h], ref) < TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 128)])
+@pytest.mark.parametrize("g,P", [(1, 200), (4, 200), (4, 100)])      # column sums per KV head, per query head, per KV head
+def test_given_normalisers_in_memory_the_call_writes(sqa, dtype, D, g, P):
+    """row_lse handed over in the buffer of the scores, at its start or beyond it, or in the workspace: the same scores."""
+    B, Hkv = 2, 2
+    rows, outs = B * Hkv * g * P, B * Hkv * P
+    gen = torch.Generator(device="cpu").manual_seed(P + g)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K = (torch.randn(B, h, P, D, generator=gen).to(dt).to(DEV) for h in (Hkv * g, Hkv))
+    lse = torch.tensor(np.stack([np.stack([O.prefill_row_lse(np64(Q)[b, h:h + 1], np64(K)[b, h // g])[0] for h in range(Hkv * g)])
+                                 for b in range(B)]), dtype=torch.float32, device=DEV)
+    want = sqa.prefill_scores(Q, K, row_lse=lse).flatten()
+
+    def run(row_lse, out, ws):
+        row_lse.copy_(lse.flatten())
+        rc = sqa._lib.sqa_prefill_scores_lse(Q.data_ptr(), K.data_ptr(), row_lse.data_ptr(), 0 if dtype == "f32" else 1, B, Hkv * g,
+                                             Hkv, P, D, out.data_ptr(), ws.data_ptr(), ws.numel() * 4,
+                                             torch.cuda.current_stream().cuda_stream, None)
+        assert rc == 0
+        return out
+
+    new = lambda n: torch.zeros(n, device=DEV)
+    for at in (0, outs // 2, rows - 1):                 # the scores lie within the normalisers, or run out of them
+        both = new(rows + outs)
+        assert torch.equal(run(both[:rows], both[at:at + outs], new(2 * rows)), want), at
+    both = new(rows + outs)
+    assert torch.equal(run(both[4:4 + rows], both[:outs], new(2 * rows)), want)
+    for at in (0, rows):
+        ws = new(3 * rows)
+        assert torch.equal(run(ws[at:at + rows], new(outs), ws), want), at
+    ws = new(2 * rows)                                  # no room left for sums per query head: the same ones per KV head
+    assert rel_err(np64(run(ws[rows // 2:rows // 2 + rows], new(outs), ws)), np64(want)) < 1e-6      # fp32 sums of g * P terms, reordered
+
+
 def _wide_range_qk(case, P, Hq, Hkv, D):
     """Queries and keys that share one direction u; the keys' component along u sets the logit level."""
     r = torch.Generator().manual_seed({"steps_up": 11, "late_peak": 12, "steps_down": 13}[case])
