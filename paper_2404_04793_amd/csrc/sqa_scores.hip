@@ -244,8 +244,7 @@ __device__ __forceinline__ void score_rowstats(const ScoreArgs& a, char* s_tiles
           for (int bb = 0; bb < NB; ++bb) {
             const float top = fmaxf(fmaxf(s4[bb][0], s4[bb][1]), fmaxf(s4[bb][2], s4[bb][3])) * scale_log2;
             const float mx = fmaxf(m_run[bb], top);
-            // (bf16 at D = 128 has always taken mx as finite)
-            const float ms = kMerged<T, D> || mx != -INFINITY ? mx : 0.f;
+            const float ms = mx == -INFINITY ? 0.f : mx;       // (nothing but logits of -inf so far)
             l_run[bb] *= __builtin_amdgcn_exp2f(m_run[bb] - ms);
             m_run[bb] = mx;
             float sum = 0.f;

@@ -203,6 +203,24 @@ def test_prefill_scores_by_query_head_and_by_kv_head(sqa, dtype, D, P):
                 assert ref[5] == 0.0 and rel_err(got[b, h], ref) < TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+def test_prefill_scores_with_runs_of_keys_that_count_nothing(sqa, dtype, D):
+    """Logits of -inf for whole groups of 4 and 16 keys, the first that a lane sees of a row among them."""
+    g, Hkv, P = 2, 2, 193
+    wl = W.scaled(W.WORKLOADS["tiny"], L=1, Hq=Hkv * g, Hkv=Hkv, D=D, B=1, P=P, dtype=dtype)
+    K, _ = W.prompt_kv(wl, 0, DEV)
+    Q = W.prompt_q(wl, 0, DEV)
+    none = torch.zeros(P, dtype=torch.bool, device=DEV)
+    none[4:12] = none[16:32] = none[68:72] = True
+    K[:, :, none, 0], Q[..., 0] = -float("inf"), Q[..., 0].abs() + 0.5
+    got = np64(sqa.prefill_scores(Q, K))[0]
+    Kn, off = np64(K)[0], none.cpu().numpy()
+    Kn[:, off, 0] = -1e6                              # (the oracle's logits stay finite; exp gives 0 all the same)
+    for h in range(Hkv):
+        ref = O.prefill_scores(np64(Q)[0, h * g:(h + 1) * g], Kn[h])
+        assert np.all(got[h][off] == 0.0) and rel_err(got[h], ref) < TOL[dtype]
+
+
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 128)])
 @pytest.mark.parametrize("g,P", [(1, 200), (4, 200), (4, 100)])      # column sums per KV head, per query head, per KV head
 def test_given_normalisers_in_memory_the_call_writes(sqa, dtype, D, g, P):
