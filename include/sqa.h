@@ -309,7 +309,11 @@ sqa_status sqa_prefill_compress_layers_ex(const void* const* K, const void* cons
  * arrival counter per unit; with 4 or more query heads per KV head (bf16,
  * D = 128) it also holds, for every unit, the step's per-head probabilities
  * that the H2O accumulation sums.  The merge order is fixed: results are
- * identical from run to run.
+ * identical from run to run.  How units are cut follows from the shapes alone
+ * (sqa_decode_plan).  A workspace of less than sqa_decode_workspace_bytes is
+ * accepted where it holds what a cut into fewer pieces needs -- the results may
+ * then differ from those with a full one in their last bits --, and refused with
+ * SQA_ERR_CAPACITY where it does not.
  * A unit that on entry is longer than its budget, or has no free slot, is left
  * untouched, its out rows are zeroed and the status word is set to
  * SQA_ERR_STATE / SQA_ERR_CAPACITY. */
@@ -336,8 +340,9 @@ sqa_status sqa_decode_step_ex(const void* q, const void* k_new, const void* v_ne
 
 /* ---- the same step for callers that cannot allocate device memory ----------
  * (code running under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc).  Identical to sqa_decode_step_ex -- same kernels, same
- * results bit for bit -- except that the scratch a step needs (layer table,
+ * forbid hipMalloc).  Identical to sqa_decode_step_ex with a workspace of
+ * sqa_decode_workspace_bytes -- same kernels, same results bit for bit --
+ * except that the scratch a step needs (layer table,
  * arrival counters, partial results of split units, H2O logits / probabilities)
  * lives in a device array of SQA_STATIC_SCRATCH_BYTES that is part of the
  * library image; each GPU the library runs on holds its copy until the process
@@ -363,9 +368,9 @@ sqa_status sqa_decode_step_static(const void* q, const void* k_new, const void* 
                                   void* out, int32_t* status, void* stream, const sqa_batch_opts* opts);
 
 /* ---- the launch a decode call would make (host arithmetic only, no GPU call) ----
- * How sqa_decode_step[_ex|_static] would lay the call out on the chip: for sizing, for logs, and so that the
- * launch configuration of a workload can be checked without a GPU.  Of `layers` only budget, capacity and
- * whether block_table is NULL are read.
+ * How sqa_decode_step[_ex|_static] would lay the call out on the chip (with a workspace of
+ * sqa_decode_workspace_bytes): for sizing, for logs, and so that the launch configuration of a workload can be
+ * checked without a GPU.  Of `layers` only budget, capacity and whether block_table is NULL are read.
  *   info      : HOST, filled in
  *   per_layer : HOST [n_layers] or NULL                                                                  */
 typedef struct sqa_decode_plan_info {

@@ -1087,6 +1087,16 @@ struct DecodePlan {
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// The device array that sqa_decode_step_static uses for scratch: layer table, arrival counters, the rest.
+constexpr size_t kStaticTableBytes = 16 * 1024;                    // >= SQA_MAX_LAYERS * sizeof(sqa_layer_cache)
+constexpr size_t kStaticCntBytes = 1024 * 1024;                    // 262144 units per call
+constexpr size_t kStaticDataBytes = SQA_STATIC_SCRATCH_BYTES - kStaticTableBytes - kStaticCntBytes;
+static_assert(SQA_MAX_LAYERS * sizeof(sqa_layer_cache) <= kStaticTableBytes, "layer table region");
+static_assert(SQA_STATIC_SCRATCH_BYTES > kStaticTableBytes + kStaticCntBytes, "scratch size");
+static bool fits_static(const DecodePlan& p) {
+  return p.cnt_bytes <= kStaticCntBytes && align256(p.part_bytes) + p.logit_bytes <= kStaticDataBytes;
+}
+
 // Units are split only when the call would otherwise leave CUs idle: the target work item is the call's
 // tokens divided by the number of CUs (at least min_item slots, and at most what lets a unit's step logits fit
 // in LDS -- kMaxUnsplit slots x heads; not for the matrix-core variant, which keeps what H2O needs in the
@@ -1111,7 +1121,8 @@ constexpr int64_t kWpuMinUnits = 4096;
 // The shortest work item: 4 waves take 128 slots of the matrix-core variant in one 32-token tile each, and 256 slots
 // there cost hardly more; the other kernels walk 16 to 128 rows at a time.  (fp32, D = 128, 8 query heads over 1, two
 // layers of 1500 and 146 slots: 35 us with 256, 25 with 128; 16 over 2, bf16, 4743 slots: 27.5 and 29.8.)
-static int min_item(bool matrix_cores) { return matrix_cores ? 256 : 128; }
+constexpr int kCoarseItem = 256;
+static int min_item(bool matrix_cores) { return matrix_cores ? kCoarseItem : 128; }
 // coarse: the fewest pieces (and the least scratch).
 // scratch_probs: the H2O step's per-token, per-head values live in the workspace for every unit, split or
 // not (the matrix-core variant: they never need LDS, so nothing limits an unsplit unit's length).
@@ -1230,6 +1241,18 @@ static sqa_status plan_decode(const sqa_layer_cache* layers, int n_layers, int B
   return SQA_OK;
 }
 
+// The cut of a call, the same for every entry point (results depend on it in their last bits): where the finer one
+// needs more scratch than the static array has and the coarse one does not, the coarse one.
+static sqa_status plan_cut(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv, int D, bool h2o,
+                           bool allow_wpu, bool scratch_probs, int min_item, DecodePlan* p) {
+  const sqa_status fine = plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, allow_wpu, scratch_probs, min_item, false, p);
+  if (fine == SQA_OK && fits_static(*p)) return fine;
+  DecodePlan c;
+  const sqa_status coarse = plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, allow_wpu, scratch_probs, kCoarseItem, true, &c);
+  if (coarse == SQA_OK && (fine != SQA_OK || fits_static(c))) *p = c;
+  return coarse == SQA_OK ? coarse : fine;
+}
+
 }  // namespace sqa
 
 extern "C" size_t sqa_decode_workspace_bytes(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv,
@@ -1245,7 +1268,7 @@ extern "C" size_t sqa_decode_workspace_bytes(const sqa_layer_cache* layers, int 
   for (int k = 0; k < 6; ++k) {                    // (a call may or may not give short units a wave each, or run on the matrix cores)
     const bool wpu = (k & 1) != 0, probs = k >= 4;
     if ((k >= 2 && !mf) || (probs && !h2o)) continue;
-    if (sqa::plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, wpu, probs, sqa::min_item(k >= 2), false, &p) != SQA_OK) return 0;
+    if (sqa::plan_cut(layers, n_layers, B, Hq, Hkv, D, h2o, wpu, probs, sqa::min_item(k >= 2), &p) != SQA_OK) return 0;
     bytes = p.bytes > bytes ? p.bytes : bytes;
   }
   return bytes;
@@ -1315,7 +1338,8 @@ static sqa_status plan_call(sqa_dtype dt, int B, int Hq, int Hkv, int D, bool h2
                             int n_layers, bool coarse, DecodePlan* plan, size_t* lds_out) {
   const int g = Hq / Hkv;
   const bool mfma = uses_mfma(dt, D, g);
-  const sqa_status ps = plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, true, h2o && mfma, coarse ? 256 : min_item(mfma), coarse, plan);
+  const sqa_status ps = coarse ? plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, true, h2o && mfma, kCoarseItem, true, plan)
+                               : plan_cut(layers, n_layers, B, Hq, Hkv, D, h2o, true, h2o && mfma, min_item(mfma), plan);
   if (ps != SQA_OK) return ps;
   const size_t lds_shared = (size_t)g * plan->lds_chunk, lds_waves = (size_t)kDecWaves * g * plan->lds_chunk_w;
   const size_t lds = (h2o ? (lds_shared > lds_waves ? lds_shared : lds_waves) * sizeof(float) : 0) +
@@ -1456,7 +1480,7 @@ extern "C" sqa_status sqa_decode_step_ex(const void* q, const void* k_new, const
                                        opts, false, &fn, &plan, &lds);
   if (ps != SQA_OK) return ps;
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return SQA_ERR_SHAPE;
-  if (ws_bytes < plan.bytes) {                     // (units cut into fewer pieces need less)
+  if (ws_bytes < plan.bytes) {                     // less than sqa_decode_workspace_bytes: fewer pieces need less
     const sqa_status cs = plan_call(dt, B, Hq, Hkv, D, policy == SQA_H2O, layers, n_layers, true, &plan, &lds);
     if (cs != SQA_OK) return cs;
     if (ws_bytes < plan.bytes) return SQA_ERR_CAPACITY;
@@ -1480,14 +1504,6 @@ extern "C" sqa_status sqa_decode_step_ex(const void* q, const void* k_new, const
 // else, is cleared once per device at set-up, and every launch returns the counters it used to zero
 // (the workgroup that merges a split unit resets the unit's counter), so each call finds them zero
 // although the array keeps the previous call's contents everywhere else.
-namespace sqa {
-constexpr size_t kStaticTableBytes = 16 * 1024;                    // >= SQA_MAX_LAYERS * sizeof(sqa_layer_cache)
-constexpr size_t kStaticCntBytes = 1024 * 1024;                    // 262144 units per call
-constexpr size_t kStaticDataBytes = SQA_STATIC_SCRATCH_BYTES - kStaticTableBytes - kStaticCntBytes;
-static_assert(SQA_MAX_LAYERS * sizeof(sqa_layer_cache) <= kStaticTableBytes, "layer table region");
-static_assert(SQA_STATIC_SCRATCH_BYTES > kStaticTableBytes + kStaticCntBytes, "scratch size");
-}  // namespace sqa
-
 static __device__ __align__(256) unsigned char scratch[SQA_STATIC_SCRATCH_BYTES];
 
 namespace sqa {
@@ -1532,14 +1548,8 @@ extern "C" sqa_status sqa_decode_step_static(const void* q, const void* k_new, c
   const sqa_status ps = decode_prepare(q, k_new, v_new, dt, B, Hq, Hkv, D, new_pos, policy, n_sink, layers, n_layers, out,
                                        opts, false, &fn, &plan, &lds);
   if (ps != SQA_OK) return ps;
-  // beyond the array's fixed size even with units cut into fewer pieces: refused, nothing is enqueued (use
-  // sqa_decode_step with a workspace)
-  auto too_large = [&] { return plan.cnt_bytes > kStaticCntBytes || align256(plan.part_bytes) + plan.logit_bytes > kStaticDataBytes; };
-  if (too_large()) {
-    const sqa_status cs = plan_call(dt, B, Hq, Hkv, D, policy == SQA_H2O, layers, n_layers, true, &plan, &lds);
-    if (cs != SQA_OK) return cs;
-    if (too_large()) return SQA_ERR_CAPACITY;
-  }
+  // beyond the array's fixed size: refused, nothing is enqueued (use sqa_decode_step with a workspace)
+  if (!fits_static(plan)) return SQA_ERR_CAPACITY;
   const size_t part_bytes = align256(plan.part_bytes);
   hipStream_t st = static_cast<hipStream_t>(stream);
   char* base = nullptr;

@@ -110,6 +110,17 @@ def test_plan_invariants_on_random_shapes(seed):
     assert p["workspace_bytes"] <= sqa._lib.sqa_decode_workspace_bytes(t, L, B, g * Hkv, Hkv, D, sqa.POLICY[policy])
 
 
+@pytest.mark.parametrize("D,budgets,pieces", [(64, [4745, 4785, 4830], [5, 4, 5]), (128, [4300, 4557, 5200], [5, 3, 5])])
+def test_cut_does_not_depend_on_where_the_scratch_lies(D, budgets, pieces):
+    """96 units, 8 query heads over 1: the finer cut where its scratch fits the static array of sqa_decode_step_static,
+    the coarser one where only that fits, the finer one again where neither does (the static call is then refused)."""
+    array = 16 * 1024 * 1024 - 1024 * 1024 - 16 * 1024
+    for b, n in zip(budgets, pieces):
+        p = sqa.decode_plan([b], [b], 12, 64, 8, D, "bf16", "h2o")
+        assert p["layers"][0]["workgroups_per_unit"] == n, b
+        assert (p["workspace_bytes"] <= array + 4096) == (b != budgets[-1]), (b, p["workspace_bytes"])
+
+
 def test_plan_argument_errors():
     lib = sqa._lib
     t = (sqa.LayerCacheStruct * 1)()

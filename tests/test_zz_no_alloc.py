@@ -86,6 +86,31 @@ def test_static_scratch_entry_point_matches_the_workspace_one(sqa):
     _run_both(sqa, big, [700, 41, 520], blocked=True)
 
 
+@pytest.mark.parametrize("D,b,pieces", [(64, 4785, 4), (128, 4557, 3)])
+def test_same_cut_where_the_finer_one_needs_more_than_the_array(sqa, D, b, pieces):
+    """96 units that would be cut in 5 with a workspace alone (plans of both cuts: tests/test_decode_plan.py): both entry
+    points take the coarser cut, whose scratch fits the array."""
+    B, Hkv, g, P = 12, 8, 8, b + 9
+    gen = torch.Generator(device=DEV).manual_seed(b)
+    mk = lambda *shape: torch.randn(*shape, generator=gen, device=DEV).bfloat16()
+    K, V, sc = mk(B, Hkv, P, D), mk(B, Hkv, P, D), torch.rand(B, Hkv, P, generator=gen, device=DEV)
+    both = [sqa.LayerCaches([b], [b], B, Hkv, D, torch.bfloat16, DEV, True) for _ in range(2)]
+    for c in both:
+        sqa.prefill_compress(K, V, sc, "h2o", 4, c, 0)
+    assert sqa.decode_plan([b], [b], B, Hkv * g, Hkv, D, "bf16", "h2o")["layers"][0]["workgroups_per_unit"] == pieces
+    ws, status = sqa.decode_workspace(both[0], Hkv * g, "h2o"), torch.zeros(1, dtype=torch.int32, device=DEV)
+    for t in range(2):
+        q, k, v = mk(1, B, Hkv * g, D), mk(1, B, Hkv, D), mk(1, B, Hkv, D)
+        out = [torch.zeros_like(q) for _ in both]
+        sqa.decode_step(q, k, v, P + t, "h2o", 4, both[0], out[0], ws)
+        sqa.decode_step_static(q, k, v, P + t, "h2o", 4, both[1], out[1], status)
+        assert torch.equal(out[0].view(torch.int16), out[1].view(torch.int16)) and bool(torch.isfinite(out[0].float()).all()), t
+        for f in ("K", "V", "score", "pos", "state"):
+            x, y = (getattr(c, f)[0].view(torch.uint8) for c in both)
+            assert torch.equal(x, y), (t, f)
+    assert int(status) == 0
+
+
 def test_static_scratch_entry_point_limits_and_status(sqa):
     """A call whose scratch exceeds the array is refused on the host (nothing runs); device-side conditions
     land in the caller's status word."""
