@@ -1121,13 +1121,31 @@ constexpr int64_t kWpuMinUnits = 4096;
 // The shortest work item: 4 waves take 128 slots of the matrix-core variant in one 32-token tile each, and 256 slots
 // there cost hardly more; the other kernels walk 16 to 128 rows at a time.  (fp32, D = 128, 8 query heads over 1, two
 // layers of 1500 and 146 slots: 35 us with 256, 25 with 128; 16 over 2, bf16, 4743 slots: 27.5 and 29.8.)
+// Units of up to 1.25 x 256 slots stay whole all the same: in two pieces they pay for a merge and save a trip or two
+// (8 to 64 units of 165 to 301 slots, one query head over 1: 8.6 -> 10.1, 9.4 -> 10.4, 11.2 -> 12.1 us; in three
+// instead of two, 321 slots 12.5 -> 11.0).
 constexpr int kCoarseItem = 256;
-static int min_item(bool matrix_cores) { return matrix_cores ? kCoarseItem : 128; }
+// How many workgroups a finer cut may come to: two per CU, which run at once in every kernel, or up to three where the
+// work items hold `beyond` slots on average.  Past that the whole units of the other layers end up in pieces too, and
+// their merges (under H2O also the scratch that they need in place of LDS) cost more than the balance brings.
+//   more than 128 registers (2 or 3 workgroups per CU): 800 slots.  bf16, D = 64, 8 heads over 1, H2O, 40 units of 1450
+//     and 240 of 529 slots 43 us in 320 workgroups, 53 in 680; 8 over 1 on the matrix cores, sliding, 48 of 4165 and 192
+//     of 988 39 us in 336, 43 in 624; but 4 over 1, H2O, 130 of 8192 and 286 of 557 175 us in 546, 145 in 676.
+//   up to 128 registers, where a workgroup spends long on arithmetic or on its unit's scores: any length.  fp32, 4 heads
+//     over 1, H2O, 78 of 1543 and 78 of 481 70 us in 312, 51 in 702; bf16, 2 over 1, H2O, 72 of 8192 and 144 of 1948 169
+//     us in 288, 112 in 720.
+//   the same without either: none.  bf16, one head, sliding, 48 of 1067 and 208 of 706 14.5 us in 304, 16.1 in 816.
+struct CutRule { int min_item; int64_t beyond; };
+static bool uses_mfma(sqa_dtype dt, int D, int g) { return dt == SQA_BF16 && D == 128 && g >= kMfmaMinGroup; }
+static CutRule cut_rule(sqa_dtype dt, int D, int g, bool h2o) {
+  const bool light = g <= (dt == SQA_F32 ? 4 : 2);         // up to 128 registers
+  return {uses_mfma(dt, D, g) ? kCoarseItem : 128, !light ? 800 : (h2o || dt == SQA_F32 ? 0 : INT32_MAX)};
+}
 // coarse: the fewest pieces (and the least scratch).
 // scratch_probs: the H2O step's per-token, per-head values live in the workspace for every unit, split or
 // not (the matrix-core variant: they never need LDS, so nothing limits an unsplit unit's length).
 static sqa_status plan_decode(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv, int D, bool h2o,
-                              bool allow_wpu, bool scratch_probs, int min_item, bool coarse, DecodePlan* p) {
+                              bool allow_wpu, bool scratch_probs, CutRule rule, bool coarse, DecodePlan* p) {
   const int64_t units = (int64_t)B * Hkv;
   const int g = Hq / Hkv;
   const bool paged = layers[0].block_table != nullptr;
@@ -1144,14 +1162,15 @@ static sqa_status plan_decode(const sqa_layer_cache* layers, int n_layers, int B
     tokens += units * (layers[i].budget < layers[i].capacity ? layers[i].budget : layers[i].capacity);
   }
   // longest work item a unit is cut for, given how many items the call's tokens are worth
-  auto item_slots = [&](int64_t items) {
+  auto item_slots = [&](int64_t items, int64_t least) {
     int64_t t = tokens / items;
-    t = t < min_item ? min_item : t;
+    t = t < least ? least : t;
     return h2o && !scratch_probs && t > kMaxUnsplit / g ? (int64_t)(kMaxUnsplit / g) : t;
   };
   auto cut = [&](int i, int64_t target, int64_t* ns_out, int64_t* ch_out) {
     // + 1: under attend-then-evict a full unit attends budget + 1 tokens
     const int nmax = (layers[i].budget < layers[i].capacity ? layers[i].budget : layers[i].capacity) + 1;
+    if (target < kCoarseItem && 4 * (int64_t)nmax <= 5 * kCoarseItem) target = kCoarseItem;
     int64_t ns = (4 * (int64_t)nmax + 5 * target - 1) / (5 * target);   // ceil(nmax / (1.25 target))
     ns = ns < 1 ? 1 : (ns > kMaxSplit ? kMaxSplit : ns);
     int64_t ch = ((nmax + ns - 1) / ns + 63) / 64 * 64;
@@ -1159,11 +1178,11 @@ static sqa_status plan_decode(const sqa_layer_cache* layers, int n_layers, int B
     *ns_out = (nmax + ch - 1) / ch;
     *ch_out = ch;
   };
-  int64_t target = item_slots(kMinItems);
+  int64_t target = item_slots(kMinItems, kCoarseItem);
   int64_t longest_ns, longest_ch;
-  cut(order[0], target, &longest_ns, &longest_ch);
-  for (int64_t items = kMinItems, best = INT64_MAX; longest_ns > 1 && items <= (coarse ? 1 : 3) * kMinItems; items += kMinItems) {
-    const int64_t t = item_slots(items);
+  cut(order[0], item_slots(kMinItems, rule.min_item), &longest_ns, &longest_ch);
+  for (int64_t items = kMinItems, best = INT64_MAX; !coarse && longest_ns > 1 && items <= 3 * kMinItems; items += kMinItems) {
+    const int64_t t = item_slots(items, rule.min_item);
     int64_t n = 0, shortest = INT64_MAX, load = 0;         // slots the busiest CU streams if it gets every 256th item
     for (int k = 0; k < n_layers; ++k) {
       int64_t ns, ch;
@@ -1173,8 +1192,9 @@ static sqa_status plan_decode(const sqa_layer_cache* layers, int n_layers, int B
       const int64_t x = (n + kMinItems - 1) / kMinItems * shortest;
       load = x > load ? x : load;
     }
+    if (n > 2 * kMinItems && (n > 3 * kMinItems || tokens < rule.beyond * n)) break;
     if (load <= best) { best = load; target = t; }
-    if (8 * load * kMinItems <= 9 * tokens || t == min_item) break;
+    if (8 * load * kMinItems <= 9 * tokens || t == rule.min_item) break;
   }
   uint64_t blocks = 0, n_units = 0, n_part = 0, n_logit = 0;
   p->tbl_entries = 0;
@@ -1244,11 +1264,11 @@ static sqa_status plan_decode(const sqa_layer_cache* layers, int n_layers, int B
 // The cut of a call, the same for every entry point (results depend on it in their last bits): where the finer one
 // needs more scratch than the static array has and the coarse one does not, the coarse one.
 static sqa_status plan_cut(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv, int D, bool h2o,
-                           bool allow_wpu, bool scratch_probs, int min_item, DecodePlan* p) {
-  const sqa_status fine = plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, allow_wpu, scratch_probs, min_item, false, p);
+                           bool allow_wpu, bool scratch_probs, CutRule rule, DecodePlan* p) {
+  const sqa_status fine = plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, allow_wpu, scratch_probs, rule, false, p);
   if (fine == SQA_OK && fits_static(*p)) return fine;
   DecodePlan c;
-  const sqa_status coarse = plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, allow_wpu, scratch_probs, kCoarseItem, true, &c);
+  const sqa_status coarse = plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, allow_wpu, scratch_probs, rule, true, &c);
   if (coarse == SQA_OK && (fine != SQA_OK || fits_static(c))) *p = c;
   return coarse == SQA_OK ? coarse : fine;
 }
@@ -1260,15 +1280,14 @@ extern "C" size_t sqa_decode_workspace_bytes(const sqa_layer_cache* layers, int 
   if (!layers || n_layers < 1 || n_layers > SQA_MAX_LAYERS || B < 1 || Hq < 1 || Hkv < 1 || Hq % Hkv != 0 || D < 1)
     return 0;
   sqa::DecodePlan p;
-  // (the element type is not known here: size for the variant that needs more, the matrix-core one if the
-  // shape allows it)
+  // (neither the element type nor whether a call gives short units a wave each is known here: the most of what they need)
   const bool h2o = policy == SQA_H2O;
+  const int g = Hq / Hkv;
   size_t bytes = 0;
-  const bool mf = D == 128 && Hq / Hkv >= sqa::kMfmaMinGroup;
-  for (int k = 0; k < 6; ++k) {                    // (a call may or may not give short units a wave each, or run on the matrix cores)
-    const bool wpu = (k & 1) != 0, probs = k >= 4;
-    if ((k >= 2 && !mf) || (probs && !h2o)) continue;
-    if (sqa::plan_cut(layers, n_layers, B, Hq, Hkv, D, h2o, wpu, probs, sqa::min_item(k >= 2), &p) != SQA_OK) return 0;
+  for (int k = 0; k < 4; ++k) {
+    const sqa_dtype dt = k & 1 ? SQA_BF16 : SQA_F32;
+    if (sqa::plan_cut(layers, n_layers, B, Hq, Hkv, D, h2o, k >= 2, h2o && sqa::uses_mfma(dt, D, g), sqa::cut_rule(dt, D, g, h2o), &p) != SQA_OK)
+      return 0;
     bytes = p.bytes > bytes ? p.bytes : bytes;
   }
   return bytes;
@@ -1333,13 +1352,13 @@ struct DecodeScratch {
 
 // Argument checks shared by the decode entry points; on success the kernel and the launch plan.
 // The launch plan of a call and the dynamic LDS its workgroups need (host arithmetic only).
-static bool uses_mfma(sqa_dtype dt, int D, int g) { return dt == SQA_BF16 && D == 128 && g >= kMfmaMinGroup; }
 static sqa_status plan_call(sqa_dtype dt, int B, int Hq, int Hkv, int D, bool h2o, const sqa_layer_cache* layers,
                             int n_layers, bool coarse, DecodePlan* plan, size_t* lds_out) {
   const int g = Hq / Hkv;
   const bool mfma = uses_mfma(dt, D, g);
-  const sqa_status ps = coarse ? plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, true, h2o && mfma, kCoarseItem, true, plan)
-                               : plan_cut(layers, n_layers, B, Hq, Hkv, D, h2o, true, h2o && mfma, min_item(mfma), plan);
+  const CutRule rule = cut_rule(dt, D, g, h2o);
+  const sqa_status ps = coarse ? plan_decode(layers, n_layers, B, Hq, Hkv, D, h2o, true, h2o && mfma, rule, true, plan)
+                               : plan_cut(layers, n_layers, B, Hq, Hkv, D, h2o, true, h2o && mfma, rule, plan);
   if (ps != SQA_OK) return ps;
   const size_t lds_shared = (size_t)g * plan->lds_chunk, lds_waves = (size_t)kDecWaves * g * plan->lds_chunk_w;
   const size_t lds = (h2o ? (lds_shared > lds_waves ? lds_shared : lds_waves) * sizeof(float) : 0) +

@@ -121,6 +121,27 @@ def test_cut_does_not_depend_on_where_the_scratch_lies(D, budgets, pieces):
         assert (p["workspace_bytes"] <= array + 4096) == (b != budgets[-1]), (b, p["workspace_bytes"])
 
 
+@pytest.mark.parametrize("budgets,B,Hq,Hkv,D,dtype,policy,workgroups,pieces", [
+    # up to 320 slots a unit stays whole (319 + the new one), from there on it is cut in three (matrix cores: in two)
+    ([319], 1, 8, 8, 128, "bf16", "h2o", 8, [1]), ([320], 1, 8, 8, 128, "bf16", "h2o", 24, [3]),
+    ([320], 1, 32, 8, 128, "bf16", "h2o", 16, [2]), ([2000, 300], 1, 8, 8, 64, "f32", "sliding", None, [None, 1]),
+    # more than two workgroups per CU: not in a heavy kernel with short work items ...
+    ([1450] + [529] * 6, 5, 64, 8, 64, "bf16", "h2o", 320, [2] + [1] * 6),
+    ([4165] + [988] * 4, 6, 64, 8, 128, "bf16", "sliding", 336, [3] + [1] * 4),
+    ([1067] * 3 + [706] * 13, 2, 8, 8, 64, "bf16", "sliding", 304, [2] * 3 + [1] * 13),
+    # ... but with long ones, and in the kernels that keep four on a CU
+    ([8192] * 5 + [557] * 11, 13, 8, 2, 128, "bf16", "h2o", 676, [3] * 5 + [1] * 11),
+    ([8192, 1948, 1948], 9, 16, 8, 128, "bf16", "h2o", 720, [6, 2, 2]),
+    ([1543] * 3 + [481] * 3, 13, 8, 2, 128, "f32", "h2o", 702, [7] * 3 + [2] * 3),
+    # never more than three
+    ([3439] * 2 + [2000] * 14, 4, 32, 8, 128, "f32", "h2o", 576, [2] * 2 + [1] * 14)])
+def test_finer_cuts_and_where_they_end(budgets, B, Hq, Hkv, D, dtype, policy, workgroups, pieces):
+    p = sqa.decode_plan(budgets, budgets, B, Hq, Hkv, D, dtype, policy)
+    assert workgroups is None or p["workgroups"] == workgroups
+    got = [l["workgroups_per_unit"] for l in p["layers"]]
+    assert all(y is None or x == y for x, y in zip(got, pieces)), got
+
+
 def test_plan_argument_errors():
     lib = sqa._lib
     t = (sqa.LayerCacheStruct * 1)()
