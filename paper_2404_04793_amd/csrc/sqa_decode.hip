@@ -95,12 +95,6 @@ __device__ __forceinline__ void st_agent(unsigned long long* p, unsigned long lo
 __device__ __forceinline__ unsigned long long ld_agent(const unsigned long long* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ void st_agent(unsigned short* p, unsigned short v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned short ld_agent(const unsigned short* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 // element i of an array whose base is the same in all lanes: a global access (the pointers come from a table in
 // memory, where the compiler can only take them for generic ones) with a 32-bit offset, one register instead of two
@@ -1350,8 +1344,8 @@ struct DecodeScratch {
   float* logit;        // H2O logits / probabilities
 };
 
-// Argument checks shared by the decode entry points; on success the kernel and the launch plan.
 // The launch plan of a call and the dynamic LDS its workgroups need (host arithmetic only).
+// coarse: for a workspace that does not hold what the plan of the call's shapes needs.
 static sqa_status plan_call(sqa_dtype dt, int B, int Hq, int Hkv, int D, bool h2o, const sqa_layer_cache* layers,
                             int n_layers, bool coarse, DecodePlan* plan, size_t* lds_out) {
   const int g = Hq / Hkv;
@@ -1370,10 +1364,11 @@ static sqa_status plan_call(sqa_dtype dt, int B, int Hq, int Hkv, int D, bool h2
   return SQA_OK;
 }
 
+// Argument checks shared by the decode entry points; on success the kernel and the launch plan.
 static sqa_status decode_prepare(const void* q, const void* k_new, const void* v_new, sqa_dtype dt,
                                  int B, int Hq, int Hkv, int D, int32_t new_pos, sqa_policy policy, int n_sink,
                                  const sqa_layer_cache* layers, int n_layers, const void* out,
-                                 const sqa_batch_opts* opts, bool coarse, decode_fn* fn_out, DecodePlan* plan, size_t* lds_out) {
+                                 const sqa_batch_opts* opts, decode_fn* fn_out, DecodePlan* plan, size_t* lds_out) {
   if (!q || !k_new || !v_new || !layers || !out) return SQA_ERR_NULL;
   if (opts && opts->order != SQA_EVICT_THEN_ATTEND && opts->order != SQA_ATTEND_THEN_EVICT) return SQA_ERR_POLICY;
   if (dt != SQA_F32 && dt != SQA_BF16) return SQA_ERR_DTYPE;
@@ -1400,7 +1395,7 @@ static sqa_status decode_prepare(const void* q, const void* k_new, const void* v
                   (int64_t)c.blocks_per_unit * SQA_BLOCK_SLOTS < (c.budget < c.capacity ? c.budget : c.capacity)))
       return SQA_ERR_SHAPE;
   }
-  const sqa_status ps = plan_call(dt, B, Hq, Hkv, D, h2o, layers, n_layers, coarse, plan, lds_out);
+  const sqa_status ps = plan_call(dt, B, Hq, Hkv, D, h2o, layers, n_layers, false, plan, lds_out);
   if (ps != SQA_OK) return ps;
   *fn_out = pick(dt, D, g, h2o, paged);
   return SQA_OK;
@@ -1496,7 +1491,7 @@ extern "C" sqa_status sqa_decode_step_ex(const void* q, const void* k_new, const
   DecodePlan plan;
   size_t lds = 0;
   const sqa_status ps = decode_prepare(q, k_new, v_new, dt, B, Hq, Hkv, D, new_pos, policy, n_sink, layers, n_layers, out,
-                                       opts, false, &fn, &plan, &lds);
+                                       opts, &fn, &plan, &lds);
   if (ps != SQA_OK) return ps;
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) return SQA_ERR_SHAPE;
   if (ws_bytes < plan.bytes) {                     // less than sqa_decode_workspace_bytes: fewer pieces need less
@@ -1565,7 +1560,7 @@ extern "C" sqa_status sqa_decode_step_static(const void* q, const void* k_new, c
   DecodePlan plan;
   size_t lds = 0;
   const sqa_status ps = decode_prepare(q, k_new, v_new, dt, B, Hq, Hkv, D, new_pos, policy, n_sink, layers, n_layers, out,
-                                       opts, false, &fn, &plan, &lds);
+                                       opts, &fn, &plan, &lds);
   if (ps != SQA_OK) return ps;
   // beyond the array's fixed size: refused, nothing is enqueued (use sqa_decode_step with a workspace)
   if (!fits_static(plan)) return SQA_ERR_CAPACITY;
