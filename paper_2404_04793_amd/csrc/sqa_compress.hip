@@ -22,7 +22,7 @@ constexpr int kCmpWaves = kCmpThreads / SQA_WAVE;
 constexpr int kCmpRows = 4;             // rows of K and of V that a thread has in flight
 constexpr int64_t kCmpFill = 384;         // workgroups that a call with few units is cut into
 constexpr int64_t kCmpCUs = 256;
-constexpr int64_t kCmpMany = 16384;           // units of a launch from which on the variant for many is used
+constexpr int64_t kCmpManyUnits = 2048, kCmpManyRows = 128;   // launches of more units than run at once, with fewer rows each: see launch_compress
 constexpr int64_t kCmpMaxParts = 256;         // workgroups per unit
 constexpr int kKeysInLdsMax = 16384;     // scores staged in LDS up to this many candidates
 
@@ -80,8 +80,8 @@ struct CompressBatch {
 };
 static_assert(SQA_MAX_LAYERS <= 256, "CompressBatch::layer holds a layer index in 8 bits");
 
-// MANY: so many units that what counts is how little each one does (one workgroup per unit, two rows in flight per
-// thread); otherwise a unit may be shared out, four rows are in flight, and many candidates are listed in runs.
+// MANY: many short units, where what counts is how little each one does (one workgroup per unit, two rows in flight
+// per thread); otherwise a unit may be shared out, four rows are in flight, and many candidates are listed in runs.
 template <typename T, int D, bool MANY>
 __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
     const CompressBatch batch, int P /*prompt rows per unit in memory*/, int policy, int n_sink, int lds_words /*dynamic LDS of the launch, in 32-bit words*/) {
@@ -329,9 +329,12 @@ static hipError_t launch_compress(CompressBatch& batch, int n, int P, int policy
     batch.parts[i] = (uint32_t)parts;
     most = batch.parts[i] > most ? batch.parts[i] : most;
   }
-  // (224 sequences of 512 tokens, 35 rows kept in most layers: 1 % slower with the other variant; 22 layers of 160 units
-  // 371 us with this one, 360 with the other)
-  auto fn = (int64_t)units * n >= kCmpMany ? prefill_compress_kernel<T, D, true> : prefill_compress_kernel<T, D, false>;
+  // Two rows in flight per thread are enough for short units once there are more of them than run at once (8 per CU), and
+  // fewer instructions then count.  32 layers, us with two / four rows: 4096 units of 27 rows on average 33.6 / 36.8, of 98
+  // 91 / 94, of 168 152.6 / 152.6; 8192 of 98, fp32, D = 64 179 / 182; 65536 of 55 772 / 784; 8192 of 409 667 / 662;
+  // 16 layers, 1024 units of 98 28.1 / 27.3.
+  const bool many = (int64_t)units * n >= kCmpManyUnits && rows < kCmpManyRows * units * n;
+  auto fn = many ? prefill_compress_kernel<T, D, true> : prefill_compress_kernel<T, D, false>;
   if (lds > 48 * 1024) {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(fn), lds);
     if (e != hipSuccess) return e;

@@ -365,6 +365,24 @@ def test_prefill_compress_units_shared_out(sqa, dtype, D, P, budgets, blocked):
     assert int(status) == 0
 
 
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("B,b", [(64, 127), (64, 128), (63, 127)])     # 2048 units on both sides of 128 rows, and 2016
+def test_prefill_compress_of_many_short_units(sqa, dtype, D, B, b):
+    Hkv, P = 32, 300
+    gen = torch.Generator(device=DEV).manual_seed(b)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    K, V = (torch.randn(B, Hkv, P, D, generator=gen, device=DEV).to(dt) for _ in range(2))
+    sc = torch.randint(0, 40, (B, Hkv, P), generator=gen, device=DEV).float() / 16
+    caches = _mk_caches(sqa, [b], [b], B, Hkv, D, dtype)
+    sqa.prefill_compress(K, V, sc, "h2o", 4, caches, 0)
+    assert bool((caches.state[0].view(-1, 4) == torch.tensor([b, 0, -2, 0], dtype=torch.int32, device=DEV)).all())
+    for x, h in ((0, 0), (1, 31), (B // 2, 7), (B - 1, 31)):
+        want = O.prefill_compress(np64(K)[x, h], np64(V)[x, h], np64(sc)[x, h], b, "h2o", 4)
+        got = export_state(caches, 0, x, h)
+        assert got["pos"].tolist() == want["pos"].tolist(), (x, h)
+        assert all(np.array_equal(got[f], want[f]) for f in ("K", "V", "score")), (x, h)
+
+
 def test_prefill_compress_layers_matches_single_layer_calls(sqa):
     """One launch over 35 layers with different budgets (two batches of kernel arguments) == 35 calls."""
     B, Hkv, P, D, L = 2, 2, 300, 128, 35
