@@ -384,7 +384,8 @@ typedef struct sqa_decode_plan_info {
 } sqa_decode_plan_info;
 typedef struct sqa_decode_layer_plan {
   int32_t workgroups_per_unit;  /* 1: a workgroup streams the whole unit; k > 1: the unit is cut into k work
-                                   items whose partial results the last one to finish merges; 0: see next  */
+                                   items (at most 128) whose partial results the last one to finish merges;
+                                   0: see next                                                             */
   int32_t slots_per_workgroup;  /* length of such a work item in slots (a multiple of 64)                   */
   int32_t wave_per_unit;        /* 1: short units, many of them: each of a workgroup's 4 waves owns a unit  */
   int32_t probs_in_lds;         /* MFMA variant under H2O, the step's per-head probabilities of a unit: 1 = all

@@ -244,7 +244,10 @@ constexpr int kWpuMaxSlots = 256;                 // one wave per unit: for unit
 // batch 2, 32 layers in one call, 80.6 -> 75.2 us; 12 layers of 128 units of 300 to 1900 slots, D = 64, 55.8 -> 51.3; fp32,
 // 2 query heads over 1, up to 1500 slots, 99 -> 96).  Beyond: no better (batch 6) or worse (batch 8, 277 -> 283).
 constexpr int kSoloMaxTokens = 512, kSoloMaxTokensMid = 768;
-constexpr int kMaxSplit = 128;                    // work items per unit (their statistics are merged in the LDS of the waves' accumulators)
+// Work items per unit: their statistics are merged in the LDS of the waves' accumulators, which at D = 64 holds 128.  A call
+// of one unit of more than 40960 slots could use more (65536 slots: 114 workgroups for 256 CUs); the merge that this allows
+// is worth more (one query head, bf16, D = 128: 229 us in 205 pieces merged one by one, 112 so; 131072 slots 344 and 207).
+constexpr int kMaxSplit = 128;
 constexpr int kLogitPad = 33;                     // a unit's H2O scratch region: G x (slots + kLogitPad) floats: the logit of the
                                                   // new token as one more slot, or whole 32-token tiles of bf16 probabilities
                                                   // plus a reference per tile and head

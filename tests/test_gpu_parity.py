@@ -333,18 +333,19 @@ def test_prefill_compress(sqa, policy, dtype, B, Hkv, P, D, b, blocked):
 @pytest.mark.parametrize("blocked", [False, True], ids=["dense", "blocked"])
 @pytest.mark.parametrize("dtype,D,P,budgets", [("bf16", 128, 1400, [100, 1287, 1399]), ("f32", 64, 2305, [641, 2304, 3000]),
                                                ("f32", 128, 1100, [33, 64, 65]), ("bf16", 64, 17000, [1031, 6]),
-                                               # 300 units: between one and two per CU, shared out for the long layer only
-                                               ("bf16", 128, 400, [8] * 49 + [390])])
+                                               # 384 units in one launch, between one and two per CU: shared out for the
+                                               # two long layers, and (lengths alike) not at all
+                                               ("bf16", 128, 400, [8] * 30 + [390] * 2), ("bf16", 64, 400, [150] * 32)])
 def test_prefill_compress_units_shared_out(sqa, dtype, D, P, budgets, blocked):
     """Few units, so that several workgroups copy a unit's rows (shares with and without remainders, more workgroups
     than a share needs), and more than 1024 candidates with many equal scores (each thread lists a run of
     positions), below and above the number whose scores are staged; sequences of different length and budget."""
-    B, Hkv = (2, 2) if len(budgets) < 10 else (3, 2)
+    B, Hkv = (2, 2) if len(budgets) < 10 else (6, 2)
     n = len(budgets)
     gen = torch.Generator(device="cpu").manual_seed(P)
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
-    plen = [P, P - P // 3, 1][:B]
-    bseq = [[b, max(2, b // 2), 2][:B] for b in budgets]
+    plen = [P, P - P // 3, 1, P, P, P][:B]
+    bseq = [[b, max(2, b // 2), 2, b, b, b][:B] for b in budgets]
     Ks = [torch.randn(B, Hkv, P, D, generator=gen).to(dt).to(DEV) for _ in range(n)]
     Vs = [torch.randn(B, Hkv, P, D, generator=gen).to(dt).to(DEV) for _ in range(n)]
     Ss = [(torch.randint(0, 40, (B, Hkv, P), generator=gen).float() / 16).to(DEV) for _ in range(n)]
@@ -353,7 +354,7 @@ def test_prefill_compress_units_shared_out(sqa, dtype, D, P, budgets, blocked):
     for opts in (None, sqa.batch_opts(prompt_len=pl, budget_seq=bs, status=status)):
         caches = _mk_caches(sqa, budgets, [min(P, b) for b in budgets], B, Hkv, D, dtype, blocked=blocked)
         sqa.prefill_compress_layers(Ks, Vs, Ss, "h2o", 4, caches, opts=opts)
-        for l in (range(n) if n < 10 else (0, 48, 49)):
+        for l in (range(n) if n < 10 else (0, n - 2, n - 1)):
             for b in range(B):
                 p, bud = (P, budgets[l]) if opts is None else (plen[b], bseq[l][b])
                 for h in range(Hkv):
@@ -957,6 +958,41 @@ def test_a_unit_in_many_pieces(sqa, dtype, D, g, b, order, flat):
         assert got["pos"].tolist() == c2["pos"].tolist(), t
         assert rel_err(np64(out)[0, 0], want) < TOL[dtype]
         check_step_scores(got, before, c2, mf, (t,))
+
+
+@pytest.mark.parametrize("order", ["evict_then_attend", "attend_then_evict"])
+def test_fewer_pieces_with_less_scratch_on_the_matrix_cores(sqa, order):
+    """16 units in 26 pieces each, and with a workspace that does not hold those in 13: both against the oracle, and the
+    same state after every step."""
+    B, Hkv, g, D, b, dtype = 8, 2, 8, 128, 8192, "bf16"
+    P = b + 20
+    gen = torch.Generator(device=DEV).manual_seed(b)
+    mk = lambda *shape: torch.randn(*shape, generator=gen, device=DEV).bfloat16()
+    K, V, sc = mk(B, Hkv, P, D), mk(B, Hkv, P, D), torch.rand(B, Hkv, P, generator=gen, device=DEV) + 0.5
+    caches = [_mk_caches(sqa, [b], [b], B, Hkv, D, dtype) for _ in range(2)]
+    for c in caches:
+        sqa.prefill_compress(K, V, sc, "h2o", 4, c, 0)
+    plan = sqa.decode_plan([b], [b], B, Hkv * g, Hkv, D, dtype, "h2o")
+    assert plan["layers"][0]["workgroups_per_unit"] == 26 and uses_matrix_cores(dtype, D, g)
+    ws = [torch.zeros(plan["workspace_bytes"] - x, dtype=torch.uint8, device=DEV) for x in (0, 256)]
+    for t in range(2):
+        q, k, v = mk(1, B, Hkv * g, D), mk(1, B, Hkv, D), mk(1, B, Hkv, D)
+        units = [(0, 0), (B - 1, Hkv - 1)]
+        outs = []
+        for c, w in zip(caches, ws):
+            before = [export_state(c, 0, x, h) for x, h in units]
+            out = torch.empty_like(q)
+            sqa.decode_step(q, k, v, P + t, "h2o", 4, c, out, w, opts=sqa.batch_opts(order=order))
+            outs.append(out)
+            for (x, h), s0 in zip(units, before):
+                want, c2 = O.decode_step(oracle_view(s0), np64(q)[0, x, h * g:(h + 1) * g], np64(k)[0, x, h], np64(v)[0, x, h], P + t, b,
+                                         "h2o", 4, order=order)
+                got = export_state(c, 0, x, h)
+                assert got["pos"].tolist() == c2["pos"].tolist(), (t, x, h)
+                assert rel_err(np64(out)[0, x, h * g:(h + 1) * g], want) < TOL[dtype]
+                check_step_scores(got, s0, c2, True, (t, x, h))
+        assert rel_err(np64(outs[0]), np64(outs[1])) < TOL[dtype]
+        assert sqa.read_device_status(ws[0]) == 0 and sqa.read_device_status(ws[1]) == 0
 
 
 @pytest.mark.parametrize("order", ["evict_then_attend", "attend_then_evict"])
