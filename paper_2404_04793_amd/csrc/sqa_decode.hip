@@ -240,9 +240,10 @@ typedef __attribute__((address_space(3))) v4s_t* lds_v4s_ptr;
 constexpr int kWpuMaxSlots = 256;                 // one wave per unit: for units of at most this many slots
 // An unsplit unit's tail (scores, decision) is left to wave 0 alone, so that the registers of the other waves are free for
 // the next workgroup -- up to this length where there is hardly a next one (at most kWideTailMaxBlocks workgroups), up to
-// the other in calls of 2 to 8 workgroups per CU, whose long units otherwise end after everything else (Llama-2-7B shape at
-// batch 2, 32 layers in one call, 80.6 -> 75.2 us; 12 layers of 128 units of 300 to 1900 slots, D = 64, 55.8 -> 51.3; fp32,
-// 2 query heads over 1, up to 1500 slots, 99 -> 96).  Beyond: no better (batch 6) or worse (batch 8, 277 -> 283).
+// the other in calls of 2 to 8 workgroups per CU, whose long units otherwise end after everything else (two runs each;
+// Llama-2-7B shape at batch 2, 32 layers in one call, 80.6 -> 75.2 and 82.9 -> 77.0 us; 12 layers of 128 units of 300 to 1900
+// slots, D = 64, 55.8 -> 51.3 and 57.3 -> 52.6; fp32, 2 query heads over 1, up to 1500 slots, 99 -> 96 and 102 -> 99).  Beyond:
+// no better (batch 6) or worse (batch 8, 277 -> 283).
 constexpr int kSoloMaxTokens = 512, kSoloMaxTokensMid = 768;
 // Work items per unit: their statistics are merged in the LDS of the waves' accumulators, which at D = 64 holds 128.  A call
 // of one unit of more than 40960 slots could use more (65536 slots: 114 workgroups for 256 CUs); the merge that this allows
@@ -1104,7 +1105,8 @@ static bool fits_static(const DecodePlan& p) {
 // 67 us whole, 82 in halves; all layers at batch 2 81 us with the long units whole, 87 cut in three.
 // Where the longest units have to be cut anyway, the pieces are made for 2 or 3 items per CU if the items of one
 // per CU come out unevenly (the busiest of 256 CUs with over 9/8 of its share): 96 units of 2271 slots 41 us in 3
-// pieces (288 items), 34.5 in 5; 130 units of 8192 with 286 of 557, 4 query heads over 1, 167 us and 140.
+// pieces (288 items), 34.5 in 5; 130 units of 8192 with 286 of 557, 4 query heads over 1, 167 us and 140 (175 and 145 in
+// another run).  How far that goes: see CutRule.
 constexpr int64_t kMinItems = 256;
 constexpr int64_t kWideTailMaxBlocks = 512, kWideTailMidBlocks = 2048;   // see kSoloMaxTokens
 // Matrix-core variant under H2O: LDS a workgroup may use for a unit's per-head probabilities so that three
