@@ -1166,12 +1166,12 @@ static sqa_status plan_decode(const sqa_layer_cache* layers, int n_layers, int B
     t = t < least ? least : t;
     return h2o && !scratch_probs && t > kMaxUnsplit / g ? (int64_t)(kMaxUnsplit / g) : t;
   };
-  auto cut = [&](int i, int64_t target, int64_t* ns_out, int64_t* ch_out) {
+  auto cut = [&](int i, int64_t target, int64_t* ns_out, int64_t* ch_out, int64_t most = kMaxSplit) {
     // + 1: under attend-then-evict a full unit attends budget + 1 tokens
     const int nmax = (layers[i].budget < layers[i].capacity ? layers[i].budget : layers[i].capacity) + 1;
     if (target < kCoarseItem && 4 * (int64_t)nmax <= 5 * kCoarseItem) target = kCoarseItem;
     int64_t ns = (4 * (int64_t)nmax + 5 * target - 1) / (5 * target);   // ceil(nmax / (1.25 target))
-    ns = ns < 1 ? 1 : (ns > kMaxSplit ? kMaxSplit : ns);
+    ns = ns < 1 ? 1 : (ns > most ? most : ns);
     int64_t ch = ((nmax + ns - 1) / ns + 63) / 64 * 64;
     if (h2o && !scratch_probs && ns == 1 && ch * g > kMaxUnsplit) { ns = 2; ch = ((nmax + 1) / 2 + 63) / 64 * 64; }
     *ns_out = (nmax + ch - 1) / ch;
@@ -1179,6 +1179,11 @@ static sqa_status plan_decode(const sqa_layer_cache* layers, int n_layers, int B
   };
   int64_t target = item_slots(kMinItems, kCoarseItem);
   int64_t longest_ns, longest_ch;
+  for (int i = 0; i < n_layers; ++i) {
+    // a unit of more than 65535 items of that length (under H2O with the logits in LDS: over 83 million slots at 8 heads) is refused
+    cut(i, target, &longest_ns, &longest_ch, INT32_MAX);
+    if (longest_ns > 65535) return SQA_ERR_CAPACITY;
+  }
   cut(order[0], item_slots(kMinItems, rule.min_item), &longest_ns, &longest_ch);
   for (int64_t items = kMinItems, best = INT64_MAX; !coarse && longest_ns > 1 && items <= 3 * kMinItems; items += kMinItems) {
     const int64_t t = item_slots(items, rule.min_item);

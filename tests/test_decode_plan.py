@@ -142,6 +142,15 @@ def test_finer_cuts_and_where_they_end(budgets, B, Hq, Hkv, D, dtype, policy, wo
     assert all(y is None or x == y for x, y in zip(got, pieces)), got
 
 
+def test_units_of_more_than_65535_items_are_refused():
+    for b, code in ((65535 * 1280 - 1, 0), (65535 * 1280, 6)):                 # (8192 / 8 slots an item and a quarter more)
+        t = (sqa.LayerCacheStruct * 1)()
+        t[0].capacity = t[0].budget = b
+        info = sqa.DecodePlanInfo()
+        assert sqa._lib.sqa_decode_plan(t, 1, 1, 8, 1, 64, 1, 2, C.byref(info), None) == code
+        assert (sqa._lib.sqa_decode_workspace_bytes(t, 1, 1, 8, 1, 64, 2) > 0) == (code == 0)
+
+
 def test_plan_argument_errors():
     lib = sqa._lib
     t = (sqa.LayerCacheStruct * 1)()
