@@ -2,8 +2,13 @@
 // sums of the causal softmax(Q K^T / sqrt(D)), added over the g query heads that
 // share a KV head.  This is the producer of sqa_prefill_compress's attn_scores.
 //
-// Two passes over the causal logits on the matrix cores; the P x P probabilities
-// never reach HBM and every sum has a fixed order (no atomics):
+// The causal logits are computed on the matrix cores; the P x P probabilities never
+// reach HBM and every sum has a fixed order (no atomics).  Two ways:
+//   one pass (score_stripes): a workgroup keeps the exponentials of a stripe of query
+//           rows in registers until their sums are known; what most calls use;
+//   two passes, for prompts of more than 4096 tokens, very many short ones, long ones
+//           of many heads at D = 64 in bf16, and (the second alone) normalisers that
+//           the caller has:
 //   pass 1  row statistics of every query row: a reference m_i and the sum of
 //           exp2(s - m_i), stored as m_i and 1 / l_i;
 //   pass 2  per key, sum of exp2(s - m_i) / l_i over its KV head's query rows.
@@ -29,7 +34,7 @@
 //           tiles of Q and their m_i, 1/l_i are staged in LDS the same way; a lane
 //           sees 4 query rows of one key per product and adds exp2(s - m_i) / l_i
 //           into a per-lane column sum over all row tiles and all g heads.
-// What bounds it.  bf16, D = 128: per 16x16 block a lane issues 4 products (64
+// What bounds the two passes.  bf16, D = 128: per 16x16 block a lane issues 4 products (64
 // cycles of the matrix pipeline) and at least 4 x (multiply-add, exp2, add); on this
 // chip vector instructions hide only partly behind matrix instructions of the same
 // SIMD (measured: 16 products + 16 such triples take 201 ns with 4 waves per SIMD,
@@ -132,6 +137,16 @@ template <typename T, int D> struct Rows {
       }
     }
   };
+  // The same for a workgroup of NW waves and ROWS rows (rows beyond `last`: that one again).
+  template <int ROWS, int NW> static __device__ __forceinline__ void stage(const T* __restrict__ src, int row0, int last, char* lds) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t dst = lds_offset(lds);
+#pragma unroll
+    for (int i = wave; i < ROWS / RPI; i += NW) {
+      const int r = i * RPI + lane / PPR;
+      copy16_to_lds(reinterpret_cast<const char*>(src) + (int64_t)min(row0 + r, last) * RB + at(r, lane % PPR) * 16, dst + 1024 * i);
+    }
+  }
   // the fragments of row `row` (global memory) for a lane of contraction group j
   static __device__ __forceinline__ void row_fragments(const T* __restrict__ src, int row, int j, uint4 (&fr)[NP]) {
 #pragma unroll
@@ -164,6 +179,28 @@ template <typename T, int D> struct Rows {
     }
     return c;
   }
+  // the same for NB blocks side by side: a product does not wait for the one before it
+  template <int NB> static __device__ __forceinline__ void block_products(const uint4 (&a)[NP], const uint4 (&b)[NB][NP], sc_f32x4_t (&c)[NB]) {
+#pragma unroll
+    for (int bb = 0; bb < NB; ++bb) c[bb] = sc_f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      if constexpr (sizeof(T) == 2) {
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb)
+          c[bb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(sc_bf16x8_t, a[i]), __builtin_bit_cast(sc_bf16x8_t, b[bb][i]), c[bb], 0, 0, 0);
+      } else {
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb) c[bb] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[i].x), __uint_as_float(b[bb][i].x), c[bb], 0, 0, 0);
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb) c[bb] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[i].y), __uint_as_float(b[bb][i].y), c[bb], 0, 0, 0);
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb) c[bb] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[i].z), __uint_as_float(b[bb][i].z), c[bb], 0, 0, 0);
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb) c[bb] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a[i].w), __uint_as_float(b[bb][i].w), c[bb], 0, 0, 0);
+      }
+    }
+  }
 };
 
 // bf16 at D = 128 keeps one value per row, c_i = m_i + log2(l_i), instead of the pair: the second pass is bound by
@@ -180,7 +217,13 @@ struct ScoreArgs {
   float* ref;                   // [B*Hq][P] m_i in the exp2 domain (pass 2 with given normalisers: ln of them, read only)
   float* inv;                   // [B*Hq][P] 1 / l_i
   float* out;                   // pass 2: [B*Hkv][P] scores, or [B*Hq][P] one partial sum per query head
+  int chunks;                   // one pass: workgroups (and partial sums) per query head
 };
+
+template <int I, typename F> __device__ __forceinline__ void for_down(F& f) {      // f(I), f(I - 1), ... f(0) with constants
+  f(std::integral_constant<int, I>{});
+  if constexpr (I > 0) for_down<I - 1>(f);
+}
 
 template <typename T, int D, int NB>
 __device__ __forceinline__ void score_rowstats(const ScoreArgs& a, char* s_tiles /*2 tiles*/) {
@@ -423,6 +466,312 @@ __device__ __forceinline__ void score_colsum(const ScoreArgs& a, char* s_tiles /
   }
 }
 
+// ---- both passes in one -------------------------------------------------------------------------------------
+// A workgroup takes stripes of 16 NB query rows.  The keys a stripe sees are dealt to the waves in blocks of 16, the
+// last block first (block nkb-1 to wave 0, nkb-2 to wave 1, ...: the waves differ by at most one block and the masked
+// blocks on the diagonal lie in slot 0).  A wave computes S^T = K.Q^T block by block and KEEPS exp2(s - m) of its last
+// SLOTS blocks in registers (m: a reference per lane and row that moves only when a sum shows it is far too low), so
+// that after the waves have put their row sums together the column sums cost one multiply-add per element instead of
+// the products and exponentials once more.  Keys further back than NW x SLOTS blocks are taken twice, as in two passes.
+// A workgroup adds its stripes' column sums up in LDS and writes one partial row; sum_heads_kernel adds those.
+// What bounds it: vector and matrix instructions of two waves per SIMD (the registers allow no more), which on this
+// chip share their time rather than overlap (bf16, D = 128: 606 cycles per block of 16 keys and 64 rows with another
+// wave's beside it, 256 of them products, 292 exponentials and sums; products 33 %, vector instructions 59 % of the time
+// at 256 heads of 2048 tokens), hence the fewest possible of both.  In fp32 the products (2 x 1024 cycles per block at
+// D = 128).  bf16 key blocks come through a ring in LDS, two ahead and across stripes (loaded into registers one ahead:
+// 381 us at 256 heads of 2048 tokens, 8 waves; 247 with no loads at all; 290 through the ring).  Two passes -> one, us:
+//   bf16, D = 128   256 heads of 2048 tokens  330 -> 290;  of 1024  115 -> 82;  of 512  43 -> 28;  64 of 1024  47 -> 26
+//   bf16, D = 64    256 of 1024  94 -> 65;  16 of 2048  54 -> 23;  fp32, D = 64  ragged up to 777, 64 heads  63 -> 30
+//   fp32, D = 128   64 of 1289  322 -> 148;  256 of 512  249 -> 98
+// Rows of fp32 are half as many per stripe, so that registers hold twice the keys.
+template <typename T, int D> struct Stripe;                        // NB row blocks, SLOTS key blocks kept per wave, RING key blocks in LDS
+template <> struct Stripe<bf16_t, 128> { static constexpr int NB = 4, SLOTS = 8, RING = 2; };
+template <> struct Stripe<bf16_t, 64> { static constexpr int NB = 4, SLOTS = 8, RING = 2; };
+template <> struct Stripe<float, 64> { static constexpr int NB = 2, SLOTS = 16, RING = 0; };
+template <> struct Stripe<float, 128> { static constexpr int NB = 2, SLOTS = 14, RING = 0; };
+constexpr float kNoRef = 3.402823466e+38f;                         // minus the reference of a lane that has none yet
+
+template <int CTRL> __device__ __forceinline__ float sc_dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
+template <typename T, int D, int NB, int SLOTS, int RING, int NW>
+__device__ __forceinline__ void score_stripes(const ScoreArgs& a, char* lds) {
+  using R = Rows<T, D>;
+  constexpr int OWN = 16 * NB, QB = OWN * R::RB;
+  static_assert(NB == 2 || NB == 4, "rows of a stripe");
+  static_assert(NB <= NW, "the blocks on the diagonal lie in slot 0");
+  const int P = a.P, Hq = a.Hq, Hkv = a.Hkv, nch = a.chunks;
+  const float scale_log2 = a.scale_log2;
+  int chunk, bh;
+  if (!xcd_tile_head(nch, a.B * Hq, Hq / Hkv, false, chunk, bh)) return;
+  const int b = bh / Hq, kvh = (bh % Hq) / (Hq / Hkv);
+  const int Pq = a.prompt_len ? max(0, min(a.prompt_len[b], P)) : P;
+  const T* Qh = static_cast<const T*>(a.Q) + (int64_t)bh * P * D;
+  const char* Kh = reinterpret_cast<const char*>(static_cast<const T*>(a.K) + ((int64_t)b * Hkv + kvh) * P * D);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n16 = lane & 15, j4 = lane >> 4;
+  constexpr int KB = 16 * R::RB;                                   // bytes of a key block
+  char* const s_ring = lds + QB + wave * RING * KB;                // this wave's key blocks on their way
+  float2* const s_st = reinterpret_cast<float2*>(lds + QB + NW * RING * KB);       // [NW][OWN] (reference, sum) of a wave's keys
+  float* const s_col = reinterpret_cast<float*>(lds + QB + NW * RING * KB + NW * OWN * 8);     // [P rounded up to 16]
+  for (int i = tid; i < P + 15; i += 64 * NW) s_col[i] = 0.f;
+
+  // the workgroup's stripes, longest first, dealt to a head's workgroups back and forth
+  const int n_str = (Pq + OWN - 1) / OWN;
+  auto stripe_at = [&](int k) { return n_str - 1 - (k * nch + ((k & 1) ? nch - 1 - chunk : chunk)); };
+  int st = stripe_at(0);
+  if (st >= 0) R::template stage<OWN, NW>(Qh, st * OWN, Pq - 1, lds);
+  // A wave's key blocks of stripe `of`: from..to in steps of NW (to < 0: none)
+  auto last_block = [&](int of) { return (min((of + 1) * OWN, Pq) + 15) / 16 - 1 - wave; };
+  // The ring is filled in the order in which the blocks are used, across stripes (at the end: the last one again, so
+  // that the number of copies in flight stays the same).  What happens per block is kept to a handful of scalar
+  // instructions: with two waves per SIMD they are not hidden.
+  constexpr int COPIES = KB / 1024;                                // instructions per block
+  struct { const char* at; int kb, to, last, k, buf; bool again; } rq = {Kh + NW * KB, NW, -1, -1, -1, 0, false};
+  const uint32_t roff = (lane / R::PPR) * R::RB + R::at(lane / R::PPR, lane % R::PPR) * 16;
+  auto next_run = [&]() {                                          // the blocks that were not kept once more, or the next stripe's
+    if (!rq.again && rq.last % NW + NW * SLOTS <= rq.last) {
+      rq.again = true;
+      rq.to = rq.last - NW * SLOTS;
+    } else {
+      do {
+        const int of = stripe_at(rq.k + 1);
+        if (of < 0) { rq.kb -= NW; rq.at -= NW * KB; return; }
+        ++rq.k;
+        rq.last = last_block(of);
+      } while (rq.last < 0);
+      rq.again = false;
+      rq.to = rq.last;
+    }
+    rq.kb = rq.last % NW;
+    rq.at = Kh + (int64_t)rq.kb * KB;
+  };
+  auto request = [&]() {
+    const uint32_t dst = lds_offset(s_ring) + rq.buf;
+    if (16 * rq.kb + 16 <= P) {
+#pragma unroll
+      for (int i = 0; i < COPIES; ++i) copy16_to_lds(rq.at + 1024 * i, roff ^ (16 * R::at(i * R::RPI, 0)), dst + 1024 * i);
+    } else {                                                       // rows beyond the end: the last one again
+#pragma unroll
+      for (int i = 0; i < COPIES; ++i) {
+        const int r = i * R::RPI + lane / R::PPR;
+        copy16_to_lds(rq.at, (uint32_t)(min(r, P - 1 - 16 * rq.kb) * R::RB + R::at(r, lane % R::PPR) * 16), dst + 1024 * i);
+      }
+    }
+    rq.buf = rq.buf + KB == RING * KB ? 0 : rq.buf + KB;
+    rq.kb += NW;
+    rq.at += NW * KB;
+    if (rq.kb > rq.to) next_run();
+  };
+  int use = 0;                                                     // ring position of the next block to be used
+  if constexpr (RING > 0) {
+    if (st >= 0) {
+      next_run();
+#pragma unroll
+      for (int i = 0; i < RING - 1; ++i) request();
+    }
+  }
+  for (int k = 0; st >= 0; ++k) {
+    const int i0 = st * OWN;
+    const int next = stripe_at(k + 1);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");               // this wave's part of the stripe's Q has landed
+    __syncthreads();                                               // ... everyone's; and the column sums of the last stripe are in
+    uint4 kf[R::NP];
+    auto load_k = [&](int kb) {                                    // (without a ring: the next block, one ahead)
+      if constexpr (RING == 0) {
+        const uint32_t off = (uint32_t)min(n16, P - 1 - 16 * kb) * R::RB + 16 * j4;
+        const char* base = Kh + (int64_t)kb * KB;
+#pragma unroll
+        for (int i = 0; i < R::NP; ++i) kf[i] = ld16(base + (off + 64 * i));
+      }
+    };
+    auto arrive_k = [&]() {                                        // (with one: the next block in order)
+      if constexpr (RING > 0) {
+        request();
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((RING - 1) * COPIES) : "memory");
+        const char* at = s_ring + use;
+#pragma unroll
+        for (int i = 0; i < R::NP; ++i) kf[i] = *reinterpret_cast<const uint4*>(at + n16 * R::RB + R::at(n16, 4 * i + j4) * 16);
+        use = use + KB == RING * KB ? 0 : use + KB;
+      }
+    };
+    const int kb_last = last_block(st), kb_first = kb_last < 0 ? -1 : kb_last % NW;    // this wave's blocks: kb_first, + NW, ... kb_last
+    int kb = kb_first;
+    if (kb >= 0) load_k(kb);
+    uint4 qf[NB][R::NP];
+#pragma unroll
+    for (int bb = 0; bb < NB; ++bb)
+#pragma unroll
+      for (int i = 0; i < R::NP; ++i) {
+        const int row = 16 * bb + n16;
+        qf[bb][i] = *reinterpret_cast<const uint4*>(lds + row * R::RB + R::at(row, 4 * i + j4) * 16);
+      }
+    float nm[NB], l[NB];                                           // minus the reference, the sum against it
+#pragma unroll
+    for (int bb = 0; bb < NB; ++bb) { nm[bb] = kNoRef; l[bb] = 0.f; }
+    sc_f32x4_t E[SLOTS][NB];
+    auto exps = [&](sc_f32x4_t (&s4)[NB], sc_f32x4_t (&e4)[NB], auto kept_tag) {
+      constexpr int S = decltype(kept_tag)::value;                 // E[S ..] hold values against the present reference
+      float part[NB];
+      bool far = false;
+      auto one = [&](int bb) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) e4[bb][e] = __builtin_amdgcn_exp2f(fmaf(s4[bb][e], scale_log2, nm[bb]));
+        part[bb] = (e4[bb][0] + e4[bb][1]) + (e4[bb][2] + e4[bb][3]);
+      };
+#pragma unroll
+      for (int bb = 0; bb < NB; ++bb) { one(bb); far |= !(part[bb] < kRefFar); }
+      if (__builtin_amdgcn_ballot_w64(far)) {
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb) {
+          const float top = fmaxf(fmaxf(s4[bb][0], s4[bb][1]), fmaxf(s4[bb][2], s4[bb][3])) * scale_log2;
+          const float mx = fmaxf(-nm[bb], top), alpha = __builtin_amdgcn_exp2f(-nm[bb] - mx);
+          l[bb] *= alpha;
+#pragma unroll
+          for (int s = S; s < SLOTS; ++s) E[s][bb] *= alpha;
+          nm[bb] = -mx;
+          one(bb);
+        }
+      }
+#pragma unroll
+      for (int bb = 0; bb < NB; ++bb) l[bb] += part[bb];
+    };
+    // blocks further back than what is kept: sums only
+    for (; kb >= 0 && kb + NW * SLOTS <= kb_last; kb += NW) {
+      sc_f32x4_t s4[NB], e4[NB];
+      arrive_k();
+      R::template block_products<NB>(kf, qf, s4);
+      load_k(kb + NW);
+      exps(s4, e4, std::integral_constant<int, SLOTS>{});
+    }
+    auto slot = [&](auto tag) {
+      constexpr int S = decltype(tag)::value;
+      if (kb_last - NW * S < 0) return;                            // (wave-uniform)
+      sc_f32x4_t s4[NB];
+      arrive_k();
+      R::template block_products<NB>(kf, qf, s4);
+      if constexpr (S > 0) {
+        load_k(kb_last - NW * (S - 1));
+      } else if (16 * kb_last + 15 > i0) {                         // on the diagonal
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            s4[bb][e] = 16 * kb_last + 4 * j4 + e <= min(i0 + 16 * bb + n16, Pq - 1) ? s4[bb][e] : -INFINITY;
+      }
+      exps(s4, E[S], std::integral_constant<int, S + 1>{});
+    };
+    for_down<SLOTS - 1>(slot);
+    // ---- the rows' sums: the 4 lanes of a row, then the waves
+    auto merge = [](float& m, float& s, float mo, float so) {
+      const float mx = fmaxf(m, mo);
+      s = s * __builtin_amdgcn_exp2f(m - mx) + so * __builtin_amdgcn_exp2f(mo - mx);
+      m = mx;
+    };
+    float m, s;
+    {
+      float m2[2], l2[2];
+      const bool up = lane & 32, up2 = lane & 16;
+      if constexpr (NB == 4) {                                     // lane j4 ends up with row block j4
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          m2[x] = up ? -nm[2 + x] : -nm[x]; l2[x] = up ? l[2 + x] : l[x];
+          const float mo = __shfl_xor(up ? -nm[x] : -nm[2 + x], 32, 64), lo = __shfl_xor(up ? l[x] : l[2 + x], 32, 64);
+          merge(m2[x], l2[x], mo, lo);
+        }
+        m = up2 ? m2[1] : m2[0]; s = up2 ? l2[1] : l2[0];
+        const float mo = __shfl_xor(up2 ? m2[0] : m2[1], 16, 64), lo = __shfl_xor(up2 ? l2[0] : l2[1], 16, 64);
+        merge(m, s, mo, lo);
+      } else {                                                     // lanes 0 and 1, 2 and 3 with row blocks 0, 1
+        m = up ? -nm[1] : -nm[0]; s = up ? l[1] : l[0];
+        const float mo = __shfl_xor(up ? -nm[0] : -nm[1], 32, 64), lo = __shfl_xor(up ? l[0] : l[1], 32, 64);
+        merge(m, s, mo, lo);
+        merge(m, s, __shfl_xor(m, 16, 64), __shfl_xor(s, 16, 64));
+      }
+      (void)m2; (void)l2; (void)up2;
+    }
+    const int my_row = NB == 4 ? lane : 16 * (lane >> 5) + n16;
+    s_st[wave * OWN + my_row] = make_float2(m, s);
+    __syncthreads();
+    if (next >= 0) R::template stage<OWN, NW>(Qh, next * OWN, Pq - 1, lds);          // (all waves have their fragments)
+    float2 w[NW];
+#pragma unroll
+    for (int x = 0; x < NW; ++x) w[x] = s_st[x * OWN + my_row];
+    m = w[0].x;
+#pragma unroll
+    for (int x = 1; x < NW; ++x) m = fmaxf(m, w[x].x);
+    s = 0.f;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) s += w[x].y * __builtin_amdgcn_exp2f(w[x].x - m);
+    const float inv = i0 + my_row < Pq ? 1.f / s : 0.f;            // (rows of padding count nothing)
+    float M[NB], I[NB], f[NB];
+#pragma unroll
+    for (int bb = 0; bb < NB; ++bb) {
+      M[bb] = __shfl(m, 64 / NB * bb + n16, 64);
+      I[bb] = __shfl(inv, 64 / NB * bb + n16, 64);
+      f[bb] = __builtin_amdgcn_exp2f(-nm[bb] - M[bb]) * I[bb];
+    }
+
+    // ---- the column sums
+    auto add = [&](const float (&c)[4], int at) {                  // c[e]: this lane's share of key 16 at + 4 j4 + e
+      const bool b0 = lane & 1, b1 = lane & 2;
+      const float a0 = (b0 ? c[1] : c[0]) + sc_dpp<0xB1>(b0 ? c[0] : c[1]);
+      const float a1 = (b0 ? c[3] : c[2]) + sc_dpp<0xB1>(b0 ? c[2] : c[3]);
+      float v = (b1 ? a1 : a0) + sc_dpp<0x4E>(b1 ? a0 : a1);      // ... of key 16 at + 4 j4 + n16 % 4
+      v += sc_dpp<0x128>(v);                                       // row_ror:8, row_ror:4
+      v += sc_dpp<0x124>(v);
+      // (in a stripe a key belongs to one wave, and stripes follow each other: the order of the additions is fixed)
+      if (n16 < 4) __hip_atomic_fetch_add(&s_col[16 * at + 4 * j4 + n16], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    auto column = [&](auto tag) {
+      constexpr int S = decltype(tag)::value;
+      const int at = kb_last - NW * S;
+      if (at < 0) return;
+      float c[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        c[e] = 0.f;
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb) {
+          const float p = E[S][bb][e] * f[bb];
+          if (S == 0) c[e] += 16 * at + 4 * j4 + e <= min(i0 + 16 * bb + n16, Pq - 1) ? p : 0.f;
+          else c[e] = bb == 0 ? p : fmaf(E[S][bb][e], f[bb], c[e]);
+        }
+      }
+      add(c, at);
+    };
+    for_down<SLOTS - 1>(column);
+    if (kb_first >= 0 && kb_first + NW * SLOTS <= kb_last) {       // the blocks that were not kept, once more
+      load_k(kb_first);
+      for (int at = kb_first; at + NW * SLOTS <= kb_last; at += NW) {
+        sc_f32x4_t s4[NB];
+        arrive_k();
+        R::template block_products<NB>(kf, qf, s4);
+        load_k(at + NW);
+        float c[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            c[e] = fmaf(__builtin_amdgcn_exp2f(fmaf(s4[bb][e], scale_log2, -M[bb])), I[bb], c[e]);
+        add(c, at);
+      }
+    }
+    st = next;
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // (copies that nobody waited for)
+  __syncthreads();
+  float* out = a.out + ((int64_t)bh * nch + chunk) * P;
+  const int me = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0));    // (= lane, not kept in a register all along)
+  for (int i = 64 * wave + me; i < P; i += 64 * NW) out[i] = s_col[i];
+}
+template <typename T, int D, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void score_stripes_kernel(const ScoreArgs a) {
+  extern __shared__ char s_tiles[];
+  score_stripes<T, D, Stripe<T, D>::NB, Stripe<T, D>::SLOTS, Stripe<T, D>::RING, NW>(a, s_tiles);
+}
+
 // The two passes of the headline configuration under names of their own, and all others.
 __global__ __launch_bounds__(kScThreads) void score_rowstats_mfma_kernel(const ScoreArgs a) {
   extern __shared__ char s_tiles[];
@@ -448,9 +797,17 @@ __global__ __launch_bounds__(256) void sum_heads_kernel(const float* __restrict_
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
   const int64_t bk = i / P, j = i % P;
-  float t = 0.f;
-  for (int h = 0; h < g; ++h) t += part[(bk * g + h) * P + j];
-  scores[i] = t;
+  double t = 0.0;                                 // (up to some hundred terms: fp32 would round more than the terms are off)
+  int h = 0;
+  for (; h + 8 <= g; h += 8) {
+    float v[8];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) v[x] = part[(bk * g + h + x) * P + j];
+#pragma unroll
+    for (int x = 0; x < 8; ++x) t += v[x];
+  }
+  for (; h < g; ++h) t += part[(bk * g + h) * P + j];
+  scores[i] = (float)t;
 }
 
 // the caller's normalisers, where they lie in memory that the call writes
@@ -494,14 +851,96 @@ static sqa_status launch_scores(ScoreArgs a, bool lse, float* part /*NULL: not s
   return SQA_OK;
 }
 
+
+template <typename T, int D, int NW>
+static sqa_status launch_stripes(ScoreArgs a, float* part, float* scores, hipStream_t st) {
+  using R = Rows<T, D>;
+  constexpr int OWN = 16 * Stripe<T, D>::NB;
+  const int g = a.Hq / a.Hkv, heads = a.B * a.Hq;
+  const size_t lds = (size_t)OWN * R::RB + (size_t)NW * (16 * R::RB * Stripe<T, D>::RING + OWN * 8) + (size_t)(a.P + 15) * sizeof(float);
+  if (lds > 48 * 1024) SQA_HIP_CHECK(allow_dynamic_lds(reinterpret_cast<const void*>(score_stripes_kernel<T, D, NW>), lds));
+  const bool direct = g * a.chunks == 1;
+  a.out = direct ? scores : part;
+  score_stripes_kernel<T, D, NW><<<(unsigned)(((heads / g + 7) / 8) * 8 * g * a.chunks), 64 * NW, lds, st>>>(a);
+  if (!direct) {
+    const int64_t n = (int64_t)a.B * a.Hkv * a.P;
+    sum_heads_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(part, g * a.chunks, a.P, n, scores);
+  }
+  SQA_HIP_CHECK(hipGetLastError());
+  return SQA_OK;
+}
+// How a call in one pass is cut: waves per workgroup (4: two workgroups per CU; 8: one, which keeps twice the keys of a
+// stripe) and workgroups per query head.  The time is estimated as rounds of resident workgroups x the longest one's
+// stripes, each a fixed part and a part per key block of a wave, with the constants (us) that fit 420 measured calls
+// (16 to 1024 heads, 45 to 4096 tokens, both wave counts, 256 to 2048 workgroups) within 13 % rms.  Measured, us:
+//   bf16, D = 128   16 heads of 2048 tokens  4 waves 43, 8 waves 26.5;  64 of 777  21.3 and 22.4;  256 of 777  57 and 68;
+//                   256 of 2048  304 and 290
+//   fp32, D = 128   16 of 2048  117 and 86;  256 of 512  98 and 112
+struct StripeCut { int waves, chunks; };
+constexpr int kStripeMaxP = 4096;
+static StripeCut stripe_cut(sqa_dtype dt, int D, int64_t heads, int g, int P, bool ragged, int64_t most_chunks) {
+  const bool f32 = dt == SQA_F32;
+  const int own = f32 ? 32 : 64, slots = f32 ? (D == 64 ? 16 : 14) : 8;
+  const double stripe = f32 ? 1.6 : 2.5, block = f32 ? (D == 64 ? 1.05 : 1.9) : (D == 64 ? 0.46 : 0.63);
+  const double again = f32 && D == 64 ? 0.5 : 1.2;           // a key block that is not kept costs this much more
+  const double half_full = f32 ? 0.5 : 0.75;     // 4 waves, one workgroup per CU
+  const int n_str = (P + own - 1) / own;
+  StripeCut best = {4, 1};
+  double best_us = 1e30;
+  for (int waves = 4; waves <= 8; waves += 4)
+    // (sequences of different length, which the host does not see: more and shorter workgroups even out long ones; 64 heads
+    // of 2766 tokens and 64 of 1383, bf16, D = 128: 261 us in one round, 183 in three; 5 x 32 heads of 613 to 306 23 and 38)
+    for (int rounds = ragged ? (P > 2048 ? 3 : (P > 1024 ? 2 : 1)) : 1; rounds <= 4; ++rounds) {
+      const int64_t resident = waves == 4 ? 512 : 256;
+      int64_t n = resident * rounds / heads;
+      n = n < n_str ? n : n_str;
+      n = n < most_chunks ? n : most_chunks;
+      n = n < 1 ? 1 : n;
+      double us = 1.5;                            // a workgroup's start: nothing is on its way yet
+      for (int64_t k = 0, st; (st = n_str - 1 - (k * n + ((k & 1) ? n - 1 : 0))) >= 0; ++k) {
+        const int64_t rows = (st + 1) * own < P ? (st + 1) * own : P, blocks = ((rows + 15) / 16 + waves - 1) / waves;
+        us += stripe + block * (blocks + (blocks > slots ? again * (blocks - slots) : 0.0));
+      }
+      us *= (double)((heads * n + resident - 1) / resident);
+      // Keys that the workgroups of one XCD read at a time, in units of its 4 MB of L2: beyond, they come from further
+      // away (256 heads of 2048 tokens, bf16, D = 128, 8 waves: 1 workgroup per head 380 us, 2 294; 1024 tokens 100 and 89).
+      const int64_t at_once = (heads * n < resident ? heads * n : resident) / 8;
+      const double l2 = (double)(at_once + n * g - 1) / (double)(n * g) * P * D * (f32 ? 4 : 2) / (4 << 20);
+      if (l2 > 1.0) us *= 1.0 + (f32 ? 0.02 : 0.08) * (l2 - 1.0);
+      if (waves == 4 && heads * n <= resident / 2) us *= half_full;
+      if (us < best_us) { best_us = us; best = {waves, (int)n}; }
+    }
+  return best;
+}
+// Two passes are still the better way for very many short prompts, whose stripes cost more than their few key blocks
+// (1024 heads, bf16, D = 64, 45 tokens 11.2 us, 12.0 in one pass, 200 tokens 32.7 and 34.4; fp32, 45 tokens 15.2 and 17.6), and for long prompts of many
+// heads in bf16 at D = 64, where most keys are taken twice either way (120 heads of 3000 tokens 253 us and 279).
+static bool two_passes(sqa_dtype dt, int D, int64_t heads, int P) {
+  if (P > kStripeMaxP) return true;
+  if (heads >= 768 && P <= (dt == SQA_BF16 && D == 64 ? 256 : 64)) return true;
+  return dt == SQA_BF16 && D == 64 && P > 2560 && heads >= 96;
+}
+
 }  // namespace sqa
 
-// Per query row: reference, 1/sum, and (pass 2 split by query head) a partial column sum.  A workspace of two
-// floats per row is enough too: the split is then left out.
+// In one pass: a partial row of column sums per workgroup of a query head.  In two, per query row: reference, 1/sum, and
+// (pass 2 split by query head) a partial column sum.  A workspace of two floats per row is enough too: fewer workgroups,
+// or no split.
 extern "C" size_t sqa_prefill_scores_workspace_bytes(int B, int Hq, int Hkv, int P, int D) {
-  (void)Hkv; (void)D;
+  (void)D;
   if (B < 1 || Hq < 1 || P < 1) return 0;
-  return (size_t)B * Hq * P * 3 * sizeof(float);
+  if (Hkv < 1 || Hkv > Hq) Hkv = Hq;
+  // (the element type is not known here: the most of what either needs)
+  const int64_t heads = (int64_t)B * Hq;
+  int floats = 3;
+  for (const sqa_dtype dt : {SQA_F32, SQA_BF16})
+    for (const int k : {0, 1, 2, 3}) {
+      const int d = k & 1 ? 64 : 128;
+      const bool ragged = k >= 2;
+      const int n = P <= sqa::kStripeMaxP ? sqa::stripe_cut(dt, d, heads, Hq / Hkv, P, ragged, INT32_MAX).chunks : 0;
+      floats = n > floats ? n : floats;
+    }
+  return (size_t)heads * P * floats * sizeof(float);
 }
 
 extern "C" sqa_status sqa_prefill_scores(const void* Q, const void* K, sqa_dtype dt,
@@ -541,6 +980,21 @@ static sqa_status prefill_scores_impl(const void* Q, const void* K, const float*
     copy_lse = shares(scores_out, (size_t)B * Hkv * P);
     if (copy_lse) { a.ref = ws; part = ws + rows; }
     else if (shares(ws, rows)) part = shares(ws + rows, rows) ? nullptr : ws + rows;
+  }
+  a.chunks = 0;
+  if (!lse && !two_passes(dt, D, (int64_t)B * Hq, P)) {
+    const StripeCut cut = stripe_cut(dt, D, (int64_t)B * Hq, Hq / Hkv, P, a.prompt_len != nullptr, (int64_t)(ws_bytes / (rows * sizeof(float))));
+    a.chunks = cut.chunks;
+    auto launch = [&](auto type, auto dim) {
+      using T = decltype(type);
+      constexpr int D_ = decltype(dim)::value;
+      hipStream_t st = static_cast<hipStream_t>(stream);
+      return cut.waves == 4 ? launch_stripes<T, D_, 4>(a, ws, scores_out, st) : launch_stripes<T, D_, 8>(a, ws, scores_out, st);
+    };
+    using D64 = std::integral_constant<int, 64>;
+    using D128 = std::integral_constant<int, 128>;
+    if (dt == SQA_F32) return D == 64 ? launch(float{}, D64{}) : launch(float{}, D128{});
+    return D == 64 ? launch(bf16_t{}, D64{}) : launch(bf16_t{}, D128{});
   }
   // Pass 2 per query head where the KV heads alone give the chip too few workgroups (8 per CU), unless the call is
   // so small that the additional launch is what one sees.  64 query heads over 8, one sequence, 1024 tokens, bf16,

@@ -221,6 +221,36 @@ def test_prefill_scores_with_runs_of_keys_that_count_nothing(sqa, dtype, D):
         assert np.all(got[h][off] == 0.0) and rel_err(got[h], ref) < TOL[dtype]
 
 
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("B,Hkv,g,P,plen", [
+    (1, 1, 1, 33, None), (1, 1, 2, 63, [31]), (2, 1, 1, 65, [65, 0]),     # edges of a stripe (32 or 64 rows) and of a block of 16 keys
+    (1, 2, 2, 1100, None), (1, 1, 1, 2115, None),                         # few heads: 8 waves; beyond what they keep of a stripe's keys
+    (40, 4, 1, 577, [577 - 3 * b for b in range(40)]),                    # many heads: 4 waves, some keys taken twice
+    (24, 4, 2, 1040, None)])                                              # ... several stripes per workgroup
+def test_prefill_scores_in_one_pass(sqa, dtype, D, B, Hkv, g, P, plen):
+    """Stripes of query rows whose exponentials stay in registers: one and several stripes per workgroup, both wave counts,
+    prompts longer than what is kept, sequences of other lengths, and a workspace with room for fewer workgroups.  fp32
+    arithmetic on exact inputs: a logit's error is below D 2^-24 |q| |k| / sqrt(D) ~ 1e-5, its exponential's the same."""
+    gen = torch.Generator(device="cpu").manual_seed(P + B)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K = (torch.randn(B, h, P, D, generator=gen).to(dt).to(DEV) for h in (Hkv * g, Hkv))
+    lens = torch.tensor([P] * B if plen is None else plen, dtype=torch.int32, device=DEV)
+    opts = None if plen is None else sqa.batch_opts(prompt_len=lens)
+    got = np64(sqa.prefill_scores(Q, K, opts=opts))
+    small = torch.full((B, Hkv, P), float("nan"), device=DEV)
+    ws = torch.empty(B * Hkv * g * P * 2, device=DEV)
+    rc = sqa._lib.sqa_prefill_scores_ex(Q.data_ptr(), K.data_ptr(), 0 if dtype == "f32" else 1, B, Hkv * g, Hkv, P, D, small.data_ptr(),
+                                        ws.data_ptr(), ws.numel() * 4, torch.cuda.current_stream().cuda_stream, sqa._opts(opts))
+    assert rc == 0 and rel_err(np64(small), got) < 1e-6      # (the same terms added in another order)
+    for b in sorted({0, B // 2, B - 1}):
+        m = P if plen is None else plen[b]
+        for h in sorted({0, Hkv - 1}):
+            assert np.all(got[b, h, m:] == 0.0)
+            if m:
+                ref = O.prefill_scores(np64(Q[b, h * g:(h + 1) * g, :m]), np64(K[b, h, :m]))
+                assert rel_err(got[b, h, :m], ref) < 1e-5
+
+
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 128)])
 @pytest.mark.parametrize("g,P", [(1, 200), (4, 200), (4, 100)])      # column sums per KV head, per query head, per KV head
 def test_given_normalisers_in_memory_the_call_writes(sqa, dtype, D, g, P):

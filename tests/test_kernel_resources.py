@@ -55,3 +55,11 @@ def test_other_hot_kernels(res):
     assert _one(res, "importance_partial_kernel", "bf16_tELb0")["Occupancy"] >= 7
     assert _one(res, "score_colsum_mfma_kernel")["Occupancy"] >= 4
     assert _one(res, "score_rowstats_mfma_kernel")["Occupancy"] >= 4
+
+
+def test_one_pass_scores_keep_their_registers(res):
+    # two waves per SIMD: a stripe's exponentials lie in registers
+    stripes = {k: v for k, v in res.items() if "score_stripes_kernel" in k}
+    assert len(stripes) == 8                           # 2 types x 2 head sizes x 4 or 8 waves
+    for k, v in stripes.items():
+        assert v["ScratchSize"] == 0 and v["VGPRs Spill"] == 0 and v["Occupancy"] >= 2, k
