@@ -30,6 +30,7 @@
 // as the streaming; one wave walks it 16 rows at a time with nothing to merge.
 #include "sqa_common.h"
 #include <cstring>
+#include <type_traits>
 
 namespace sqa {
 
@@ -114,34 +115,77 @@ __device__ __forceinline__ float ld_agent_at(const float* base, int i) {
   return __hip_atomic_load((const g_float_t*)((const g_char_t*)base + (uint32_t)i * 4u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+template <int CTRL> __device__ __forceinline__ float dpp_mov(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
+// The values of the two lanes whose numbers differ by O (8, 16 or 32): own row group and the other one; for 16 and 32
+// the lower lane's first, in both lanes.  Vector instructions: a shuffle through LDS costs its latency.
+template <int O> __device__ __forceinline__ void both(float v, float& lo, float& hi) {
+  static_assert(O == 8 || O == 16 || O == 32, "row groups of a wave");
+  if constexpr (O == 8) {
+    lo = v; hi = dpp_mov<0x128>(v);               // row_ror:8
+  } else {
+    typedef unsigned u2_t __attribute__((ext_vector_type(2)));
+    const unsigned x = __float_as_uint(v);
+    const u2_t r = O == 16 ? __builtin_bit_cast(u2_t, __builtin_amdgcn_permlane16_swap(x, x, false, false))
+                           : __builtin_bit_cast(u2_t, __builtin_amdgcn_permlane32_swap(x, x, false, false));
+    lo = __uint_as_float(r.x); hi = __uint_as_float(r.y);
+  }
+}
+// wave-wide minimum / maximum, in every lane: within rows of 16 lanes, then the rows
+__device__ __forceinline__ float wave_min(float v) {
+  v = fminf(v, dpp_mov<0xB1>(v));
+  v = fminf(v, dpp_mov<0x4E>(v));
+  v = fminf(v, dpp_mov<0x141>(v));
+  v = fminf(v, dpp_mov<0x140>(v));
+  float a, b;
+  both<16>(v, a, b);
+  both<32>(fminf(a, b), a, b);
+  return fminf(a, b);
+}
+__device__ __forceinline__ uint32_t wave_max_u(uint32_t v) {
+  auto step = [](uint32_t x, float y) { const uint32_t o = __float_as_uint(y); return o > x ? o : x; };
+  v = step(v, dpp_mov<0xB1>(__uint_as_float(v)));
+  v = step(v, dpp_mov<0x4E>(__uint_as_float(v)));
+  v = step(v, dpp_mov<0x141>(__uint_as_float(v)));
+  v = step(v, dpp_mov<0x140>(__uint_as_float(v)));
+  float a, b;
+  both<16>(__uint_as_float(v), a, b);
+  v = step(__float_as_uint(a), b);
+  both<32>(__uint_as_float(v), a, b);
+  return step(__float_as_uint(a), b);
+}
+// the largest 64-bit key: its upper half, then the lower half among the lanes that have it
+__device__ __forceinline__ unsigned long long wave_max64(unsigned long long v) {
+  const uint32_t hi = wave_max_u((uint32_t)(v >> 32));
+  const uint32_t lo = wave_max_u((uint32_t)(v >> 32) == hi ? (uint32_t)v : 0u);
+  return ((unsigned long long)hi << 32) | lo;
+}
+
 // block-wide reductions; every thread gets the result
-// solo: only wave 0 of the workgroup is still running (the others have left),
-// so the reduction stays inside the wave and no barrier may be used.
-__device__ __forceinline__ float block_min(float v, float* s_red, bool solo) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fminf(v, __shfl_xor(v, o, SQA_WAVE));
+// solo: only one wave of the workgroup is still running (the others have left) or
+// has a unit of its own, so the reduction stays inside the wave and no barrier may be used.
+template <int NW> __device__ __forceinline__ float block_min(float v, float* s_red, bool solo) {
+  v = wave_min(v);
   if (solo) return v;
   __syncthreads();
   if ((threadIdx.x & (SQA_WAVE - 1)) == 0) s_red[threadIdx.x / SQA_WAVE] = v;
   __syncthreads();
   v = s_red[0];
 #pragma unroll
-  for (int w = 1; w < kDecWaves; ++w) v = fminf(v, s_red[w]);
+  for (int w = 1; w < NW; ++w) v = fminf(v, s_red[w]);
   return v;
 }
-__device__ __forceinline__ unsigned long long block_max64(unsigned long long v, unsigned long long* s_red, bool solo) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long other = __shfl_xor(v, o, SQA_WAVE);
-    v = other > v ? other : v;
-  }
+template <int NW> __device__ __forceinline__ unsigned long long block_max64(unsigned long long v, unsigned long long* s_red, bool solo) {
+  v = wave_max64(v);
   if (solo) return v;
   __syncthreads();
   if ((threadIdx.x & (SQA_WAVE - 1)) == 0) s_red[threadIdx.x / SQA_WAVE] = v;
   __syncthreads();
   v = s_red[0];
 #pragma unroll
-  for (int w = 1; w < kDecWaves; ++w) v = s_red[w] > v ? s_red[w] : v;
+  for (int w = 1; w < NW; ++w) v = s_red[w] > v ? s_red[w] : v;
   return v;
 }
 
@@ -152,27 +196,23 @@ __device__ __forceinline__ unsigned long long block_max64(unsigned long long v, 
 // slot that is evicted (the leaver moves there).  `mn` = min over the heavy
 // scores, already reduced over the block.  pos_override: slot whose position
 // is not yet in memory (or -1).
-__device__ __forceinline__ int pick_victim(const float* sc, const int32_t* posu, int hh, float mn, float leaver_score,
+template <int NW> __device__ __forceinline__ int pick_victim(const float* sc, const int32_t* posu, int hh, float mn, float leaver_score,
                                            int override_slot, int override_pos, unsigned long long* s_red64,
                                            bool solo, int t /*thread index among the nthr threads at work*/) {
   if (leaver_score <= mn) return -1;             // uniform over the block
   unsigned long long best = 0ull;                // (position + 1) << 32 | slot
-  const int nthr = solo ? SQA_WAVE : kDecThreads;
+  const int nthr = solo ? SQA_WAVE : NW * SQA_WAVE;
   for (int i = t; i < hh; i += nthr)
     if (sc[i] == mn) {
       const int ps = i == override_slot ? override_pos : posu[i];
       const unsigned long long key = ((unsigned long long)(uint32_t)(ps + 1) << 32) | (uint32_t)i;
       best = key > best ? key : best;
     }
-  return (int)(uint32_t)block_max64(best, s_red64, solo);
+  return (int)(uint32_t)block_max64<NW>(best, s_red64, solo);
 }
 
 // v_exp_f32: 2^x, 1 ulp, denormal results flush to 0 (harmless in a softmax)
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-template <int CTRL> __device__ __forceinline__ float dpp_mov(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
 
 // sum over the LPR consecutive lanes that share a row; every lane gets the sum
 template <int LPR> __device__ __forceinline__ float group_sum(float v) {
@@ -182,7 +222,7 @@ template <int LPR> __device__ __forceinline__ float group_sum(float v) {
   v += dpp_mov<0x4E>(v);            // quad_perm [2,3,0,1]
   v += dpp_mov<0x141>(v);           // row_half_mirror
   if (LPR >= 16) v += dpp_mov<0x140>(v);   // row_mirror
-  if (LPR >= 32) v += __shfl_xor(v, 16, SQA_WAVE);
+  if constexpr (LPR >= 32) { float a, b; both<16>(v, a, b); v = a + b; }
   return v;
 }
 
@@ -426,8 +466,8 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
     } else {                                      // no decision carried over: take it now
       float mn = INFINITY;
       for (int i = tix; i < hh; i += nthr0) mn = fminf(mn, sc[i]);
-      mn = block_min(mn, s_red, wpu);
-      moved_to = pick_victim(sc, posu, hh, mn, sc[slot_wr], -1, 0, s_red64, wpu, tix);
+      mn = block_min<kDecWaves>(mn, s_red, wpu);
+      moved_to = pick_victim<kDecWaves>(sc, posu, hh, mn, sc[slot_wr], -1, 0, s_red64, wpu, tix);
     }
   }
   // the ring leaver's score and position, needed in step 3 if it moves
@@ -567,8 +607,10 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
         sv[e] = d;
         mx = fmaxf(mx, d);
       }
-      mx = fmaxf(mx, __shfl_xor(mx, 16, SQA_WAVE));
-      mx = fmaxf(mx, __shfl_xor(mx, 32, SQA_WAVE));
+      float ra, rb;
+      both<16>(mx, ra, rb);
+      both<32>(fmaxf(ra, rb), ra, rb);
+      mx = fmaxf(ra, rb);
       const float m_new = fmaxf(m_run, mx);
       const float ms = m_new == -INFINITY ? 0.f : m_new;
       const float alpha = fast_exp2(m_run - ms);
@@ -637,8 +679,10 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
         request_k(base + TSTEP);
       }
     }
-    l_run += __shfl_xor(l_run, 16, SQA_WAVE);
-    l_run += __shfl_xor(l_run, 32, SQA_WAVE);
+    float la, lb;
+    both<16>(l_run, la, lb);
+    both<32>(la + lb, la, lb);
+    l_run = la + lb;
     if (hd < G) {
       if (j4 == 0) { s_m[wave][hd] = m_run; s_l[wave][hd] = l_run; }
 #pragma unroll
@@ -724,21 +768,24 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
     // ---- 2. combine row groups of the wave, then the waves --------------------
 #pragma unroll
     for (int g = 0; g < G; ++g) {
+      auto fold = [&](auto apart) {
+        constexpr int O = decltype(apart)::value;
+        if constexpr (O >= LPR) {
+          float ma, mb, a, b;
+          both<O>(m[g], ma, mb);
+          const float mx = fmaxf(ma, mb);
+          const float ms = mx == -INFINITY ? 0.f : mx;
+          const float fa = fast_exp2(ma - ms), fb = fast_exp2(mb - ms);
+          both<O>(l[g], a, b);
+          l[g] = a * fa + b * fb;
 #pragma unroll
-      for (int o = LPR; o < SQA_WAVE; o <<= 1) {
-        const float mo = __shfl_xor(m[g], o, SQA_WAVE);
-        const float lo2 = __shfl_xor(l[g], o, SQA_WAVE);
-        const float mx = fmaxf(m[g], mo);
-        const float ms = mx == -INFINITY ? 0.f : mx;
-        const float fa = fast_exp2(m[g] - ms), fb = fast_exp2(mo - ms);
-        l[g] = l[g] * fa + lo2 * fb;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) {
-          const float ao = __shfl_xor(acc[g][e], o, SQA_WAVE);
-          acc[g][e] = acc[g][e] * fa + ao * fb;
+          for (int e = 0; e < EPL; ++e) { both<O>(acc[g][e], a, b); acc[g][e] = a * fa + b * fb; }
+          m[g] = mx;
         }
-        m[g] = mx;
-      }
+      };
+      fold(std::integral_constant<int, 8>{});
+      fold(std::integral_constant<int, 16>{});
+      fold(std::integral_constant<int, 32>{});
       if (r == 0) {
         if (c == 0) { s_m[wave][g] = m[g]; s_l[wave][g] = l[g]; }
 #pragma unroll
@@ -980,7 +1027,7 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
       }
     }
     if (decide) {
-      const float low = block_min(mn, s_red, solo);   // (the barrier inside also orders the s_ctlf writes)
+      const float low = block_min<kDecWaves>(mn, s_red, solo);   // (the barrier inside also orders the s_ctlf writes)
       // positions as they will be after step 4: the moved token brings its own
       int v = -1;
       if (!(s_ctlf[wq][0] <= low)) {
@@ -995,8 +1042,8 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
             key = ((unsigned long long)(uint32_t)(ps + 1) << 32) | (uint32_t)mn_slot;
           }
         }
-        key = block_max64(key, s_red64, solo);
-        v = (key >> 63) ? pick_victim(sc, posu, hh, low, s_ctlf[wq][0], moved_to, leaver_pos, s_red64, solo, tq) : (int)(uint32_t)key;
+        key = block_max64<kDecWaves>(key, s_red64, solo);
+        v = (key >> 63) ? pick_victim<kDecWaves>(sc, posu, hh, low, s_ctlf[wq][0], moved_to, leaver_pos, s_red64, solo, tq) : (int)(uint32_t)key;
       }
       if (ae) {
         // Apply it now.  Each score is rewritten by the thread that wrote it
