@@ -114,6 +114,16 @@ def test_stepping_whole_long_units_in_a_small_call(sqa, order):
     _run_case(sqa, ("h2o_bf16_mha_whole_long_units", "bf16", 8, 8, 128, 26, 640, 24, "h2o", [600], order), stride=19)
 
 
+@pytest.mark.parametrize("order", ["evict_then_attend", "attend_then_evict"])
+@pytest.mark.parametrize("dtype,D,g", [("bf16", 128, 1), ("bf16", 64, 2), ("f32", 64, 4), ("f32", 128, 1)])
+@pytest.mark.parametrize("B,budget", [(32, 127), (32, 523), (33, 127), (33, 523)])
+def test_stepping_one_work_item_per_cu_and_more(sqa, dtype, D, g, B, budget, order):
+    """256 units have workgroups of 8 waves, 264 of 4 waves: units of about one trip of the 8 waves and of several, with more
+    tokens than threads at 523; rows, scores and the carried decision against the oracle's."""
+    _run_case(sqa, ("waves_%s_D%d_g%d_%d_%d" % (dtype, D, g, 8 * B, budget), dtype, 8 * g, 8, D, B, budget + 20, 6, "h2o", [budget],
+                    order), stride=61, need_both_outcomes=False)
+
+
 def test_stepping_matrix_core_units_at_the_lds_limit(sqa):
     """8 query heads per KV head, 208 whole units per layer.  1050 slots: the largest units whose per-head
     probabilities of a step (33 tiles x 8 heads x 68 bytes) all fit in LDS next to the stage buffers; 1200 and
