@@ -136,8 +136,15 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
+# The current stream's handle without a torch.cuda.Stream object around it: 0.3 instead of 2.8 us, a fifth of what the
+# host spends on a small call (torch's own compiled code asks for it this way; a build of torch without it: the long way).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def batch_opts(prompt_len: Optional[torch.Tensor] = None, budget_seq: Optional[torch.Tensor] = None,
@@ -459,7 +466,7 @@ def decode_step(q: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor, new_p
                 opts: Optional[BatchOptsStruct] = None) -> torch.Tensor:
     """q [n_layers, B, Hq, D], k_new / v_new [n_layers, B, Hkv, D] -> out like q."""
     n_layers = caches.L - layer0 if n_layers is None else n_layers
-    B, Hq, D = q.shape[-3], q.shape[-2], q.shape[-1]
+    B, Hq, D = q.shape[-3:]
     Hkv = k_new.shape[-2]
     if opts is None:
         _check(_lib.sqa_decode_step(_ptr(q), _ptr(k_new), _ptr(v_new), _dt(q), B, Hq, Hkv, D, int(new_pos),
