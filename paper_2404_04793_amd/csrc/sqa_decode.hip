@@ -318,6 +318,11 @@ constexpr int kLogitPad = 33;                     // a unit's H2O scratch region
 constexpr int kStageRow = 256 + 16;               // LDS row pitch of a staged bf16 D=128 row (padded: no bank conflicts)
 constexpr int kStageBytesPerWave = 32 * kStageRow;   // one 32-token tile
 
+// Grouped queries of 4 or more heads per KV head in bf16 at D = 128 go to the matrix cores: with 8 heads
+// the vector-ALU path is arithmetic bound (4.2 TB/s against 6.5 TB/s on the Llama-2-70B shape), with 4
+// heads the matrix-core variant is still slightly ahead (779 against 797 us per step on the Mistral-7B shape).
+constexpr int kMfmaMinGroup = 4;      // query heads per KV head from which the matrix-core variant is used
+template <typename T, int D, int G> constexpr bool use_mfma() { return sizeof(T) == 2 && D == 128 && G >= kMfmaMinGroup; }
 // MF = true (bf16, D = 128, grouped queries): the chunk is streamed in 32-token
 // tiles through LDS and q.K^T / P.V run on the matrix cores, see section 1M.
 // PG = true: blocked allocation -- the unit's K and V rows lie in 16-row blocks of the layer's pools, named by
@@ -330,23 +335,19 @@ __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_
 // The same with more than 4 waves per workgroup (WIDE in the body), for calls that have no more work items than CUs.
 template <typename T, int D, int G, bool H2O, bool PG, int NW>
 __global__ __launch_bounds__(NW * SQA_WAVE) void decode_wide_kernel(const DecodeArgs a) {
-  constexpr bool MF = false;
+  constexpr bool MF = use_mfma<T, D, G>();
 #include "sqa_decode_unit.inc"
 }
 
 typedef void (*decode_fn)(const DecodeArgs);
 
-// Grouped queries of 4 or more heads per KV head in bf16 at D = 128 go to the matrix cores: with 8 heads
-// the vector-ALU path is arithmetic bound (4.2 TB/s against 6.5 TB/s on the Llama-2-70B shape), with 4
-// heads the matrix-core variant is still slightly ahead (779 against 797 us per step on the Mistral-7B shape).
-constexpr int kMfmaMinGroup = 4;      // query heads per KV head from which the matrix-core variant is used
-template <typename T, int D, int G> constexpr bool use_mfma() { return sizeof(T) == 2 && D == 128 && G >= kMfmaMinGroup; }
 constexpr int kWideWaves = 8;
 template <typename T, int D, bool H2O, bool PG> decode_fn pick_wide(int g) {
   switch (g) {
     case 1: return decode_wide_kernel<T, D, 1, H2O, PG, kWideWaves>;
     case 2: return decode_wide_kernel<T, D, 2, H2O, PG, kWideWaves>;
-    case 4: if constexpr (!use_mfma<T, D, 4>()) return decode_wide_kernel<T, D, 4, H2O, PG, kWideWaves>; break;
+    case 4: return decode_wide_kernel<T, D, 4, H2O, PG, kWideWaves>;
+    case 8: if constexpr (use_mfma<T, D, 8>()) return decode_wide_kernel<T, D, 8, H2O, PG, kWideWaves>; break;
   }
   return nullptr;
 }
@@ -430,7 +431,8 @@ constexpr int kLdsProbsMax = 18 * 1024;
 // against 71, but the number of waves would have to depend on the units' lengths, and with it the last bits of a layer's
 // results on which layers are called together).  8 query heads per KV head keep 4: 8 waves need 256 registers each and
 // start and merge for longer (D = 64, 17 slots 11.2 and 14.2 us; 143 15.7 and 14.8).  Beyond 256 work items 8 waves are
-// slower (320 units of 800 slots 26.9 -> 28.3).  The matrix-core kernel holds 12 waves per CU either way.
+// slower (320 units of 800 slots 26.9 -> 28.3).  The matrix-core kernel only shares a unit's tiles out among 8 waves: 256
+// units, 8 heads per KV head, H2O, 143 slots 11.4 -> 9.8, 1500 40.4 -> 36.6; 24 units of 1500 18.9 -> 14.5; sliding 12.4 -> 10.6.
 constexpr int64_t kWideMaxBlocks = 256;
 constexpr int kMaxUnsplit = 8192;
 // One wave per unit: for units of at most kWpuMaxSlots slots, in calls that have at least kWpuMinUnits
@@ -456,11 +458,11 @@ constexpr int kCoarseItem = 256;
 //   the same without either: none.  bf16, one head, sliding, 48 of 1067 and 208 of 706 14.5 us in 304, 16.1 in 816.
 struct CutRule { int min_item; int64_t beyond; bool wide; };
 static bool uses_mfma(sqa_dtype dt, int D, int g) { return dt == SQA_BF16 && D == 128 && g >= kMfmaMinGroup; }
-static bool wide_rule(sqa_dtype dt, int D, int g) { return g <= 4 && !uses_mfma(dt, D, g); }
+static bool wide_rule(sqa_dtype dt, int D, int g) { return g <= 4 || uses_mfma(dt, D, g); }
 static CutRule cut_rule(sqa_dtype dt, int D, int g, bool h2o) {
   const bool light = g <= (dt == SQA_F32 ? 4 : 2);         // up to 128 registers
   const bool mfma = uses_mfma(dt, D, g);
-  return {mfma ? kCoarseItem : 128, !light ? 800 : (h2o || dt == SQA_F32 ? 0 : INT32_MAX), wide_rule(dt, D, g)};
+  return {mfma ? kCoarseItem : 128, !light ? 800 : (h2o || dt == SQA_F32 ? 0 : INT32_MAX), wide_rule(dt, D, g) && !mfma};
 }
 // coarse: the fewest pieces (and the least scratch).
 // scratch_probs: the H2O step's per-token, per-head values live in the workspace for every unit, split or
@@ -688,13 +690,15 @@ static sqa_status plan_call(sqa_dtype dt, int B, int Hq, int Hkv, int D, bool h2
                                : plan_cut(layers, n_layers, B, Hq, Hkv, D, h2o, true, h2o && mfma, rule, plan);
   if (ps != SQA_OK) return ps;
   const size_t lds_shared = (size_t)g * plan->lds_chunk, lds_waves = (size_t)kDecWaves * g * plan->lds_chunk_w;
-  const size_t lds = (h2o ? (lds_shared > lds_waves ? lds_shared : lds_waves) * sizeof(float) : 0) +
-                     (mfma ? (size_t)kDecWaves * kStageBytesPerWave : 0) + (size_t)plan->lds_probs;
+  const size_t lds_h2o = (h2o ? (lds_shared > lds_waves ? lds_shared : lds_waves) * sizeof(float) : 0) + (size_t)plan->lds_probs;
   // (blocked allocation: the staged block numbers come last; decode_launch passes their offset)
-  const size_t lds_all = ((lds + 15) & ~(size_t)15) + (size_t)plan->tbl_entries * sizeof(int);
-  if (lds_all > 160 * 1024) return SQA_ERR_CAPACITY;
-  *lds_out = lds_all;
-  plan->waves = wide_rule(dt, D, g) && plan->blocks <= (uint64_t)kWideMaxBlocks ? kWideWaves : kDecWaves;
+  auto lds_of = [&](int waves) {
+    return ((lds_h2o + (mfma ? (size_t)waves * kStageBytesPerWave : 0) + 15) & ~(size_t)15) + (size_t)plan->tbl_entries * sizeof(int);
+  };
+  if (lds_of(kDecWaves) > 160 * 1024) return SQA_ERR_CAPACITY;
+  const bool wide = wide_rule(dt, D, g) && plan->blocks <= (uint64_t)kWideMaxBlocks && lds_of(kWideWaves) <= 160 * 1024;
+  plan->waves = wide ? kWideWaves : kDecWaves;
+  *lds_out = lds_of(plan->waves);
   return SQA_OK;
 }
 

@@ -115,7 +115,7 @@ def test_stepping_whole_long_units_in_a_small_call(sqa, order):
 
 
 @pytest.mark.parametrize("order", ["evict_then_attend", "attend_then_evict"])
-@pytest.mark.parametrize("dtype,D,g", [("bf16", 128, 1), ("bf16", 64, 2), ("f32", 64, 4), ("f32", 128, 1)])
+@pytest.mark.parametrize("dtype,D,g", [("bf16", 128, 1), ("bf16", 64, 2), ("f32", 64, 4), ("f32", 128, 1), ("bf16", 128, 8)])
 @pytest.mark.parametrize("B,budget", [(32, 127), (32, 523), (33, 127), (33, 523)])
 def test_stepping_one_work_item_per_cu_and_more(sqa, dtype, D, g, B, budget, order):
     """256 units have workgroups of 8 waves, 264 of 4 waves: units of about one trip of the 8 waves and of several, with more
