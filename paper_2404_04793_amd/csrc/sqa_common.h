@@ -67,6 +67,19 @@ template <typename T> __device__ __forceinline__ T wave_sum(T v) {
   return v;
 }
 
+// the largest of the 64 lanes' values, in every lane: DPP within rows of 16 lanes, then the rows
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  auto of = [&](int x) { const uint32_t y = (uint32_t)x; v = y > v ? y : v; };
+  of(__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true));      // quad_perm [1,0,3,2], [2,3,0,1]
+  of(__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true));
+  of(__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true));     // row_half_mirror, row_mirror
+  of(__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true));
+  const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 0), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
+  const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)v, 32), d = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+  const uint32_t x = a > b ? a : b, y = c > d ? c : d;
+  return x > y ? x : y;
+}
+
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // A kernel needs a one-time opt-in per device before a launch may ask for more dynamic LDS than the

@@ -4,8 +4,12 @@
 // the chip (every one of them makes the selection for itself):
 //   select  sliding / streaming: index arithmetic on the position;
 //           H2O: the floor(b/2) largest accumulated scores among the non-recent
-//           tokens by an LDS radix select (4 passes of 8 bits over the fp32 bit
-//           patterns, which order like the values because scores are >= 0);
+//           tokens by an LDS radix select over the fp32 bit patterns, which order
+//           like the values because scores are >= 0: 256 bins over the range that
+//           the keys have, then over the bin that holds the last one to be taken,
+//           until exactly the rest of a bin is taken (twice, as a rule; 8 bits at
+//           a time from the top it was four times, the first with most keys in a
+//           few bins, one atomic after the other);
 //           tokens equal to the threshold are taken in ascending position by an
 //           index-ordered prefix count -- never by arrival order;
 //   compact an order-preserving prefix sum turns keep flags into slot numbers;
@@ -31,6 +35,19 @@ __device__ __forceinline__ uint32_t score_key(float s) {
   return (b & 0x80000000u) ? 0u : b;     // scores are >= 0; -0.0 and negatives order as 0
 }
 
+template <int CTRL, int ROWS> __device__ __forceinline__ int dpp_add(int x) {   // x + the lane's DPP source (0 where there is none)
+  return x + __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false);
+}
+// inclusive prefix sum over the 64 lanes: within rows of 16 (row_shr 1, 2, 4, 8), then the rows' totals (row_bcast 15, 31)
+__device__ __forceinline__ int wave_incl_sum(int x) {
+  x = dpp_add<0x111, 0xF>(x);
+  x = dpp_add<0x112, 0xF>(x);
+  x = dpp_add<0x114, 0xF>(x);
+  x = dpp_add<0x118, 0xF>(x);
+  x = dpp_add<0x142, 0xA>(x);
+  return dpp_add<0x143, 0xC>(x);
+}
+
 // exclusive prefix count of `flag` over the 256 threads (position order), and the total
 __device__ __forceinline__ int block_excl_count(bool flag, int* s_wave_tot, int& total) {
   const int lane = threadIdx.x & (SQA_WAVE - 1), wave = threadIdx.x / SQA_WAVE;
@@ -49,12 +66,7 @@ __device__ __forceinline__ int block_excl_count(bool flag, int* s_wave_tot, int&
 // inclusive prefix sum of v over the 256 threads
 __device__ __forceinline__ int block_incl_sum(int v, int* s_wave_tot) {
   const int lane = threadIdx.x & (SQA_WAVE - 1), wave = threadIdx.x / SQA_WAVE;
-  int x = v;
-#pragma unroll
-  for (int o = 1; o < SQA_WAVE; o <<= 1) {
-    const int y = __shfl_up(x, o, SQA_WAVE);
-    x += lane >= o ? y : 0;
-  }
+  const int x = wave_incl_sum(v);
   __syncthreads();                        // previous users of s_wave_tot are done
   if (lane == SQA_WAVE - 1) s_wave_tot[wave] = x;
   __syncthreads();
@@ -99,7 +111,8 @@ __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
   extern __shared__ uint32_t s_mem[];
   __shared__ int s_hist[256];
   __shared__ int s_wave_tot[kCmpWaves];
-  __shared__ uint32_t s_sel[2];           // threshold key, how many equal keys to take
+  __shared__ uint32_t s_sel[3];           // the bin that holds the last key to be taken, how many of its keys are, how many it has
+  __shared__ uint32_t s_range[2][kCmpWaves];
 
   const int tid = threadIdx.x;
   const int bidx = u / batch.Hkv;
@@ -162,37 +175,60 @@ __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
   uint32_t* s_keys = s_mem + hh;                           // [M] when staged
   const bool keys_in_lds = hh > 0 && M <= kKeysInLdsMax && hh + M <= lds_words;
 
-  uint32_t thr = 0xffffffffu, take_eq = 0;
+  // (Bound by its barriers and the chain between them.  Four passes from the top bits with scans through LDS shuffles ->
+  // two over the range with DPP scans: one sequence of 32 heads joining, 2 layers, 494 tokens 11.0 -> 9.3 us; 8 layers of 32 units,
+  // 8000 tokens 95 -> 82; 7 layers of 384 units, 1355 tokens, D = 64 89 -> 79.5; 229376 units of 512 tokens 4.57 -> 4.44 ms.)
+  uint32_t thr = 0xffffffffu, take_eq = 0;                 // keys above thr are taken, and the first take_eq equal ones
   if (hh > 0) {
-    const uint32_t* keys;
-    if (keys_in_lds) {
-      for (int i = tid; i < M; i += kCmpThreads) s_keys[i] = score_key(sc[i]);
-      keys = s_keys;
-    } else {
-      keys = nullptr;
+    const int lane = tid & (SQA_WAVE - 1), wave = tid / SQA_WAVE;
+    uint32_t kmin = 0xffffffffu, kmax = 0;
+    constexpr int BATCH = MANY ? 4 : 8;
+    for (int i0 = tid; i0 < M; i0 += BATCH * kCmpThreads) {         // scores of a thread requested together
+      float v[BATCH];
+#pragma unroll
+      for (int x = 0; x < BATCH; ++x) v[x] = sc[min(i0 + x * kCmpThreads, M - 1)];
+#pragma unroll
+      for (int x = 0; x < BATCH; ++x) {
+        const uint32_t key = score_key(v[x]);
+        kmin = min(kmin, key); kmax = max(kmax, key);      // (beyond the end: the last one again)
+        if (keys_in_lds && i0 + x * kCmpThreads < M) s_keys[i0 + x * kCmpThreads] = key;
+      }
     }
-    uint32_t prefix = 0, mask = 0;
-    int k = hh;
-    for (int pass = 3; pass >= 0; --pass) {
-      s_hist[tid] = 0;
-      __syncthreads();
-      const int sh = pass * 8;
+    kmin = ~wave_max_u32(~kmin); kmax = wave_max_u32(kmax);
+    if (lane == 0) { s_range[0][wave] = kmin; s_range[1][wave] = kmax; }
+    s_hist[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kCmpWaves; ++w) { kmin = min(kmin, s_range[0][w]); kmax = max(kmax, s_range[1][w]); }
+    const int bits = 32 - __clz(kmax - kmin);              // (0 keys apart: 0)
+    int sh = bits > 8 ? bits - 8 : 0, k = hh;
+    uint32_t lo = kmin, bins = 256;                        // keys below lo, and from lo + (bins << sh) on, are decided
+    while (true) {
       for (int i = tid; i < M; i += kCmpThreads) {
-        const uint32_t key = keys ? keys[i] : score_key(sc[i]);
-        if ((key & mask) == prefix) atomicAdd(&s_hist[(key >> sh) & 255u], 1);
+        const uint32_t bin = ((keys_in_lds ? s_keys[i] : score_key(sc[i])) - lo) >> sh;      // (below lo: beyond 255, sh <= 16 then)
+        if (bin < bins) atomicAdd(&s_hist[bin], 1);
       }
       __syncthreads();
-      // the digit of the k-th largest key: thread t looks at bin 255 - t; the sum over the bins above and
-      // including its own reaches k in exactly one non-empty bin (at least k keys carry the prefix)
+      // thread t looks at bin 255 - t; the sum over the bins above and including its own reaches k in exactly one
+      // non-empty bin (at least k keys are in them)
       static_assert(kCmpThreads == 256, "one thread per histogram bin");
       const int h = s_hist[255 - tid];
-      const int incl = block_incl_sum(h, s_wave_tot);
-      if (incl >= k && incl - h < k) { s_sel[0] = (uint32_t)(255 - tid); s_sel[1] = (uint32_t)(k - (incl - h)); }
+      s_hist[255 - tid] = 0;
+      const int x = wave_incl_sum(h);
+      if (lane == SQA_WAVE - 1) s_wave_tot[wave] = x;
       __syncthreads();
-      prefix |= s_sel[0] << sh; mask |= 255u << sh; k = (int)s_sel[1];
+      int incl = x;
+#pragma unroll
+      for (int w = 0; w < kCmpWaves; ++w) incl += w < wave ? s_wave_tot[w] : 0;
+      if (incl >= k && incl - h < k) { s_sel[0] = (uint32_t)(255 - tid); s_sel[1] = (uint32_t)(k - (incl - h)); s_sel[2] = (uint32_t)h; }
       __syncthreads();
+      lo += s_sel[0] << sh;
+      k = (int)s_sel[1];
+      if (s_sel[2] == s_sel[1]) { thr = lo - 1; break; }   // the bin's keys are all taken (lo > 0: not every candidate is)
+      if (sh == 0) { thr = lo; take_eq = (uint32_t)k; break; }
+      bins = sh > 8 ? 256u : 1u << sh;
+      sh = sh > 8 ? sh - 8 : 0;
     }
-    thr = prefix; take_eq = (uint32_t)k;
   }
 
   // keep flags of the candidates -> their order among the chosen, in position order

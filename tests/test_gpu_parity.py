@@ -435,6 +435,42 @@ def test_prefill_compress_layers_matches_single_layer_calls(sqa):
         assert torch.equal(a.score[l], b.score[l]) and bool((a.hint[l] == -2).all())
 
 
+def _score_bits(kind, n, r):
+    """Non-negative fp32 scores given by their bit patterns, which the selection works on."""
+    one = 0x3f800000
+    if kind == "equal":
+        bits = np.full(n, one)
+    elif kind == "two":
+        bits = one + r.integers(0, 2, n)
+    elif kind.startswith("range"):                     # that many different patterns, next to each other
+        bits = one + r.integers(0, int(kind[5:]), n)
+    elif kind == "wide":                               # from 0 and the smallest denormal to +inf
+        bits = r.choice(np.array([0, 1, 2, 0x007fffff, 0x00800000, one, 0x7f7fffff, 0x7f800000]), n)
+    elif kind == "steps":                              # a few values many octaves apart, one of them crowded
+        bits = np.where(r.random(n) < 0.7, one, r.choice(np.array([one - (20 << 23), one + 1, one + (9 << 23)]), n))
+    else:
+        return r.exponential(size=n).astype(np.float32)
+    return bits.astype(np.uint32).view(np.float32)
+
+
+@pytest.mark.parametrize("P,b", [(300, 3), (300, 180), (1500, 700)])
+@pytest.mark.parametrize("kind", ["equal", "two", "range255", "range256", "range257", "range300", "range5000", "range70000", "wide", "steps",
+                                  "exponential"])
+def test_prefill_compress_selection_of_close_and_far_scores(sqa, kind, P, b):
+    """Bins over the range the keys have: ranges around the number of bins and its square, bins that are taken whole,
+    equal scores (the earlier position is kept).  Bit for bit."""
+    B, Hkv, D = 1, 3, 64
+    r = np.random.default_rng(P + b + len(kind))
+    K = torch.randn(B, Hkv, P, D, device=DEV).to(torch.bfloat16)
+    sc = np.stack([_score_bits(kind, P, r) for _ in range(Hkv)])[None]
+    caches = _mk_caches(sqa, [b], [b], B, Hkv, D, "bf16")
+    sqa.prefill_compress(K, K, torch.from_numpy(sc).to(DEV), "h2o", 4, caches, 0)
+    for h in range(Hkv):
+        keep = O.select_keep(np.arange(P), sc[0, h].astype(np.float64), b, "h2o")
+        assert caches.pos[0][0, h, :b].cpu().tolist() == keep.tolist()
+        assert torch.equal(caches.score[0][0, h, :b].cpu(), torch.from_numpy(sc[0, h][keep]))
+
+
 def test_prefill_compress_large_prompt_h2o_global_keys(sqa):
     """More candidates than the LDS staging limit: the select reads scores from memory."""
     B, Hkv, P, D, b = 1, 1, 20000, 64, 300
