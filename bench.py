@@ -43,7 +43,7 @@ MEASURED_TRAFFIC = {
 def decode_kernel_sha() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("sqa_decode.hip", "sqa_common.h"):
+    for f in ("sqa_decode.hip", "sqa_decode_unit.inc", "sqa_common.h"):
         with open(os.path.join(ROOT, "paper_2404_04793_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

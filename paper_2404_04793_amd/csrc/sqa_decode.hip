@@ -413,7 +413,7 @@ static bool fits_static(const DecodePlan& p) {
 // workspace), and a unit is cut into equal chunks only if it is more than a quarter longer than that.
 // One workgroup per CU already streams at 80 % of what the chip reaches, so what splitting buys is balance,
 // and the hand-over between a unit's workgroups costs more than a small imbalance: with 256 equal units (a
-// layer of the Llama-2-7B shape at batch 8 launched on its own) whole units take 56 us, halves 67 us; 320 units
+// layer of the Llama-2-7B shape at batch 8 launched on its own) whole units take 56 us (47.6 with 8 waves each), halves 67 us; 320 units
 // 67 us whole, 82 in halves; all layers at batch 2 81 us with the long units whole, 87 cut in three.
 // Where the longest units have to be cut anyway, the pieces are made for 2 or 3 items per CU if the items of one
 // per CU come out unevenly (the busiest of 256 CUs with over 9/8 of its share): 96 units of 2271 slots 41 us in 3
