@@ -476,8 +476,8 @@ __device__ __forceinline__ void score_colsum(const ScoreArgs& a, char* s_tiles /
 // A workgroup adds its stripes' column sums up in LDS and writes one partial row; sum_heads_kernel adds those.
 // What bounds it: vector and matrix instructions of two waves per SIMD (the registers allow no more), which on this
 // chip share their time rather than overlap (bf16, D = 128: 606 cycles per block of 16 keys and 64 rows with another
-// wave's beside it, 256 of them products, 292 exponentials and sums; products 33 %, vector instructions 59 % of the time
-// at 256 heads of 2048 tokens), hence the fewest possible of both.  In fp32 the products (2 x 1024 cycles per block at
+// wave's beside it, 256 of them products, 292 exponentials and sums; products 26 %, vector instructions 59 % of the time
+// at 256 heads of 2048 tokens, 8 waves), hence the fewest possible of both.  In fp32 the products (2 x 1024 cycles per block at
 // D = 128).  bf16 key blocks come through a ring in LDS, one ahead and across stripes (loaded into registers one ahead:
 // 381 us at 256 heads of 2048 tokens, 8 waves; 247 with no loads at all; 290 through the ring).  Two passes -> one, us:
 //   bf16, D = 128   256 heads of 2048 tokens  330 -> 290;  of 1024  115 -> 82;  of 512  43 -> 28;  64 of 1024  47 -> 26
