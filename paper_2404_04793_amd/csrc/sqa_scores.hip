@@ -6,9 +6,9 @@
 // reach HBM and every sum has a fixed order (no atomics).  Two ways:
 //   one pass (score_stripes): a workgroup keeps the exponentials of a stripe of query
 //           rows in registers until their sums are known; what most calls use;
-//   two passes, for prompts of more than 4096 tokens, very many short ones, long ones
-//           of many heads at D = 64 in bf16, and (the second alone) normalisers that
-//           the caller has:
+//   two passes, for prompts of more than 4096 tokens, where they are the cheaper way
+//           (many short prompts, bf16 at D = 64 with many heads: see StripeCut), and (the
+//           second alone) normalisers that the caller has:
 //   pass 1  row statistics of every query row: a reference m_i and the sum of
 //           exp2(s - m_i), stored as m_i and 1 / l_i;
 //   pass 2  per key, sum of exp2(s - m_i) / l_i over its KV head's query rows.
@@ -869,56 +869,139 @@ static sqa_status launch_stripes(ScoreArgs a, float* part, float* scores, hipStr
   SQA_HIP_CHECK(hipGetLastError());
   return SQA_OK;
 }
-// How a call in one pass is cut: waves per workgroup (4: two workgroups per CU; 8: one, which keeps twice the keys of a
-// stripe) and workgroups per query head.  The time is estimated as rounds of resident workgroups x the longest one's
-// stripes, each a fixed part and a part per key block of a wave, with the constants (us) that fit 420 measured calls
-// (16 to 1024 heads, 45 to 4096 tokens, both wave counts, 256 to 2048 workgroups) within 13 % rms.  Measured, us:
-//   bf16, D = 128   16 heads of 2048 tokens  4 waves 43, 8 waves 26.5;  64 of 777  21.3 and 22.4;  256 of 777  57 and 68;
-//                   256 of 2048  304 and 290
+// How a call goes: in one pass, with 4 waves per workgroup (two workgroups per CU) or 8 (one, which keeps twice the keys of a
+// stripe) and so many workgroups per query head, or in two passes.  Both ways are estimated (us), the cheaper one is taken.
+// All workgroups of a KV head run on one XCD, so what counts is the fullest XCD: (KV heads / 8, rounded up) x g x chunks
+// workgroups on 32 CUs.  (Counted over the whole chip, 44 heads of 3817 tokens, bf16, D = 128, got 11 workgroups each: 66 on an
+// XCD, three rounds, 275 us; 5 each take 214.)
+// The constants are fitted to 3700 shapes of one length, each measured in two passes and in up to 14 cuts (1 to 4096 heads,
+// 33 to 4096 tokens, 1 to 8 query heads per KV head): what is chosen takes 1.1 % longer than the fastest of a shape's ways on
+// average, over 10 % longer in one of 60.  Measured, us:
+//   bf16, D = 128   16 heads of 2048 tokens  4 waves 43, 8 waves 26.5;  64 of 777  21.3 and 22.4;  256 of 2048  304 and 290
 //   fp32, D = 128   16 of 2048  117 and 86;  256 of 512  98 and 112
-struct StripeCut { int waves, chunks; };
+//   two passes and one   bf16, D = 64: 640 heads of 96 tokens 12.2 and 14.7, 400 of 2154 (8 per KV head) 392 and 457;
+//                        D = 128: 736 of 71 15.4 and 18.2;  fp32, D = 64: 640 of 41 12.1 and 13.2
+struct StripeCut { int waves, chunks; double us; };
 constexpr int kStripeMaxP = 4096;
-static StripeCut stripe_cut(sqa_dtype dt, int D, int64_t heads, int g, int P, bool ragged, int64_t most_chunks) {
+constexpr int kXcds = 8, kXcdCus = 32;
+struct StripeFit {
+  double stripe, block, again;                   // of a workgroup of 4 waves: per stripe, per key block of a wave, and that much more per block that is not kept
+  double alone;                                  // 4 waves: as the only workgroup of a CU it takes this share of the time
+  double start;                                  // a workgroup's start: nothing is on its way yet
+  double whole, spread;                          // several rounds: how much of a last, partial round counts; of the longest workgroup beyond the average
+  double base;                                   // the launches
+  double far, l2;                                // keys read at a time, in units of an XCD's 4 MB of L2: beyond l2 each costs this much more
+  double stripe8, block8;                        // 8 waves: the first two times these
+};
+constexpr StripeFit kStripeFit[2][2] = {         // [bf16, fp32][D = 64, 128]
+    {{1.88, 0.498, 0.75, 0.842, 2.84, 0.669, 0.926, 2.679, 0.101, 0.529, 1.318, 0.983},
+     {2.221, 0.611, 0.959, 0.82, 3.3, 0.725, 0.481, 2.047, 0.142, 1.168, 1.202, 0.893}},
+    {{1.411, 1.042, 1.227, 0.688, 3.11, 0.607, 0.564, 2.554, 0.129, 0.518, 1.11, 1.039},
+     {1.897, 1.897, 1.193, 0.617, 3.141, 0.784, 0.637, 2.395, 0.057, 0.531, 0.786, 1.032}}};
+struct TwoPassFit {
+  double alone1, alone2;                         // per 64-row tile of the longest workgroup of each pass
+  double each1, each2;                           // per tile and workgroup of the fullest XCD's CUs
+  double start, wg, base;                        // per pass, per workgroup of a CU, the launches
+  double power;                                  // the two add up as powers (latency and throughput overlap)
+  double split;                                  // column sums per query head: the kernel that adds them
+  double whole;                                  // how much of a partly filled CU counts
+};
+constexpr TwoPassFit kTwoPassFit[2][2] = {
+    {{0.845, 0.435, 0.502, 0.178, 3.312, 0.466, 0, 1.23, 1.939, 0.467},
+     {0.739, 0.95, 0.104, 0.812, 3.327, 1.547, 0, 1.6, 2.813, 0.076}},
+    {{1.609, 0.786, 0.024, 2.302, 2.933, 0.628, 0, 1.767, 1.355, 0.65},
+     {3.048, 1.421, 1.854, 2.794, 0, 1.122, 3.515, 1.759, 3.068, 0.701}}};
+
+// Pass 2 per query head where the KV heads alone give the chip too few workgroups (8 per CU), unless the call is
+// so small that the additional launch is what one sees.  64 query heads over 8, one sequence, 1024 tokens, bf16,
+// D = 64: 129 -> 42 us for both passes; the same at 4096 tokens, D = 128: 650 -> 362; 32 over 8, 69 tokens: 14 -> 17.
+static bool split_heads(sqa_dtype dt, int B, int Hq, int Hkv, int P) {
+  const int own = dt == SQA_F32 ? kMT : 2 * kMT;
+  return Hq != Hkv && P > 128 && (int64_t)((P + own - 1) / own) * B * Hkv < 2048;
+}
+
+static StripeCut stripe_cut(sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, bool ragged, int64_t most_chunks) {
   const bool f32 = dt == SQA_F32;
-  const int own = f32 ? 32 : 64, slots = f32 ? (D == 64 ? 16 : 14) : 8;
-  const double stripe = f32 ? 1.6 : 2.5, block = f32 ? (D == 64 ? 1.05 : 1.9) : (D == 64 ? 0.46 : 0.63);
-  const double again = f32 && D == 64 ? 0.5 : 1.2;           // a key block that is not kept costs this much more
-  const double half_full = f32 ? 0.5 : 0.75;     // 4 waves, one workgroup per CU
+  const StripeFit& f = kStripeFit[f32][D == 128];
+  const int own = f32 ? 32 : 64, slots = f32 ? (D == 64 ? 16 : 14) : 8, g = Hq / Hkv;
   const int n_str = (P + own - 1) / own;
-  StripeCut best = {4, 1};
-  double best_us = 1e30;
-  for (int waves = 4; waves <= 8; waves += 4)
+  const int64_t xcd_heads = ((int64_t)B * Hkv + kXcds - 1) / kXcds * g;
+  StripeCut best = {4, 1, 1e30};
+  for (int waves = 4; waves <= 8; waves += 4) {
+    const int64_t resident = waves == 4 ? 2 * kXcdCus : kXcdCus;
+    const double stripe = waves == 4 ? f.stripe : f.stripe * f.stripe8, block = waves == 4 ? f.block : f.block * f.block8;
+    auto stripe_us = [&](int st) {
+      const int rows = (st + 1) * own < P ? (st + 1) * own : P, blocks = (rows + 16 * waves - 1) >> (waves == 4 ? 6 : 7);
+      return stripe + block * (blocks + (blocks > slots ? f.again * (blocks - slots) : 0.0));
+    };
+    double all = 0.0;
+    for (int st = 0; st < n_str; ++st) all += stripe_us(st);
+    int64_t before = 0;
     // (sequences of different length, which the host does not see: more and shorter workgroups even out long ones; 64 heads
     // of 2766 tokens and 64 of 1383, bf16, D = 128: 261 us in one round, 183 in three; 5 x 32 heads of 613 to 306 23 and 38)
-    for (int rounds = ragged ? (P > 2048 ? 3 : (P > 1024 ? 2 : 1)) : 1; rounds <= 4; ++rounds) {
-      const int64_t resident = waves == 4 ? 512 : 256;
-      int64_t n = resident * rounds / heads;
+    const int least = ragged ? (P > 2048 ? 6 : (P > 1024 ? 4 : 2)) : 1;      // in half rounds
+    for (const int halves : {1, 2, 3, 4, 6, 8, 12}) {
+      if (halves < least) continue;
+      int64_t n = resident * halves / (2 * xcd_heads);
       n = n < n_str ? n : n_str;
       n = n < most_chunks ? n : most_chunks;
       n = n < 1 ? 1 : n;
-      double us = 1.5;                            // a workgroup's start: nothing is on its way yet
-      for (int64_t k = 0, st; (st = n_str - 1 - (k * n + ((k & 1) ? n - 1 : 0))) >= 0; ++k) {
-        const int64_t rows = (st + 1) * own < P ? (st + 1) * own : P, blocks = ((rows + 15) / 16 + waves - 1) / waves;
-        us += stripe + block * (blocks + (blocks > slots ? again * (blocks - slots) : 0.0));
+      if (n == before) continue;
+      before = n;
+      // the longest workgroup: the first of a head, its last, or the last that has a stripe more than others
+      double longest = n == 1 ? f.start + all : 0.0;
+      const int m = (int)n, rem = n_str % m;
+      for (const int c : {0, m - 1, rem ? m - rem : 0}) {
+        if (m == 1) break;
+        double us = f.start;
+        for (int top = n_str - 1, odd = 0; top >= 0; top -= m, odd ^= 1) {
+          const int st = top - (odd ? m - 1 - c : c);
+          if (st >= 0) us += stripe_us(st);
+        }
+        longest = us > longest ? us : longest;
       }
-      us *= (double)((heads * n + resident - 1) / resident);
-      // Keys that the workgroups of one XCD read at a time, in units of its 4 MB of L2: beyond, they come from further
-      // away (256 heads of 2048 tokens, bf16, D = 128, 8 waves: 1 workgroup per head 380 us, 2 294; 1024 tokens 100 and 89).
-      const int64_t at_once = (heads * n < resident ? heads * n : resident) / 8;
-      const double l2 = (double)(at_once + n * g - 1) / (double)(n * g) * P * D * (f32 ? 4 : 2) / (4 << 20);
-      if (l2 > 1.0) us *= 1.0 + (f32 ? 0.02 : 0.08) * (l2 - 1.0);
-      if (waves == 4 && heads * n <= resident / 2) us *= half_full;
-      if (us < best_us) { best_us = us; best = {waves, (int)n}; }
+      const int64_t wgs = xcd_heads * n, at_once = wgs < resident ? wgs : resident;
+      double us = longest;
+      if (wgs > resident) {
+        const double average = f.start + all / (double)n;
+        const double rounds = f.whole * (double)((wgs + resident - 1) / resident) + (1.0 - f.whole) * (double)wgs / (double)resident;
+        const double queued = rounds * average + f.spread * (longest - average);
+        us = queued > us ? queued : us;
+      } else if (waves == 4 && 2 * wgs <= resident) {
+        us *= f.alone;
+      }
+      const double keys = (double)((at_once + n * g - 1) / (n * g)) * P * D * (f32 ? 4 : 2) / (4 << 20);
+      us = f.base + us * (1.0 + f.far * (keys > f.l2 ? keys - f.l2 : 0.0));
+      if (us < best.us) best = {waves, (int)n, us};
     }
+  }
   return best;
 }
-// Two passes are still the better way for very many short prompts, whose stripes cost more than their few key blocks
-// (1024 heads, bf16, D = 64, 45 tokens 11.2 us, 12.0 in one pass, 200 tokens 32.7 and 34.4; fp32, 45 tokens 15.2 and 17.6), and for long prompts of many
-// heads in bf16 at D = 64, where most keys are taken twice either way (120 heads of 3000 tokens 253 us and 279).
-static bool two_passes(sqa_dtype dt, int D, int64_t heads, int P) {
+static double two_passes_us(sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, bool split) {
+  const bool f32 = dt == SQA_F32;
+  const TwoPassFit& f = kTwoPassFit[f32][D == 128];
+  const int nb = f32 ? 1 : 2, own = kMT * nb, g = Hq / Hkv, tiles = (P + own - 1) / own, n64 = (P + kMT - 1) / kMT;
+  double rows = 0.0, cols = 0.0;                 // 64-row tiles of an average workgroup of each pass
+  for (int t = 0; t < tiles; ++t) {
+    rows += (((t + 1) * own < P ? (t + 1) * own : P) + kMT - 1) / kMT;
+    cols += n64 - t * nb;
+  }
+  const double xcd_kv = (double)(((int64_t)B * Hkv + kXcds - 1) / kXcds);
+  auto pass = [&](double longest, double average, double heads, double alone, double each) {
+    const double per_cu = heads * tiles / kXcdCus;
+    const double latency = f.start + alone * longest;
+    const double work = (f.wg + each * average) * (f.whole * ceil(per_cu) + (1.0 - f.whole) * per_cu);
+    return pow(pow(latency, f.power) + pow(work, f.power), 1.0 / f.power);
+  };
+  const int heads_each = split ? 1 : g;          // query heads that a workgroup of pass 2 adds up
+  return f.base + pass(n64, rows / tiles, xcd_kv * g, f.alone1, f.each1) +
+         pass((double)n64 * heads_each, cols / tiles * heads_each, xcd_kv * (g / heads_each), f.alone2, f.each2) + (split ? f.split : 0.0);
+}
+// Two passes have to be clearly ahead where the sequences' lengths differ: the estimates know the longest only.
+static bool two_passes(sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, bool ragged) {
   if (P > kStripeMaxP) return true;
-  if (heads >= 768 && P <= (dt == SQA_BF16 && D == 64 ? 256 : 64)) return true;
-  return dt == SQA_BF16 && D == 64 && P > 2560 && heads >= 96;
+  return two_passes_us(dt, D, B, Hq, Hkv, P, split_heads(dt, B, Hq, Hkv, P)) <
+         (ragged ? 0.93 : 1.0) * stripe_cut(dt, D, B, Hq, Hkv, P, ragged, INT32_MAX).us;
 }
 
 }  // namespace sqa
@@ -929,18 +1012,18 @@ static bool two_passes(sqa_dtype dt, int D, int64_t heads, int P) {
 extern "C" size_t sqa_prefill_scores_workspace_bytes(int B, int Hq, int Hkv, int P, int D) {
   (void)D;
   if (B < 1 || Hq < 1 || P < 1) return 0;
-  if (Hkv < 1 || Hkv > Hq) Hkv = Hq;
-  // (the element type is not known here: the most of what either needs)
-  const int64_t heads = (int64_t)B * Hq;
+  if (Hkv < 1 || Hq % Hkv != 0) Hkv = Hq;
+  // (neither the element type nor whether the sequences differ in length is known here: the most of what they need)
+  const int64_t rows = (int64_t)B * Hq * P;
   int floats = 3;
-  for (const sqa_dtype dt : {SQA_F32, SQA_BF16})
-    for (const int k : {0, 1, 2, 3}) {
-      const int d = k & 1 ? 64 : 128;
-      const bool ragged = k >= 2;
-      const int n = P <= sqa::kStripeMaxP ? sqa::stripe_cut(dt, d, heads, Hq / Hkv, P, ragged, INT32_MAX).chunks : 0;
-      floats = n > floats ? n : floats;
-    }
-  return (size_t)heads * P * floats * sizeof(float);
+  for (const int d : {64, 128})
+    for (const sqa_dtype dt : {SQA_F32, SQA_BF16})
+      for (const bool ragged : {false, true}) {
+        if (sqa::two_passes(dt, d, B, Hq, Hkv, P, ragged)) continue;
+        const int n = sqa::stripe_cut(dt, d, B, Hq, Hkv, P, ragged, INT32_MAX).chunks;
+        floats = n > floats ? n : floats;
+      }
+  return (size_t)rows * floats * sizeof(float);
 }
 
 extern "C" sqa_status sqa_prefill_scores(const void* Q, const void* K, sqa_dtype dt,
@@ -982,8 +1065,8 @@ static sqa_status prefill_scores_impl(const void* Q, const void* K, const float*
     else if (shares(ws, rows)) part = shares(ws + rows, rows) ? nullptr : ws + rows;
   }
   a.chunks = 0;
-  if (!lse && !two_passes(dt, D, (int64_t)B * Hq, P)) {
-    const StripeCut cut = stripe_cut(dt, D, (int64_t)B * Hq, Hq / Hkv, P, a.prompt_len != nullptr, (int64_t)(ws_bytes / (rows * sizeof(float))));
+  if (!lse && !two_passes(dt, D, B, Hq, Hkv, P, a.prompt_len != nullptr)) {
+    const StripeCut cut = stripe_cut(dt, D, B, Hq, Hkv, P, a.prompt_len != nullptr, (int64_t)(ws_bytes / (rows * sizeof(float))));
     a.chunks = cut.chunks;
     auto launch = [&](auto type, auto dim) {
       using T = decltype(type);
@@ -996,11 +1079,7 @@ static sqa_status prefill_scores_impl(const void* Q, const void* K, const float*
     if (dt == SQA_F32) return D == 64 ? launch(float{}, D64{}) : launch(float{}, D128{});
     return D == 64 ? launch(bf16_t{}, D64{}) : launch(bf16_t{}, D128{});
   }
-  // Pass 2 per query head where the KV heads alone give the chip too few workgroups (8 per CU), unless the call is
-  // so small that the additional launch is what one sees.  64 query heads over 8, one sequence, 1024 tokens, bf16,
-  // D = 64: 129 -> 42 us for both passes; the same at 4096 tokens, D = 128: 650 -> 362; 32 over 8, 69 tokens: 14 -> 17.
-  const int own = dt == SQA_F32 ? kMT : 2 * kMT;
-  if (Hq == Hkv || P <= 128 || (int64_t)((P + own - 1) / own) * B * Hkv >= 2048) part = nullptr;
+  if (!split_heads(dt, B, Hq, Hkv, P)) part = nullptr;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (copy_lse) copy_lse_kernel<<<(unsigned)(rows / 256 + 1 < 4096 ? rows / 256 + 1 : 4096), 256, 0, st>>>(row_lse, (int64_t)rows, ws);
   if (dt == SQA_F32) {

@@ -251,6 +251,39 @@ def test_prefill_scores_in_one_pass(sqa, dtype, D, B, Hkv, g, P, plen):
                 assert rel_err(got[b, h, :m], ref) < 1e-5
 
 
+def _scores_us(sqa, Q, K, floats, scores, lse=None):
+    """Least time of a prompt-score call with a workspace of that many floats per query row, of 5 series."""
+    B, Hq, P, D = Q.shape
+    ws = torch.empty(int(B * Hq * P * floats), device=DEV)
+    args = (B, Hq, K.shape[1], P, D, scores.data_ptr(), ws.data_ptr(), ws.numel() * 4, torch.cuda.current_stream().cuda_stream, None)
+    dt = 0 if Q.dtype == torch.float32 else 1
+    def series(n):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        for _ in range(n):
+            rc = (sqa._lib.sqa_prefill_scores_ex(Q.data_ptr(), K.data_ptr(), dt, *args) if lse is None else
+                  sqa._lib.sqa_prefill_scores_lse(Q.data_ptr(), K.data_ptr(), lse.data_ptr(), dt, *args))
+            assert rc == 0
+        t1.record()
+        torch.cuda.synchronize()
+        return t0.elapsed_time(t1) / n * 1e3
+    series(3)
+    return min(series(10) for _ in range(5))
+
+
+@pytest.mark.parametrize("B,H,P", [(11, 4, 3817), (23, 2, 3742)])
+def test_prefill_scores_more_workspace_is_not_slower(sqa, B, H, P):
+    """44 and 46 heads: all workgroups of a KV head run on one of the 8 XCDs, and some have 6 heads, others 5.  A cut that
+    counts the rounds over the whole chip puts one more workgroup on the full ones than they have places for (275 against
+    214 us), which a smaller workspace, with room for fewer workgroups, is spared."""
+    Q, K = (torch.randn(B, H, P, 128, device=DEV).to(torch.bfloat16) for _ in range(2))
+    scores = torch.empty(B, H, P, device=DEV)
+    room = sqa._lib.sqa_prefill_scores_workspace_bytes(B, H, H, P, 128) // (4 * B * H * P)
+    full = _scores_us(sqa, Q, K, room, scores)
+    for floats in (5, 8):
+        assert full < 1.12 * _scores_us(sqa, Q, K, min(floats, room), scores)
+
+
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 128)])
 @pytest.mark.parametrize("g,P", [(1, 200), (4, 200), (4, 100)])      # column sums per KV head, per query head, per KV head
 def test_given_normalisers_in_memory_the_call_writes(sqa, dtype, D, g, P):
