@@ -215,7 +215,10 @@ sqa_status sqa_allocate_budgets(const float* cos, int n_layers, int64_t total_bu
  * over prompt queries i >= j of softmax_j'<=i(Q_i.K_j'/sqrt(D))[j].
  *   Q : DEVICE [B][Hq][P][D], K : DEVICE [B][Hkv][P][D], dtype dt
  *   scores_out : DEVICE float [B][Hkv][P]
- *   workspace  : DEVICE, >= sqa_prefill_scores_workspace_bytes(...) */
+ *   workspace  : DEVICE, 8-byte aligned, at least two floats per query row (8 B Hq P bytes).  The call is fastest
+ *                with sqa_prefill_scores_workspace_bytes(...), up to one float per row and 32 tokens where the heads
+ *                are few (calls of up to 4096 tokens; otherwise 3 floats per row); with less it takes the fastest
+ *                way that the memory allows, and the last bits of the sums differ */
 size_t sqa_prefill_scores_workspace_bytes(int B, int Hq, int Hkv, int P, int D);
 sqa_status sqa_prefill_scores(const void* Q, const void* K, sqa_dtype dt,
                               int B, int Hq, int Hkv, int P, int D,

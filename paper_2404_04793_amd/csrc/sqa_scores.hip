@@ -997,32 +997,34 @@ static double two_passes_us(sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, 
   return f.base + pass(n64, rows / tiles, xcd_kv * g, f.alone1, f.each1) +
          pass((double)n64 * heads_each, cols / tiles * heads_each, xcd_kv * (g / heads_each), f.alone2, f.each2) + (split ? f.split : 0.0);
 }
-// Two passes have to be clearly ahead where the sequences' lengths differ: the estimates know the longest only.
-static bool two_passes(sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, bool ragged) {
+// The way of a call whose workspace holds `most_chunks` floats per query row.  Two passes have to be clearly ahead where
+// the sequences' lengths differ: the estimates know the longest only.
+static bool two_passes(sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, bool ragged, int64_t most_chunks, StripeCut* cut) {
   if (P > kStripeMaxP) return true;
-  return two_passes_us(dt, D, B, Hq, Hkv, P, split_heads(dt, B, Hq, Hkv, P)) <
-         (ragged ? 0.93 : 1.0) * stripe_cut(dt, D, B, Hq, Hkv, P, ragged, INT32_MAX).us;
+  *cut = stripe_cut(dt, D, B, Hq, Hkv, P, ragged, most_chunks);
+  return two_passes_us(dt, D, B, Hq, Hkv, P, most_chunks >= 3 && split_heads(dt, B, Hq, Hkv, P)) < (ragged ? 0.93 : 1.0) * cut->us;
 }
 
 }  // namespace sqa
 
 // In one pass: a partial row of column sums per workgroup of a query head.  In two, per query row: reference, 1/sum, and
 // (pass 2 split by query head) a partial column sum.  A workspace of two floats per row is enough too: fewer workgroups,
-// or no split.
+// or two passes where those are faster then (8 heads of 4096 tokens, bf16, D = 128, two floats per row: 544 us in one pass,
+// 114 in two; 48 with the whole workspace.  16 of 2048, fp32, D = 64: 353, 155 and 54).
 extern "C" size_t sqa_prefill_scores_workspace_bytes(int B, int Hq, int Hkv, int P, int D) {
-  (void)D;
   if (B < 1 || Hq < 1 || P < 1) return 0;
   if (Hkv < 1 || Hq % Hkv != 0) Hkv = Hq;
   // (neither the element type nor whether the sequences differ in length is known here: the most of what they need)
   const int64_t rows = (int64_t)B * Hq * P;
   int floats = 3;
-  for (const int d : {64, 128})
+  for (const int d : {64, 128}) {
+    if (D != d && (D == 64 || D == 128)) continue;
     for (const sqa_dtype dt : {SQA_F32, SQA_BF16})
       for (const bool ragged : {false, true}) {
-        if (sqa::two_passes(dt, d, B, Hq, Hkv, P, ragged)) continue;
-        const int n = sqa::stripe_cut(dt, d, B, Hq, Hkv, P, ragged, INT32_MAX).chunks;
-        floats = n > floats ? n : floats;
+        sqa::StripeCut cut;
+        if (!sqa::two_passes(dt, d, B, Hq, Hkv, P, ragged, INT32_MAX, &cut) && cut.chunks > floats) floats = cut.chunks;
       }
+  }
   return (size_t)rows * floats * sizeof(float);
 }
 
@@ -1065,8 +1067,8 @@ static sqa_status prefill_scores_impl(const void* Q, const void* K, const float*
     else if (shares(ws, rows)) part = shares(ws + rows, rows) ? nullptr : ws + rows;
   }
   a.chunks = 0;
-  if (!lse && !two_passes(dt, D, B, Hq, Hkv, P, a.prompt_len != nullptr)) {
-    const StripeCut cut = stripe_cut(dt, D, B, Hq, Hkv, P, a.prompt_len != nullptr, (int64_t)(ws_bytes / (rows * sizeof(float))));
+  StripeCut cut;
+  if (!lse && !two_passes(dt, D, B, Hq, Hkv, P, a.prompt_len != nullptr, (int64_t)(ws_bytes / (rows * sizeof(float))), &cut)) {
     a.chunks = cut.chunks;
     auto launch = [&](auto type, auto dim) {
       using T = decltype(type);

@@ -31,6 +31,18 @@ def test_struct_layout_matches_header():
     assert sqa.LayerCacheStruct.budget.offset == 60 and sqa.LayerCacheStruct.n_blocks.offset == 68
 
 
+def test_prefill_scores_workspace_follows_the_head_size():
+    """What a call of that head size is fastest with: at least 3 floats per query row, at most one per 32 rows, and not
+    what the other head size would need."""
+    need = lambda B, Hq, Hkv, P, D: sqa._lib.sqa_prefill_scores_workspace_bytes(B, Hq, Hkv, P, D) // (4 * B * Hq * P)
+    shapes = [(B, g * H, H, P) for B in (1, 2, 8) for g in (1, 8) for H in (2, 8) for P in (33, 500, 1500, 4096, 4097)]
+    per_row = [[need(*s, D) for D in (64, 128)] for s in shapes]
+    for (B, Hq, Hkv, P), n in zip(shapes, per_row):
+        assert all(3 <= x <= max(3, (P + 31) // 32) for x in n) and (P <= 4096 or n == [3, 3])
+        assert need(B, Hq, Hkv, P, 96) == max(n)          # (a head size that the calls refuse)
+    assert any(a != b for a, b in per_row)
+
+
 def test_batch_opts_layout_and_validation():
     assert C.sizeof(sqa.BatchOptsStruct) == 40 and sqa.BatchOptsStruct.order.offset == 32
     lib = sqa._lib

@@ -284,6 +284,19 @@ def test_prefill_scores_more_workspace_is_not_slower(sqa, B, H, P):
         assert full < 1.12 * _scores_us(sqa, Q, K, min(floats, room), scores)
 
 
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("H,P", [(16, 2048), (8, 4096)])
+def test_prefill_scores_with_a_small_workspace_takes_two_passes(sqa, dtype, D, H, P):
+    """Few heads and a workspace of 2 or 3 floats per query row: one pass would have 2 or 3 workgroups per head.  The
+    second pass alone (given normalisers) is about half of two passes; one pass in so few workgroups takes 3 to 9 times as long."""
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K = (torch.randn(1, H, P, D, device=DEV).to(dt) for _ in range(2))
+    scores = torch.empty(1, H, P, device=DEV)
+    half = _scores_us(sqa, Q, K, 3, scores, torch.full((1, H, P), 8.0, device=DEV))
+    for floats in (2, 3):
+        assert _scores_us(sqa, Q, K, floats, scores) < 2.6 * half
+
+
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("bf16", 128)])
 @pytest.mark.parametrize("g,P", [(1, 200), (4, 200), (4, 100)])      # column sums per KV head, per query head, per KV head
 def test_given_normalisers_in_memory_the_call_writes(sqa, dtype, D, g, P):
