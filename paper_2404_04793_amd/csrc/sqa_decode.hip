@@ -219,16 +219,38 @@ template <int NW> __device__ __forceinline__ int pick_victim(const float* sc, co
 // v_exp_f32: 2^x, 1 ulp, denormal results flush to 0 (harmless in a softmax)
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// sum over the LPR consecutive lanes that share a row; every lane gets the sum
-template <int LPR> __device__ __forceinline__ float group_sum(float v) {
+// sum over groups of N consecutive lanes, in every lane
+template <int N> __device__ __forceinline__ float group_sum(float v) {
   static_assert(sizeof(DecodeArgs) <= 4096, "kernel arguments are limited to 4 KiB");
-  static_assert(LPR == 8 || LPR == 16 || LPR == 32, "lanes per row");
+  static_assert(N == 8 || N == 16, "lanes");
   v += dpp_mov<0xB1>(v);            // quad_perm [1,0,3,2]
   v += dpp_mov<0x4E>(v);            // quad_perm [2,3,0,1]
   v += dpp_mov<0x141>(v);           // row_half_mirror
-  if (LPR >= 16) v += dpp_mov<0x140>(v);   // row_mirror
-  if constexpr (LPR >= 32) { float a, b; both<16>(v, a, b); v = a + b; }
+  if (N == 16) v += dpp_mov<0x140>(v);     // row_mirror
   return v;
+}
+// The same over 32 lanes (a row of fp32 at D = 128), for the G heads of a row at once.  This is in the streaming loop, and
+// with 4 heads and more vector instructions bound that loop: the last step is then a shuffle through LDS, requested for all
+// heads before the first is used (a lane swap is a vector instruction itself and overwrites both its operands: a copy and wait
+// states).  Sliding window, rows in blocks, us: 8 layers of 96 units under 8 heads, a swap for each head by itself 181, a shuffle
+// 160, shuffles together 155; 320 units under 4 heads 51.7, 51.0, 46.4.  With 1 or 2 heads there is hardly anything to overlap
+// a shuffle's latency with: 160 units under 2 heads, H2O, 2 % less with swaps.
+template <int G> __device__ __forceinline__ void group_sums32(float (&v)[G]) {
+#pragma unroll
+  for (int g = 0; g < G; ++g) v[g] = group_sum<16>(v[g]);
+  float o[G];
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    if constexpr (G >= 4) {
+      o[g] = __shfl_xor(v[g], 16, SQA_WAVE);
+    } else {
+      float a, b;
+      both<16>(v[g], a, b);
+      v[g] = a; o[g] = b;
+    }
+  }
+#pragma unroll
+  for (int g = 0; g < G; ++g) v[g] += o[g];
 }
 
 // maximum over groups of N = 8 or 16 consecutive lanes, in every lane

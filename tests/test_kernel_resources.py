@@ -3,8 +3,10 @@ lane decide how many waves a SIMD holds, and a source change that looks harmless
 of its waves (a struct selected between two address spaces once moved the decode kernel's layer
 descriptor from scalar into vector registers: 84 -> 118 VGPRs, 1.2 % slower on every workload) or make it
 spill.  The figures asserted here are the ones the measured numbers in the profiles were taken with."""
+import collections
 import json
 import os
+import subprocess
 
 import pytest
 
@@ -63,3 +65,33 @@ def test_one_pass_scores_keep_their_registers(res):
     assert len(stripes) == 8                           # 2 types x 2 head sizes x 4 or 8 waves
     for k, v in stripes.items():
         assert v["ScratchSize"] == 0 and v["VGPRs Spill"] == 0 and v["Occupancy"] >= 2, k
+
+
+LLVM = "/opt/rocm/llvm/bin/"
+
+
+def _instructions(tmp_path, kernel):
+    """The instructions of one decode kernel of this build, by name."""
+    obj = os.path.join(os.path.dirname(PATH), "sqa_decode.hip.o")
+    if not (os.path.exists(obj) and os.path.exists(LLVM + "llvm-objdump")):
+        pytest.skip("no objects of a build, or no LLVM tools to list them")
+    fat, code = str(tmp_path / "fat"), str(tmp_path / "code")
+    run = lambda *a: subprocess.run(a, check=True, capture_output=True, text=True).stdout
+    run(LLVM + "llvm-objcopy", "-O", "binary", "--only-section=.hip_fatbin", obj, fat)
+    run(LLVM + "clang-offload-bundler", "--unbundle", "--type=o", "--input=" + fat,
+        "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--output=" + code)
+    text = run(LLVM + "llvm-objdump", "-d", "--disassemble-symbols=" + kernel, code)
+    names = [l.split()[0] for l in text.splitlines() if l.startswith("\t")]
+    assert len(names) > 500, kernel
+    return collections.Counter(names)
+
+
+@pytest.mark.parametrize("g", [4, 8])
+@pytest.mark.parametrize("blocked", [0, 1])
+def test_streaming_loop_of_grouped_fp32_rows_has_no_lane_swaps(res, tmp_path, g, blocked):
+    """fp32 at D = 128: the sums over a row's 32 lanes, one per row and head, end in a shuffle through LDS; a lane swap is a
+    vector instruction, which bound this loop (8 heads, rows in blocks: 0.89 of the speed).  4 rows per trip."""
+    kernel = "_ZN3sqa18decode_unit_kernelIfLi128ELi%dELb0ELb0ELb%dEEEvNS_10DecodeArgsE" % (g, blocked)
+    assert kernel in res
+    n = _instructions(tmp_path, kernel)
+    assert not any(k.startswith("v_permlane16_swap") for k in n) and n["ds_bpermute_b32"] >= 4 * g
