@@ -377,12 +377,13 @@ sqa_status sqa_decode_step_static(const void* q, const void* k_new, const void* 
  *   info      : HOST, filled in
  *   per_layer : HOST [n_layers] or NULL                                                                  */
 typedef struct sqa_decode_plan_info {
-  int64_t workgroups;       /* grid of the one launch, 256 threads each                                   */
+  int64_t workgroups;       /* grid of the one launch, 64 x sqa_decode_plan_waves threads each            */
   int64_t workspace_bytes;  /* what the call uses of its workspace (<= sqa_decode_workspace_bytes)        */
   int32_t lds_bytes;        /* dynamic LDS per workgroup                                                  */
   int32_t matrix_cores;     /* 1: the MFMA variant runs (bf16, D = 128, 4 or 8 query heads per KV head)   */
-  int32_t wide_tail;        /* 1: so few workgroups that a long unit's score walk keeps all four waves
-                               (0: only that of units over 768 tokens does, up to 2048 workgroups)        */
+  int32_t wide_tail;        /* 1: so few workgroups (up to 512) that a long unit's score walk keeps all waves
+                               (0: only that of units over 768 tokens does, up to 2048 workgroups; with 8
+                               waves per workgroup off the matrix cores any unit's does)                   */
   int32_t table_entries;    /* blocked allocation: block numbers a workgroup stages in LDS (else 0)       */
 } sqa_decode_plan_info;
 typedef struct sqa_decode_layer_plan {
@@ -398,6 +399,10 @@ typedef struct sqa_decode_layer_plan {
 sqa_status sqa_decode_plan(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv, int D,
                            sqa_dtype dt, sqa_policy policy, sqa_decode_plan_info* info,
                            sqa_decode_layer_plan* per_layer);
+/* Waves of 64 threads per workgroup of that launch: 8 where it has at most 256 workgroups (one per CU; not for 8
+ * query heads per KV head off the matrix cores), else 4.  0 where sqa_decode_plan returns an error. */
+int32_t sqa_decode_plan_waves(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv, int D,
+                              sqa_dtype dt, sqa_policy policy);
 
 /* Zeroes the status word (a small fill kernel enqueued on stream; like
  * sqa_decode_workspace_init it uses no memset, so both may be recorded into a HIP graph). */

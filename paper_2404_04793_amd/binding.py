@@ -114,6 +114,8 @@ _lib.sqa_read_device_status.argtypes = [_vp, _vp, C.POINTER(C.c_int32)]
 _lib.sqa_kept_idx_sorted.restype = _i
 _lib.sqa_kept_idx_sorted.argtypes = [_LCp, _i, _i, _vp, _vp]
 _lib.sqa_decode_plan.argtypes = [_LCp, _i, _i, _i, _i, _i, _i, _i, C.POINTER(DecodePlanInfo), C.POINTER(DecodeLayerPlan)]
+_lib.sqa_decode_plan_waves.restype = C.c_int32
+_lib.sqa_decode_plan_waves.argtypes = [_LCp, _i, _i, _i, _i, _i, _i, _i]
 _lib.sqa_block_pool_create.argtypes = [C.c_int32]
 _lib.sqa_block_pool_create.restype = _vp
 _lib.sqa_block_pool_destroy.argtypes = [_vp]
@@ -246,8 +248,8 @@ def prefill_scores(Q: torch.Tensor, K: torch.Tensor, scores_out: Optional[torch.
 
 def decode_plan(budgets: Sequence[int], capacities: Sequence[int], B: int, Hq: int, Hkv: int, D: int,
                 dtype: str, policy: str, blocked: bool = False) -> dict:
-    """sqa_decode_plan: the launch a decode call over these layers would make (host arithmetic, no GPU).
-    dtype: "bf16" or "f32"."""
+    """sqa_decode_plan: the launch a decode call over these layers would make (host arithmetic, no GPU), "waves" (per
+    workgroup) from sqa_decode_plan_waves.  dtype: "bf16" or "f32"."""
     n = len(budgets)
     t = (LayerCacheStruct * n)()
     for i in range(n):
@@ -257,9 +259,10 @@ def decode_plan(budgets: Sequence[int], capacities: Sequence[int], B: int, Hq: i
             t[i].blocks_per_unit = (min(int(capacities[i]), int(budgets[i])) + SQA_BLOCK_SLOTS - 1) // SQA_BLOCK_SLOTS
             t[i].n_blocks = 1
     info, per = DecodePlanInfo(), (DecodeLayerPlan * n)()
-    _check(_lib.sqa_decode_plan(t, n, B, Hq, Hkv, D, {"f32": 0, "bf16": 1}[dtype], POLICY[policy], C.byref(info), per),
-           "sqa_decode_plan")
+    shape = (t, n, B, Hq, Hkv, D, {"f32": 0, "bf16": 1}[dtype], POLICY[policy])
+    _check(_lib.sqa_decode_plan(*shape, C.byref(info), per), "sqa_decode_plan")
     out = {f: int(getattr(info, f)) for f, _ in DecodePlanInfo._fields_}
+    out["waves"] = int(_lib.sqa_decode_plan_waves(*shape))
     out["layers"] = [{f: int(getattr(per[i], f)) for f, _ in DecodeLayerPlan._fields_} for i in range(n)]
     return out
 

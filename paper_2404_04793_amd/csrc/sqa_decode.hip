@@ -807,19 +807,35 @@ static sqa_status decode_launch(sqa_dtype dt, const DecodePlan& plan, size_t lds
 
 }  // namespace sqa
 
-extern "C" sqa_status sqa_decode_plan(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv, int D,
-                                      sqa_dtype dt, sqa_policy policy, sqa_decode_plan_info* info,
-                                      sqa_decode_layer_plan* per_layer) {
-  using namespace sqa;
-  if (!layers || !info) return SQA_ERR_NULL;
+namespace sqa {
+// The plan of a call from its shapes alone.
+static sqa_status plan_shapes(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv, int D, sqa_dtype dt,
+                              sqa_policy policy, DecodePlan* plan, size_t* lds) {
+  if (!layers) return SQA_ERR_NULL;
   if (dt != SQA_F32 && dt != SQA_BF16) return SQA_ERR_DTYPE;
   if (policy != SQA_SLIDING && policy != SQA_STREAMING && policy != SQA_H2O) return SQA_ERR_POLICY;
   if (B < 1 || Hq < 1 || Hkv < 1 || n_layers < 1 || n_layers > SQA_MAX_LAYERS || Hq % Hkv != 0) return SQA_ERR_SHAPE;
   const bool h2o = policy == SQA_H2O;
   if (!pick(dt, D, Hq / Hkv, h2o, layers[0].block_table != nullptr)) return SQA_ERR_SHAPE;
+  return plan_call(dt, B, Hq, Hkv, D, h2o, layers, n_layers, false, plan, lds);
+}
+}  // namespace sqa
+
+extern "C" int32_t sqa_decode_plan_waves(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv, int D,
+                                         sqa_dtype dt, sqa_policy policy) {
+  sqa::DecodePlan plan;
+  size_t lds = 0;
+  return sqa::plan_shapes(layers, n_layers, B, Hq, Hkv, D, dt, policy, &plan, &lds) == SQA_OK ? plan.waves : 0;
+}
+
+extern "C" sqa_status sqa_decode_plan(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv, int D,
+                                      sqa_dtype dt, sqa_policy policy, sqa_decode_plan_info* info,
+                                      sqa_decode_layer_plan* per_layer) {
+  using namespace sqa;
+  if (!info) return SQA_ERR_NULL;
   DecodePlan plan;
   size_t lds = 0;
-  const sqa_status ps = plan_call(dt, B, Hq, Hkv, D, h2o, layers, n_layers, false, &plan, &lds);
+  const sqa_status ps = plan_shapes(layers, n_layers, B, Hq, Hkv, D, dt, policy, &plan, &lds);
   if (ps != SQA_OK) return ps;
   info->workgroups = (int64_t)plan.blocks;
   info->workspace_bytes = (int64_t)plan.bytes;

@@ -110,6 +110,23 @@ def test_plan_invariants_on_random_shapes(seed):
     assert p["workspace_bytes"] <= sqa._lib.sqa_decode_workspace_bytes(t, L, B, g * Hkv, Hkv, D, sqa.POLICY[policy])
 
 
+@pytest.mark.parametrize("dtype,D,g,waves", [("f32", 64, 1, 8), ("f32", 128, 4, 8), ("f32", 128, 8, 4), ("bf16", 64, 2, 8), ("bf16", 64, 8, 4),
+                                             ("bf16", 128, 1, 8), ("bf16", 128, 4, 8), ("bf16", 128, 8, 8)])
+@pytest.mark.parametrize("policy,blocked", [("h2o", False), ("sliding", True)])
+def test_waves_per_workgroup(dtype, D, g, waves, policy, blocked):
+    """8 waves where a call has at most 256 workgroups, except under 8 heads off the matrix cores; the number follows from
+    the whole call, not from a layer."""
+    for B, H, layers, n, expect in ((32, 8, 1, 256, waves), (33, 8, 1, 264, 4), (1, 257, 1, 257, 4), (32, 8, 2, 512, 4), (16, 4, 4, 256, waves),
+                                    (1, 1, 1, 1, waves), (64, 64, 2, 2048, 4)):
+        p = sqa.decode_plan([143] * layers, [143] * layers, B, g * H, H, D, dtype, policy, blocked)
+        assert p["workgroups"] == n and p["waves"] == expect, (B, H, layers)
+        assert p["layers"][0]["wave_per_unit"] == int(n == 2048)          # (2 x 4096 units in workgroups of 4)
+    # few long units, cut into pieces
+    p = sqa.decode_plan([4000], [4000], 2, 8 * g, 8, D, dtype, policy, blocked)
+    assert p["layers"][0]["workgroups_per_unit"] > 1 and p["waves"] == (waves if p["workgroups"] <= 256 else 4)
+    assert sqa._lib.sqa_decode_plan_waves(None, 1, 1, 1, 1, 64, 0, 0) == 0
+
+
 @pytest.mark.parametrize("D,budgets,pieces", [(64, [4745, 4785, 4830], [5, 4, 5]), (128, [4300, 4557, 5200], [5, 3, 5])])
 def test_cut_does_not_depend_on_where_the_scratch_lies(D, budgets, pieces):
     """96 units, 8 query heads over 1: the finer cut where its scratch fits the static array of sqa_decode_step_static,
