@@ -8,9 +8,10 @@ This is the check of what a unit carries from step to step: under H2O the kernel
 eviction at the end of a step and stores it in the unit record (evict_hint); a teacher-forced test
 overwrites that record, this one does not.  The decision is also compared directly: the token the record
 says will go next must be the token the oracle's selection drops when the next token is appended.
-Covered: the vector-ALU kernel with 4 waves per unit (whole and split units) and one wave per unit, the
-matrix-core kernel (4 and 8 query heads per KV head; whole, split, one wave per unit), both orders of a
-step, fp32 and bf16."""
+Covered: workgroups of 8 waves (calls of at most 256 work items: most cases here; whole and split units), one
+wave per unit, the matrix-core kernel (4 and 8 query heads per KV head; whole, split, one wave per unit), both
+orders of a step, fp32 and bf16.  Calls of more work items, whose workgroups have 4 waves: a few here, the rest in
+test_gpu_four_waves.py."""
 import os
 
 import numpy as np
@@ -88,7 +89,7 @@ def _rows_by_position(Kp, Vp, k_all, v_all, l, b, h):
 
 STEPPING = [
     # name, dtype, Hq, Hkv, D, B, P, S, policy, budgets, order
-    # budgets: 300 = a whole unit shared by 4 waves, 700 = split into 3 chunks over 3 workgroups, 37 = shorter than one pass
+    # budgets: 300 = a whole unit shared by a workgroup's waves, 700 = split over several workgroups, 37 = shorter than one pass
     ("h2o_bf16_mha", "bf16", 2, 2, 128, 2, 750, 48, "h2o", [300, 700, 37], "evict_then_attend"),
     ("h2o_bf16_gqa4_matrix", "bf16", 8, 2, 128, 2, 750, 48, "h2o", [300, 700, 37], "evict_then_attend"),
     ("h2o_bf16_gqa8_matrix", "bf16", 16, 2, 128, 2, 750, 48, "h2o", [300, 700, 37], "evict_then_attend"),
@@ -109,8 +110,8 @@ def test_stepping_from_the_gpus_own_state(sqa, case):
 @pytest.mark.parametrize("order", ["evict_then_attend", "attend_then_evict"])
 def test_stepping_whole_long_units_in_a_small_call(sqa, order):
     """208 units of 600 slots in one call: few enough workgroups that units stay whole although they are
-    long, and that all four waves of a workgroup stay for the unit's tail (score update, eviction
-    decision) instead of leaving it to the first wave."""
+    long; all 8 waves of a workgroup work on the unit's tail (score update, eviction decision)."""
+    assert sqa.decode_plan([600], [600], 26, 8, 8, 128, "bf16", "h2o")["waves"] == 8
     _run_case(sqa, ("h2o_bf16_mha_whole_long_units", "bf16", 8, 8, 128, 26, 640, 24, "h2o", [600], order), stride=19)
 
 
