@@ -312,8 +312,12 @@ sqa_status sqa_prefill_compress_layers_ex(const void* const* K, const void* cons
  * arrival counter per unit; with 4 or more query heads per KV head (bf16,
  * D = 128) it also holds, for every unit, the step's per-head probabilities
  * that the H2O accumulation sums.  The merge order is fixed: results are
- * identical from run to run.  How units are cut follows from the shapes alone
- * (sqa_decode_plan).  A workspace of less than sqa_decode_workspace_bytes is
+ * identical from run to run.  How units are cut and how many waves share one
+ * follows from the shapes of the whole call alone (sqa_decode_plan and
+ * sqa_decode_plan_waves).  A layer's results are the same bit for bit alone and in a call
+ * over several layers where those give it the same pieces per unit, slots per piece
+ * and waves (or a wave per unit); otherwise they agree to rounding, and under H2O
+ * scores that lie within it of each other may evict another token.  A workspace of less than sqa_decode_workspace_bytes is
  * accepted where it holds what a cut into fewer pieces needs -- the results may
  * then differ from those with a full one in their last bits --, and refused with
  * SQA_ERR_CAPACITY where it does not.

@@ -449,9 +449,10 @@ constexpr int kLdsProbsMax = 18 * 1024;
 // Calls of no more work items than CUs have a CU to each: 4 waves leave it short of requests in flight, and walk a unit's
 // scores one wave after the streaming.  8 waves per workgroup (device time of one layer, us, before and after; H2O, bf16,
 // D = 128, 256 units): 17 slots 6.3 -> 5.9, 143 9.2 -> 7.3, 300 13.2 -> 9.4, 2271 55.4 -> 47.6; fp32, D = 128, 4 query
-// heads per KV head, 300 slots 34 -> 21.  16 waves: 143 slots the same, 17 7.0, 2271 48.5 (128 units of 5000 slots 64
-// against 71, but the number of waves would have to depend on the units' lengths, and with it the last bits of a layer's
-// results on which layers are called together).  8 query heads per KV head keep 4: 8 waves need 256 registers each and
+// heads per KV head, 300 slots 34 -> 21.  16 waves: 143 slots the same, 17 7.0, 2271 48.5; 64 against 71 for 128 units of 5000
+// slots, 20 % worse below 128 slots: another set of kernels for few and long units, not taken.  (The number of waves follows
+// from the whole call: a layer of up to 256 items has 8 alone and 4 together with others, and its results differ in their
+// last bits between the two.)  8 query heads per KV head keep 4: 8 waves need 256 registers each and
 // start and merge for longer (D = 64, 17 slots 11.2 and 14.2 us; 143 15.7 and 14.8).  Beyond 256 work items 8 waves are
 // slower (320 units of 800 slots 26.9 -> 28.3).  The matrix-core kernel only shares a unit's tiles out among 8 waves: 256
 // units, 8 heads per KV head, H2O, 143 slots 11.4 -> 9.8, 1500 40.4 -> 36.6; 24 units of 1500 18.9 -> 14.5; sliding 12.4 -> 10.6.

@@ -238,3 +238,43 @@ def test_replays_of_a_recorded_step(sqa, dtype, D, g, B, b):
         runs.append(snaps)
     for a, c in zip(*runs):
         assert all(torch.equal(x, y) for x, y in zip(a, c))
+
+
+@pytest.mark.parametrize("dtype,D,g", [("f32", 64, 1), ("bf16", 128, 1), ("f32", 128, 4), ("bf16", 128, 8)])
+def test_one_call_over_layers_and_one_per_layer_agree_to_rounding(sqa, dtype, D, g):
+    """132 units per layer: 8 waves each in a call over one layer, 4 in a call over both.  Whole units either way, so only the
+    order in which the waves' parts are added differs; the tokens kept are the same (scores that are far apart), and a call
+    made twice gives the same bytes."""
+    B, Hkv, L, P, S, budgets = 33, 4, 2, 250, 5, [200, 143]
+    dt = _dtype(dtype)
+    _plan(sqa, budgets, B, g, Hkv, D, dtype, "h2o")
+    assert all(sqa.decode_plan([b], [b], B, g * Hkv, Hkv, D, dtype, "h2o")["waves"] == 8 for b in budgets)
+    gen = torch.Generator(device=DEV).manual_seed(D + g)
+    mk = lambda *shape: torch.randn(*shape, generator=gen, device=DEV).to(dt)
+    K, V = [mk(B, Hkv, P, D) for _ in range(L)], [mk(B, Hkv, P, D) for _ in range(L)]
+    sc = [torch.argsort(torch.rand(B, Hkv, P, generator=gen, device=DEV), dim=-1).float() for _ in range(L)]
+    q, k, v = mk(S, L, B, Hkv * g, D), mk(S, L, B, Hkv, D), mk(S, L, B, Hkv, D)
+    runs = []
+    for together in (True, True, False):
+        caches = sqa.LayerCaches(budgets, budgets, B, Hkv, D, dt, DEV, True)
+        sqa.prefill_compress_layers(K, V, sc, "h2o", 4, caches)
+        ws = sqa.decode_workspace(caches, Hkv * g, "h2o")
+        wl = [sqa.decode_workspace(caches, Hkv * g, "h2o", l, 1) for l in range(L)]
+        out = torch.empty_like(q)
+        for t in range(S):
+            if together:
+                sqa.decode_step(q[t], k[t], v[t], P + t, "h2o", 4, caches, out[t], ws)
+            else:
+                for l in range(L):
+                    sqa.decode_step(q[t, l], k[t, l], v[t, l], P + t, "h2o", 4, caches, out[t, l], wl[l], layer0=l, n_layers=1)
+        runs.append((out, caches))
+    (a, ca), (b, cb), (c, cc) = runs
+    assert torch.equal(a, b) and all(torch.equal(x, y) for x, y in zip(ca.score + ca.pos + ca.state, cb.score + cb.pos + cb.state))
+    assert rel_err(np64(a), np64(c)) < TOL[dtype]
+    for l in range(L):
+        assert torch.equal(ca.pos[l], cc.pos[l])
+        # each step adds probabilities that are off by a few 1e-6 of themselves in either run (on the matrix cores by the
+        # rounding of a bf16 number, 2^-8, relative to one reference or another), and rounds the sum
+        rel = 2 * ((2.0 ** -8 if uses_matrix_cores(dtype, D, g) else 1e-5) + S * 2.0 ** -23)
+        x, y = np64(ca.score[l]), np64(cc.score[l])
+        assert np.all(np.abs(x - y) <= rel * np.abs(x) + 1e-37)

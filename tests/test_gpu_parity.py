@@ -1137,8 +1137,8 @@ def test_long_whole_units_in_a_call_of_some_hundred_workgroups(sqa, dtype, D, g,
 
 
 def test_decode_is_deterministic_and_per_layer_calls_agree(sqa):
-    """Same inputs twice -> identical bytes; one call over all layers == one call per layer
-    (with and without the device copy of the layer table)."""
+    """Same inputs twice -> identical bytes; one call over all layers == one call per layer (with and without the
+    device copy of the layer table), where both give a layer the same cut and waves, as in calls as small as these."""
     wl = W.scaled(W.WORKLOADS["tiny"], L=3, Hq=4, Hkv=2, D=128, B=2, P=320, S=5, dtype="bf16")
     budgets = [30, 323, 17]
     u_dirs, mask = W.unit_dirs(wl), W.hh_mask(wl, DEV)
