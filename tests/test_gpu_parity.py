@@ -180,8 +180,8 @@ def test_prefill_scores_random_shapes(sqa, case):
 @pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
 @pytest.mark.parametrize("P", [129, 191, 193, 320])
 def test_prefill_scores_by_query_head_and_by_kv_head(sqa, dtype, D, P):
-    """The column sums of a small call are taken per query head and added up afterwards; with a workspace of two
-    floats per query row (no room for those) per KV head.  Both against the oracle, around the edges of the 64-row
+    """A partial row of column sums per query head and workgroup, added up afterwards; with a workspace of two floats
+    per query row fewer of them, or two passes.  Both against the oracle, around the edges of the 64-row stripes and
     tiles, with one key whose logits are -inf (it counts nothing)."""
     g, Hkv, B = 4, 2, 2
     wl = W.scaled(W.WORKLOADS["tiny"], L=1, Hq=Hkv * g, Hkv=Hkv, D=D, B=B, P=P, dtype=dtype)
@@ -249,6 +249,45 @@ def test_prefill_scores_in_one_pass(sqa, dtype, D, B, Hkv, g, P, plen):
             if m:
                 ref = O.prefill_scores(np64(Q[b, h * g:(h + 1) * g, :m]), np64(K[b, h, :m]))
                 assert rel_err(got[b, h, :m], ref) < 1e-5
+
+
+def _scores_with_workspace(sqa, Q, K, floats, opts=None):
+    """prefill_scores with a workspace of that many floats per query row (full of NaN before) -> scores, workspace."""
+    B, Hq, P, D = Q.shape
+    out = torch.full((B, K.shape[1], P), float("nan"), device=DEV)
+    ws = torch.full((floats, B, Hq, P), float("nan"), device=DEV)
+    rc = sqa._lib.sqa_prefill_scores_ex(Q.data_ptr(), K.data_ptr(), 0 if Q.dtype == torch.float32 else 1, B, Hq, K.shape[1], P, D,
+                                        out.data_ptr(), ws.data_ptr(), ws.numel() * 4, torch.cuda.current_stream().cuda_stream, sqa._opts(opts))
+    assert rc == 0
+    return np64(out), ws
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("B,Hkv,g,P,plen,floats", [
+    (1, 1, 3, 4100, None, 3), (1, 1, 3, 4100, None, 2),     # beyond one pass; second pass per query head, and per KV head
+    (1, 2, 1, 4161, None, 3),
+    (2, 2, 2, 1930, [1930, 333], 2),                        # few heads, room for two workgroups each: two passes are faster
+    (20, 32, 1, 45, [45 - b % 7 for b in range(20)], 3)])   # many short prompts, the larger types in one pass
+def test_prefill_scores_in_two_passes(sqa, dtype, D, B, Hkv, g, P, plen, floats):
+    """Row statistics, then column sums of exp2(s - m_i) / l_i: around the 64-row tiles, sequences of other lengths, a key whose
+    logits are -inf.  That a call went this way shows in its workspace, which then holds the rows' normalisers."""
+    gen = torch.Generator(device="cpu").manual_seed(P + B)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    Q, K = (torch.randn(B, h, P, D, generator=gen).to(dt).to(DEV) for h in (Hkv * g, Hkv))
+    K[:, :, 5, 0], Q[..., 0] = -float("inf"), Q[..., 0].abs() + 0.5
+    lens = torch.tensor([P] * B if plen is None else plen, dtype=torch.int32, device=DEV)
+    got, ws = _scores_with_workspace(sqa, Q, K, floats, None if plen is None else sqa.batch_opts(prompt_len=lens))
+    for b, h in sorted({(0, 0), (B // 2, Hkv // 2), (B - 1, Hkv - 1)}):
+        m = P if plen is None else plen[b]
+        q, k = np64(Q[b, h * g:(h + 1) * g, :m]), np64(K[b, h, :m])
+        k[5, 0] = -1e6                                      # (the oracle's logits stay finite; exp gives 0 all the same)
+        if (B, P) != (20, 45) or (dtype, D) in (("bf16", 64), ("f32", 64)):
+            stat = np64(ws[0, b, h * g:(h + 1) * g, :m])
+            if (dtype, D) != ("bf16", 128):
+                stat -= np.log2(np64(ws[1, b, h * g:(h + 1) * g, :m]))
+            assert np.abs(stat - O.prefill_row_lse(q, k) / np.log(2.0)).max() < 1e-4
+        ref = O.prefill_scores(q, k)
+        assert np.all(got[b, h, m:] == 0.0) and got[b, h, 5] == 0.0 and rel_err(got[b, h, :m], ref) < 1e-5
 
 
 def _scores_us(sqa, Q, K, floats, scores, lse=None):
@@ -366,6 +405,20 @@ def test_prefill_scores_wide_logit_range(sqa, case):
         ref = O.prefill_scores(Qn[0, h * g:(h + 1) * g], Kn[0, h])
         assert rel_err(got[0, h], ref) < TOL["bf16"]
         assert abs(got[0, h].sum() - g * P) < 1e-3 * g * P
+
+
+@pytest.mark.parametrize("dtype,D", [("f32", 64), ("f32", 128), ("bf16", 64), ("bf16", 128)])
+@pytest.mark.parametrize("case", ["steps_up", "late_peak", "steps_down"])
+def test_prefill_scores_wide_logit_range_in_two_passes(sqa, case, dtype, D):
+    """The same beyond 4096 tokens.  Logits reach 5000 in the exp2 domain, where fp32 holds them to 5e-4: so far may an
+    exponential be off."""
+    P = 4110
+    Q, K = (x.to(torch.float32 if dtype == "f32" else torch.bfloat16).to(DEV) for x in _wide_range_qk(case, P, 2, 1, D))
+    got, ws = _scores_with_workspace(sqa, Q, K, 3)
+    Qn, Kn = np64(Q)[0], np64(K)[0, 0]
+    assert np.all(np.isfinite(got)) and rel_err(got[0, 0], O.prefill_scores(Qn, Kn)) < 2e-3
+    stat = np64(ws[0, 0]) - (0.0 if (dtype, D) == ("bf16", 128) else np.log2(np64(ws[1, 0])))
+    assert np.abs(stat - O.prefill_row_lse(Qn, Kn) / np.log(2.0)).max() < 2e-3
 
 
 # ---------------------------------------------------------------- prefill compress
