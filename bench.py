@@ -367,7 +367,7 @@ def main():
                     help="time only the H2O prompt-score producer (sqa_prefill_scores; set-up work of the pass, "
                          "matrix-core bound): a step = the scores of all layers of one prompt batch")
     ap.add_argument("--lse", action="store_true",
-                    help="with --scores-only: the row normalisers are given (sqa_prefill_scores_lse), one pass instead of two")
+                    help="with --scores-only: the row normalisers are given (sqa_prefill_scores_lse), column sums only")
     ap.add_argument("--progress", action="store_true", help="say on stderr when each phase of the run begins")
     ap.add_argument("--no-others", action="store_true",
                     help="skip the short decode-only legs on the other workloads (they run by default with the "

@@ -232,7 +232,8 @@ sqa_status sqa_prefill_scores_ex(const void* Q, const void* K, sqa_dtype dt,
 
 /* The same scores when the softmax normalisers of the prompt's attention are already known: a fused
  * attention kernel that runs the prompt returns, per query row, the logarithm of its normaliser, and with it
- * the column sums need one pass over the logits instead of two (half the work of sqa_prefill_scores).
+ * the column sums need no row sums first.  8 x 32 heads of 2048 tokens, bf16, D = 128: 176 us instead of 303; few heads and
+ * fp32 gain nothing (16 heads of 2048 31 and 26; fp32, 256 heads of 512 122 and 100): leave the normalisers out there.
  *   row_lse : DEVICE float [B][Hq][P], row_lse[b][h][i] = ln sum_{j<=i} exp(Q_i.K_j / sqrt(D))
  *             (natural logarithm, logits already scaled by 1/sqrt(D), causal); those of padding count
  *             nothing.  May lie in the memory of scores_out, or of the workspace (not of both)

@@ -228,7 +228,7 @@ def prefill_scores(Q: torch.Tensor, K: torch.Tensor, scores_out: Optional[torch.
                    opts: Optional[BatchOptsStruct] = None, row_lse: Optional[torch.Tensor] = None) -> torch.Tensor:
     """Q [B, Hq, P, D], K [B, Hkv, P, D] -> scores [B, Hkv, P] fp32.  row_lse [B, Hq, P] fp32 (optional): the
     natural-log softmax normalisers of the prompt's causal attention, if the caller has them
-    (sqa_prefill_scores_lse: one pass instead of two)."""
+    (sqa_prefill_scores_lse: column sums alone; worth it in bf16 with many heads)."""
     B, Hq, P, D = Q.shape
     Hkv = K.shape[1]
     if scores_out is None:

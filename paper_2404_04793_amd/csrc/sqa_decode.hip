@@ -253,22 +253,17 @@ template <int G> __device__ __forceinline__ void group_sums32(float (&v)[G]) {
   for (int g = 0; g < G; ++g) v[g] += o[g];
 }
 
-// maximum over groups of N = 8 or 16 consecutive lanes, in every lane
-template <int N> __device__ __forceinline__ float group_max(float v) {
-  static_assert(N == 8 || N == 16, "lanes");
+// maximum over groups of 8 consecutive lanes, in every lane
+__device__ __forceinline__ float group_max(float v) {
   v = fmaxf(v, dpp_mov<0xB1>(v));
   v = fmaxf(v, dpp_mov<0x4E>(v));
-  v = fmaxf(v, dpp_mov<0x141>(v));
-  if constexpr (N == 16) v = fmaxf(v, dpp_mov<0x140>(v));
-  return v;
+  return fmaxf(v, dpp_mov<0x141>(v));
 }
-template <int N> __device__ __forceinline__ uint32_t group_max_u(uint32_t v) {
+__device__ __forceinline__ uint32_t group_max_u(uint32_t v) {
   auto step = [](uint32_t x, float y) { const uint32_t o = __float_as_uint(y); return o > x ? o : x; };
   v = step(v, dpp_mov<0xB1>(__uint_as_float(v)));
   v = step(v, dpp_mov<0x4E>(__uint_as_float(v)));
-  v = step(v, dpp_mov<0x141>(__uint_as_float(v)));
-  if constexpr (N == 16) v = step(v, dpp_mov<0x140>(__uint_as_float(v)));
-  return v;
+  return step(v, dpp_mov<0x141>(__uint_as_float(v)));
 }
 
 template <typename T> struct RowMath;

@@ -3,7 +3,7 @@
 // share a KV head.  This is the producer of sqa_prefill_compress's attn_scores.
 //
 // The causal logits are computed on the matrix cores; the P x P probabilities never
-// reach HBM and every sum has a fixed order (no atomics).  Two ways:
+// reach HBM and every sum has a fixed order (LDS atomics have one writer per key and stripe).  Two ways:
 //   one pass (score_stripes): a workgroup keeps the exponentials of a stripe of query
 //           rows in registers until their sums are known; what most calls use;
 //   two passes, for prompts of more than 4096 tokens, where they are the cheaper way
@@ -791,7 +791,7 @@ __global__ __launch_bounds__(kScThreads) void score_colsum_kernel(const ScoreArg
   extern __shared__ char s_tiles[];
   score_colsum<T, D, NB, LSE, SPLIT>(a, s_tiles);
 }
-// scores[bk][j] = the sum over the g query heads of a KV head, in head order
+// scores[bk][j] = the sum of the g partial rows of a KV head (one per query head, or per workgroup of one), in order
 __global__ __launch_bounds__(256) void sum_heads_kernel(const float* __restrict__ part, int g, int P, int64_t n /*B*Hkv*P*/,
                                                         float* __restrict__ scores) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
