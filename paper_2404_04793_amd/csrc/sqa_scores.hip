@@ -977,7 +977,8 @@ static StripeCut stripe_cut(sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, 
   }
   return best;
 }
-static double two_passes_us(sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, bool split) {
+// Are two passes estimated below `limit` us?
+static bool two_passes_below(double limit, sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, bool split) {
   const bool f32 = dt == SQA_F32;
   const TwoPassFit& f = kTwoPassFit[f32][D == 128];
   const int nb = f32 ? 1 : 2, own = kMT * nb, g = Hq / Hkv, tiles = (P + own - 1) / own, n64 = (P + kMT - 1) / kMT;
@@ -987,22 +988,26 @@ static double two_passes_us(sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, 
     cols += n64 - t * nb;
   }
   const double xcd_kv = (double)(((int64_t)B * Hkv + kXcds - 1) / kXcds);
-  auto pass = [&](double longest, double average, double heads, double alone, double each) {
-    const double per_cu = heads * tiles / kXcdCus;
-    const double latency = f.start + alone * longest;
-    const double work = (f.wg + each * average) * (f.whole * ceil(per_cu) + (1.0 - f.whole) * per_cu);
-    return pow(pow(latency, f.power) + pow(work, f.power), 1.0 / f.power);
-  };
   const int heads_each = split ? 1 : g;          // query heads that a workgroup of pass 2 adds up
-  return f.base + pass(n64, rows / tiles, xcd_kv * g, f.alone1, f.each1) +
-         pass((double)n64 * heads_each, cols / tiles * heads_each, xcd_kv * (g / heads_each), f.alone2, f.each2) + (split ? f.split : 0.0);
+  const double per_cu[2] = {xcd_kv * g * tiles / kXcdCus, xcd_kv * (g / heads_each) * tiles / kXcdCus};
+  const double latency[2] = {f.start + f.alone1 * n64, f.start + f.alone2 * n64 * heads_each};
+  const double each[2] = {f.wg + f.each1 * rows / tiles, f.wg + f.each2 * cols / tiles * heads_each};
+  double work[2], least = f.base + (split ? f.split : 0.0);
+  limit -= least;
+  least = 0.0;
+  for (int i = 0; i < 2; ++i) {
+    work[i] = each[i] * (f.whole * ceil(per_cu[i]) + (1.0 - f.whole) * per_cu[i]);
+    least += latency[i] > work[i] ? latency[i] : work[i];
+  }
+  if (least >= limit) return false;              // (the power sum lies between the larger term and the sum: most calls end here)
+  double us = 0.0;
+  for (int i = 0; i < 2; ++i) us += pow(pow(latency[i], f.power) + pow(work[i], f.power), 1.0 / f.power);
+  return us < limit;
 }
 // The way of a call whose workspace holds `most_chunks` floats per query row.  Two passes have to be clearly ahead where
 // the sequences' lengths differ: the estimates know the longest only.
-static bool two_passes(sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, bool ragged, int64_t most_chunks, StripeCut* cut) {
-  if (P > kStripeMaxP) return true;
-  *cut = stripe_cut(dt, D, B, Hq, Hkv, P, ragged, most_chunks);
-  return two_passes_us(dt, D, B, Hq, Hkv, P, most_chunks >= 3 && split_heads(dt, B, Hq, Hkv, P)) < (ragged ? 0.93 : 1.0) * cut->us;
+static bool two_passes(sqa_dtype dt, int D, int B, int Hq, int Hkv, int P, bool ragged, int64_t most_chunks, const StripeCut& cut) {
+  return two_passes_below((ragged ? 0.93 : 1.0) * cut.us, dt, D, B, Hq, Hkv, P, most_chunks >= 3 && split_heads(dt, B, Hq, Hkv, P));
 }
 
 }  // namespace sqa
@@ -1018,11 +1023,11 @@ extern "C" size_t sqa_prefill_scores_workspace_bytes(int B, int Hq, int Hkv, int
   const int64_t rows = (int64_t)B * Hq * P;
   int floats = 3;
   for (const int d : {64, 128}) {
-    if (D != d && (D == 64 || D == 128)) continue;
+    if (P > sqa::kStripeMaxP || (D != d && (D == 64 || D == 128))) continue;
     for (const sqa_dtype dt : {SQA_F32, SQA_BF16})
       for (const bool ragged : {false, true}) {
-        sqa::StripeCut cut;
-        if (!sqa::two_passes(dt, d, B, Hq, Hkv, P, ragged, INT32_MAX, &cut) && cut.chunks > floats) floats = cut.chunks;
+        const sqa::StripeCut cut = sqa::stripe_cut(dt, d, B, Hq, Hkv, P, ragged, INT32_MAX);
+        if (cut.chunks > floats && !sqa::two_passes(dt, d, B, Hq, Hkv, P, ragged, INT32_MAX, cut)) floats = cut.chunks;
       }
   }
   return (size_t)rows * floats * sizeof(float);
@@ -1067,8 +1072,10 @@ static sqa_status prefill_scores_impl(const void* Q, const void* K, const float*
     else if (shares(ws, rows)) part = shares(ws + rows, rows) ? nullptr : ws + rows;
   }
   a.chunks = 0;
-  StripeCut cut;
-  if (!lse && !two_passes(dt, D, B, Hq, Hkv, P, a.prompt_len != nullptr, (int64_t)(ws_bytes / (rows * sizeof(float))), &cut)) {
+  const int64_t chunks = (int64_t)(ws_bytes / (rows * sizeof(float)));
+  StripeCut cut = {4, 0, 0.0};
+  if (!lse && P <= kStripeMaxP) cut = stripe_cut(dt, D, B, Hq, Hkv, P, a.prompt_len != nullptr, chunks);
+  if (cut.chunks > 0 && !two_passes(dt, D, B, Hq, Hkv, P, a.prompt_len != nullptr, chunks, cut)) {
     a.chunks = cut.chunks;
     auto launch = [&](auto type, auto dim) {
       using T = decltype(type);
