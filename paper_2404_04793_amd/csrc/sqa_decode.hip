@@ -234,7 +234,7 @@ template <int N> __device__ __forceinline__ float group_sum(float v) {
 // heads before the first is used (a lane swap is a vector instruction itself and overwrites both its operands: a copy and wait
 // states).  Sliding window, rows in blocks, us: 8 layers of 96 units under 8 heads, a swap for each head by itself 181, a shuffle
 // 160, shuffles together 155; 320 units under 4 heads 51.7, 51.0, 46.4.  With 1 or 2 heads there is hardly anything to overlap
-// a shuffle's latency with: 160 units under 2 heads, H2O, 2 % less with swaps.
+// a shuffle's latency with: 96 to 320 units under 2 heads, H2O, 2 to 4 % less with swaps.
 template <int G> __device__ __forceinline__ void group_sums32(float (&v)[G]) {
 #pragma unroll
   for (int g = 0; g < G; ++g) v[g] = group_sum<16>(v[g]);
