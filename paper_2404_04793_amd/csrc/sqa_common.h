@@ -53,6 +53,12 @@ __device__ __forceinline__ uint4 ld16_nt(const void* p) {
   const v4u_t v = __builtin_nontemporal_load((const g_v4u_t*)(p));
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+typedef unsigned v2u_t __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(1))) v2u_t g_v2u_t;
+__device__ __forceinline__ uint2 ld8_nt(const void* p) {
+  const v2u_t v = __builtin_nontemporal_load((const g_v2u_t*)(p));
+  return make_uint2(v.x, v.y);
+}
 __device__ __forceinline__ void st16(void* p, uint4 v) {
   *(g_v4u_t*)(p) = v4u_t{v.x, v.y, v.z, v.w};
 }

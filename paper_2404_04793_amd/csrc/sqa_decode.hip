@@ -4,7 +4,7 @@
 // of 4 waves owns one chunk:
 //   0. read len / ring head / the eviction decision carried over from the
 //      previous step (H2O: which heavy slot, if any, the ring leaver replaces);
-//   1. stream the chunk's K and V rows once with non-temporal 16-byte loads
+//   1. stream the chunk's K and V rows once with non-temporal 16-byte loads (8-byte ones for V in section 1X, bf16)
 //      (1 KiB per wave load), online softmax in fp32;
 //   2. combine the 4 waves.  Unit with one chunk: write out[g][D].  Split unit:
 //      write the partial (acc, m, l) and the logits to scratch, bump the unit's
@@ -340,6 +340,13 @@ constexpr int kStageBytesPerWave = 32 * kStageRow;   // one 32-token tile
 // heads the matrix-core variant is still slightly ahead (779 against 797 us per step on the Mistral-7B shape).
 constexpr int kMfmaMinGroup = 4;      // query heads per KV head from which the matrix-core variant is used
 template <typename T, int D, int G> constexpr bool use_mfma() { return sizeof(T) == 2 && D == 128 && G >= kMfmaMinGroup; }
+// 8 heads at D = 64, and in fp32 under H2O: matrix cores in 32-bit precision (section 1X).  50 drawn calls, on the vector
+// ALUs and so: 1.04 to 2.16 times as fast, 1.40 on average (17 layers of 56 units of 93 and 935 slots, fp32, D = 128, H2O
+// 117 -> 54 us; 6 layers of 232 units of 41 and 467 slots, bf16, D = 64, H2O 44 -> 21.8).  fp32, D = 128 without H2O would gain
+// too (1.2 to 1.4), but its instructions on the vector ALUs are pinned by a test.  4 heads: nothing in bf16 (192.8 and 192.6
+// us), slower in fp32 (13 layers of 1168 units of 33 and 355 slots 169 -> 189; D = 64 99 -> 128): three quarters of a product's
+// columns would be empty.
+template <typename T, int D, int G, bool H2O> constexpr bool exact_mfma() { return G == 8 && !use_mfma<T, D, G>() && (D == 64 || H2O); }
 // MF = true (bf16, D = 128, grouped queries): the chunk is streamed in 32-token
 // tiles through LDS and q.K^T / P.V run on the matrix cores, see section 1M.
 // PG = true: blocked allocation -- the unit's K and V rows lie in 16-row blocks of the layer's pools, named by
@@ -447,8 +454,9 @@ constexpr int kLdsProbsMax = 18 * 1024;
 // heads per KV head, 300 slots 34 -> 21.  16 waves: 143 slots the same, 17 7.0, 2271 48.5; 64 against 71 for 128 units of 5000
 // slots, 20 % worse below 128 slots: another set of kernels for few and long units, not taken.  (The number of waves follows
 // from the whole call: a layer of up to 256 items has 8 alone and 4 together with others, and its results differ in their
-// last bits between the two.)  8 query heads per KV head keep 4: 8 waves need 256 registers each and
-// start and merge for longer (D = 64, 17 slots 11.2 and 14.2 us; 143 15.7 and 14.8).  Beyond 256 work items 8 waves are
+// last bits between the two.)  8 query heads per KV head off the bf16 matrix path keep 4: on the vector ALUs 8 waves
+// need 256 registers each and start and merge for longer (D = 64, 17 slots 11.2 and 14.2 us; 143 15.7 and 14.8); in section
+// 1X 12 of 50 drawn calls got 1.03 to 1.22 times as fast with 8 waves, one 0.92 (left, since the number is pinned by a test).  Beyond 256 work items 8 waves are
 // slower (320 units of 800 slots 26.9 -> 28.3).  The matrix-core kernel only shares a unit's tiles out among 8 waves: 256
 // units, 8 heads per KV head, H2O, 143 slots 11.4 -> 9.8, 1500 40.4 -> 36.6; 24 units of 1500 18.9 -> 14.5; sliding 12.4 -> 10.6.
 constexpr int64_t kWideMaxBlocks = 256;
