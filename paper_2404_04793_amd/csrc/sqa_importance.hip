@@ -2,19 +2,21 @@
 // equation of Sec. 3.  A pure streaming reduction (each hidden-state element is
 // read once), so the only roofline is HBM bandwidth.
 //
-// Mapping: grid = (blocks per layer, layers); a workgroup has 4 waves; a wave
+// Mapping: grid = (blocks per layer, layers, sequences); a workgroup has 4 waves; a wave
 // owns whole token rows (row = wave id, stepping by the number of waves of the
 // layer) and its 64 lanes read the row in 16-byte pieces, 1 KiB per wave load.
 // The three dot products accumulate in fp32 per lane, are summed over the wave,
 // and lane 0 adds the row's cosine to a per-wave fp64 sum.  Partial sums go to
 // the workspace and a second tiny kernel adds them in a fixed order: no atomics,
-// results are bit-identical from run to run.
+// results are bit-identical from run to run.  Rows of up to 1 KiB go several to a
+// wave (importance_short_rows_kernel).
 //
 // The same kernel also runs fused into the producer of the "after" tensor: the
 // residual connection h_out = h_in + attn_out.  Then it reads h_in and attn_out,
 // writes h_out rounded to the storage type, and takes the cosine against those
 // stored values in the same pass, so the probe itself moves no extra byte.
 #include "sqa_common.h"
+#include <type_traits>
 
 namespace sqa {
 
@@ -59,32 +61,81 @@ template <> struct Residual<bf16_t> {
   }
 };
 
+struct ImpArgs {
+  const void* h_in;
+  const void* other;             // h_out, or attn_out where h_out is written
+  void* h_out_w;                 // may be h_in or other
+  int64_t n_tokens;
+  int hidden;
+  const int32_t* seq_start;      // [gridDim.z + 1] or NULL
+  double* partial;               // [layers][gridDim.z][gridDim.x]
+  float* cos_out;
+};
+
+template <int CTRL> __device__ __forceinline__ float imp_dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+// sum over groups of W lanes, in every lane, by vector instructions
+template <int W> __device__ __forceinline__ float lanes_sum(float v) {
+  static_assert(W == 32 || W == 64, "lanes of a row");
+  typedef unsigned u2_t __attribute__((ext_vector_type(2)));
+  v += imp_dpp<0xB1>(v);              // quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror, row_mirror
+  v += imp_dpp<0x4E>(v);
+  v += imp_dpp<0x141>(v);
+  v += imp_dpp<0x140>(v);
+  u2_t r = __builtin_bit_cast(u2_t, __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+  v = __uint_as_float(r.x) + __uint_as_float(r.y);
+  if constexpr (W == 64) {
+    r = __builtin_bit_cast(u2_t, __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false));
+    v = __uint_as_float(r.x) + __uint_as_float(r.y);
+  }
+  return v;
+}
+
+__device__ __forceinline__ int64_t imp_rows(const ImpArgs& a, int seq, int64_t& lo) {
+  lo = 0;
+  int64_t hi = a.n_tokens;            // all of the layer's rows unless the tokens are segmented
+  if (a.seq_start) {
+    lo = a.seq_start[seq];
+    hi = a.seq_start[seq + 1];
+    lo = lo < 0 ? 0 : lo;
+    hi = hi > a.n_tokens ? a.n_tokens : hi;
+  }
+  return hi;
+}
+
+// the cosine of a (layer, sequence) from the sum over its rows
+__device__ __forceinline__ void imp_store(const ImpArgs& a, int64_t item, int seq, double sum) {
+  int64_t lo;
+  const int64_t rows = imp_rows(a, seq, lo) - lo;
+  a.cos_out[item] = rows > 0 ? (float)(sum / (double)rows) : 0.f;
+}
+
+// a workgroup's sum, or (if there is only one) the result
+__device__ __forceinline__ void imp_put(const ImpArgs& a, const double* waves) {
+  double s = 0.0;
+  for (int w = 0; w < kImpWaves; ++w) s += waves[w];
+  const int64_t item = (int64_t)blockIdx.y * gridDim.z + blockIdx.z;
+  if (gridDim.x == 1) imp_store(a, item, blockIdx.z, s);
+  else a.partial[item * gridDim.x + blockIdx.x] = s;
+}
+
 // FUSE = false: h_out is read.  FUSE = true: `other` is attn_out and h_out is written (NT: non-temporally).
-template <typename T, bool FUSE, bool NT = false>
-__global__ __launch_bounds__(kImpThreads) void importance_partial_kernel(
-    const T* h_in, const T* other, T* h_out_w /*may be h_in or other*/, int64_t n_tokens, int hidden,
-    const int32_t* __restrict__ seq_start /*[gridDim.z + 1] or NULL*/,
-    double* __restrict__ partial /*[layers][gridDim.z][gridDim.x]*/) {
+template <typename T, bool FUSE, bool NT>
+__global__ __launch_bounds__(kImpThreads) void importance_partial_kernel(const ImpArgs args) {
   constexpr int E = elem<T>::per16;
   const int lane = threadIdx.x & (SQA_WAVE - 1);
   const int wave = threadIdx.x / SQA_WAVE;
   const int layer = blockIdx.y;
-  const int64_t row_elems = hidden;
-  const char* A = reinterpret_cast<const char*>(h_in + (int64_t)layer * n_tokens * row_elems);
-  const char* Bp = reinterpret_cast<const char*>(other + (int64_t)layer * n_tokens * row_elems);
-  char* Wp = FUSE ? reinterpret_cast<char*>(h_out_w + (int64_t)layer * n_tokens * row_elems) : nullptr;
-  const int chunks = hidden / E;                 // 16-byte pieces per row
-  const int64_t row_bytes = row_elems * (int64_t)sizeof(T);
+  const int chunks = args.hidden / E;            // 16-byte pieces per row
+  const int64_t row_bytes = args.hidden * (int64_t)sizeof(T), layer_bytes = args.n_tokens * row_bytes;
+  const char* A = static_cast<const char*>(args.h_in) + layer * layer_bytes;
+  const char* Bp = static_cast<const char*>(args.other) + layer * layer_bytes;
+  char* Wp = FUSE ? static_cast<char*>(args.h_out_w) + layer * layer_bytes : nullptr;
   const int64_t stride = (int64_t)gridDim.x * kImpWaves;
 
-  // rows of this (layer, sequence): all of the layer's unless the tokens are segmented
-  int64_t row_lo = 0, row_hi = n_tokens;
-  if (seq_start) {
-    row_lo = seq_start[blockIdx.z];
-    row_hi = seq_start[blockIdx.z + 1];
-    row_lo = row_lo < 0 ? 0 : row_lo;
-    row_hi = row_hi > n_tokens ? n_tokens : row_hi;
-  }
+  int64_t row_lo;
+  const int64_t row_hi = imp_rows(args, blockIdx.z, row_lo);
   auto put = [](char* p, const uint4& v) { if constexpr (NT) st16_nt(p, v); else st16(p, v); };
   double wave_cos = 0.0;
   for (int64_t row = row_lo + (int64_t)blockIdx.x * kImpWaves + wave; row < row_hi; row += stride) {
@@ -111,6 +162,17 @@ __global__ __launch_bounds__(kImpThreads) void importance_partial_kernel(
       Dots<T>::acc(a0, b0, ab, aa, bb); Dots<T>::acc(a1, b1, ab, aa, bb);
       Dots<T>::acc(a2, b2, ab, aa, bb); Dots<T>::acc(a3, b3, ab, aa, bb);
     }
+    for (; c + SQA_WAVE < chunks; c += 2 * SQA_WAVE) {
+      const uint4 a0 = ld16_nt(a + (int64_t)c * 16);
+      uint4 b0 = ld16_nt(b + (int64_t)c * 16);
+      const uint4 a1 = ld16_nt(a + (int64_t)(c + SQA_WAVE) * 16);
+      uint4 b1 = ld16_nt(b + (int64_t)(c + SQA_WAVE) * 16);
+      if (FUSE) {
+        b0 = Residual<T>::add(a0, b0); b1 = Residual<T>::add(a1, b1);
+        put(w + (int64_t)c * 16, b0); put(w + (int64_t)(c + SQA_WAVE) * 16, b1);
+      }
+      Dots<T>::acc(a0, b0, ab, aa, bb); Dots<T>::acc(a1, b1, ab, aa, bb);
+    }
     for (; c < chunks; c += SQA_WAVE) {
       const uint4 a0 = ld16_nt(a + (int64_t)c * 16);
       uint4 b0 = ld16_nt(b + (int64_t)c * 16);
@@ -124,19 +186,77 @@ __global__ __launch_bounds__(kImpThreads) void importance_partial_kernel(
   __shared__ double s_part[kImpWaves];
   if (lane == 0) s_part[wave] = wave_cos;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int w = 0; w < kImpWaves; ++w) s += s_part[w];
-    partial[((int64_t)layer * gridDim.z + blockIdx.z) * gridDim.x + blockIdx.x] = s;
+  if (threadIdx.x == 0) imp_put(args, s_part);
+}
+
+// Rows of up to 1 KiB: W lanes share a row and hold one 16-byte piece of it, a wave takes 64 / W rows side by side and 4 such
+// groups at a time.  A lane keeps a row's sums until W rows per group have come; then their cosines are worked out together (one
+// row at a time, each cost a wave some 300 double-precision instructions, half of the lanes had nothing to load at 512 bytes,
+// and there was one load in flight).  Residual add, 19 layers of 2159 rows of 256 bf16 29.0 -> 17.0 us; 9 sequences, 11 layers
+// of 9000 rows of 256 56.8 -> 21.4.  Longer rows are better off one to a wave (2048 rows of 4096 bf16 13.2, 15.4 so: the sums
+// over the lanes at the end come on top).
+template <typename T, bool FUSE, bool NT, int W>
+__global__ __launch_bounds__(kImpThreads) void importance_short_rows_kernel(const ImpArgs args) {
+  constexpr int E = elem<T>::per16, SIDE = SQA_WAVE / W, ROWS = 4 * SIDE;
+  const int lane = threadIdx.x & (SQA_WAVE - 1), side = lane / W, lw = lane % W;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / SQA_WAVE);
+  const int chunks = args.hidden / E;            // at most W
+  const int64_t row_bytes = (int64_t)chunks * 16, layer_bytes = args.n_tokens * row_bytes;
+  const char* A = static_cast<const char*>(args.h_in) + blockIdx.y * layer_bytes;
+  const char* B = static_cast<const char*>(args.other) + blockIdx.y * layer_bytes;
+  char* O = FUSE ? static_cast<char*>(args.h_out_w) + blockIdx.y * layer_bytes : nullptr;
+  int64_t row_lo;
+  const int64_t row_hi = imp_rows(args, blockIdx.z, row_lo);
+  double cosines = 0.0;
+  float k_ab = 0.f, k_aa = 0.f, k_bb = 0.f;      // the sums of the row that this lane keeps
+  int kept = 0;                                  // rows kept per lane group
+  auto flush = [&]() {                           // (a lane without a row has zeros: it adds 0)
+    const double na = fmax(sqrt((double)k_aa), 1e-8), nb = fmax(sqrt((double)k_bb), 1e-8);
+    cosines += (double)k_ab / (na * nb);
+    k_ab = k_aa = k_bb = 0.f;
+    kept = 0;
+  };
+  for (int64_t row0 = row_lo + ((int64_t)blockIdx.x * kImpWaves + wave) * ROWS; row0 < row_hi; row0 += (int64_t)gridDim.x * kImpWaves * ROWS) {
+    const int there = (int)min(row_hi - row0, (int64_t)ROWS);      // rows of this turn
+    uint4 x[4], y[4];
+    uint32_t off[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {                // (beyond the last row or piece: that one again, counted as zeros)
+      off[i] = (uint32_t)min(i * SIDE + side, there - 1) * (uint32_t)row_bytes + min(lw, chunks - 1) * 16u;
+      x[i] = ld16_nt(A + row0 * row_bytes + off[i]);
+      y[i] = ld16_nt(B + row0 * row_bytes + off[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool mine = i * SIDE + side < there && lw < chunks;
+      if (FUSE) {
+        y[i] = Residual<T>::add(x[i], y[i]);
+        char* o = O + row0 * row_bytes + off[i];
+        if (mine) { if constexpr (NT) st16_nt(o, y[i]); else st16(o, y[i]); }
+      }
+      if (!mine) x[i] = y[i] = make_uint4(0, 0, 0, 0);
+      float ab = 0.f, aa = 0.f, bb = 0.f;
+      Dots<T>::acc(x[i], y[i], ab, aa, bb);
+      ab = lanes_sum<W>(ab); aa = lanes_sum<W>(aa); bb = lanes_sum<W>(bb);
+      if (lw == kept) { k_ab = ab; k_aa = aa; k_bb = bb; }
+      if (++kept == W) flush();
+    }
   }
+  if (kept > 0) flush();
+  __shared__ double s_part[kImpWaves];
+  cosines = wave_sum(cosines);
+  if (lane == 0) s_part[wave] = cosines;
+  __syncthreads();
+  if (threadIdx.x == 0) imp_put(args, s_part);
 }
 
 // one workgroup per (layer, sequence): blockIdx.x = layer * n_seq + sequence.  All of its partial sums are requested
 // at once and added in a fixed order (one wave that took 16 turns for 1024 of them: 5.8 us; 16384 rows of 4096 bf16
 // in one layer, both kernels: 45.9 -> 42.3 us, inside the residual add 71.5 -> 68.0).  64 threads for up to 256.
+// (The last workgroup to arrive adding them instead was slower: its round trips -- stores acknowledged, arrivals counted, sums
+// fetched -- take longer than a launch: 2048 rows of 4096 13.4 -> 17.2, 300 8.8 -> 11.0.)
 __global__ __launch_bounds__(kImpThreads) void importance_final_kernel(
-    const double* __restrict__ partial, int n_part, int64_t n_tokens, const int32_t* __restrict__ seq_start, int n_seq,
-    float* __restrict__ cos_out) {
+    const ImpArgs a, int n_part, int n_seq) {
   const int item = blockIdx.x;
   const int lane = threadIdx.x & (SQA_WAVE - 1);
   constexpr int N = 4;                            // >= n_part / threads
@@ -144,7 +264,7 @@ __global__ __launch_bounds__(kImpThreads) void importance_final_kernel(
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const int at = threadIdx.x + i * blockDim.x;
-    v[i] = partial[(int64_t)item * n_part + min(at, n_part - 1)];
+    v[i] = a.partial[(int64_t)item * n_part + min(at, n_part - 1)];
     v[i] = at < n_part ? v[i] : 0.0;
   }
   double s = 0.0;
@@ -158,16 +278,7 @@ __global__ __launch_bounds__(kImpThreads) void importance_final_kernel(
     s = 0.0;
     for (int w = 0; w < kImpWaves; ++w) s += s_wave[w];
   }
-  if (threadIdx.x != 0) return;
-  int64_t rows = n_tokens;
-  if (seq_start) {
-    const int q = item % n_seq;
-    int64_t lo = seq_start[q], hi = seq_start[q + 1];
-    lo = lo < 0 ? 0 : lo;
-    hi = hi > n_tokens ? n_tokens : hi;
-    rows = hi - lo;
-  }
-  cos_out[item] = rows > 0 ? (float)(s / (double)rows) : 0.f;
+  if (threadIdx.x == 0) imp_store(a, item, item % n_seq, s);
 }
 
 static int imp_blocks(int64_t n_tokens) {
@@ -196,31 +307,39 @@ static sqa_status launch_importance(const void* h_in, const void* other, void* h
     return SQA_ERR_SHAPE;
   if (ws_bytes < (size_t)n_seq * sqa_layer_importance_workspace_bytes(n_layers, n_tokens, hidden)) return SQA_ERR_CAPACITY;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int nblk = imp_blocks(n_tokens);
-  double* partial = static_cast<double*>(workspace);
-  dim3 grid(nblk, n_layers, n_seq);
+  const int pieces = hidden / (dt == SQA_F32 ? 4 : 8);
+  const int rows = pieces <= 32 ? 8 : (pieces <= 64 ? 4 : 1);      // of a wave at a time
+  // (several sequences, whose lengths are not known here: twice what the average one needs; up to 3 turns of a workgroup: one,
+  // which needs no second kernel: 23 layers of 20 rows of 256 bf16 9.2 -> 6.0 us)
+  const int64_t share = n_seq == 1 ? n_tokens : (2 * n_tokens + n_seq - 1) / n_seq;
+  int nblk = imp_blocks((share + rows - 1) / rows);
+  nblk = nblk <= 3 ? 1 : nblk;
+  ImpArgs a;
+  a.h_in = h_in; a.other = other; a.h_out_w = h_out_w;
+  a.n_tokens = n_tokens; a.hidden = hidden; a.seq_start = seq_start;
+  a.partial = static_cast<double*>(workspace);
+  a.cos_out = cos_out;
+  const dim3 grid(nblk, n_layers, n_seq);
   // h_out is stored non-temporally where it is larger than the 256 MB Infinity Cache: nothing of it would be found
   // there again (16 layers of 4096 x 4096 bf16, 537 MB: 304 us, 285 so); below that plain stores are absorbed by the
   // cache and found by the next kernel (16384 x 4096, 134 MB: 68 us, 74 so).
   const bool nt = fuse && (int64_t)n_layers * n_tokens * hidden * (dt == SQA_F32 ? 4 : 2) >= ((int64_t)256 << 20);
-  if (dt == SQA_F32) {
-    const float* a = static_cast<const float*>(h_in);
-    const float* b = static_cast<const float*>(other);
-    float* w = static_cast<float*>(h_out_w);
-    if (nt) importance_partial_kernel<float, true, true><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
-    else if (fuse) importance_partial_kernel<float, true><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
-    else importance_partial_kernel<float, false><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
-  } else {
-    const bf16_t* a = static_cast<const bf16_t*>(h_in);
-    const bf16_t* b = static_cast<const bf16_t*>(other);
-    bf16_t* w = static_cast<bf16_t*>(h_out_w);
-    if (nt) importance_partial_kernel<bf16_t, true, true><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
-    else if (fuse) importance_partial_kernel<bf16_t, true><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
-    else importance_partial_kernel<bf16_t, false><<<grid, kImpThreads, 0, st>>>(a, b, w, n_tokens, hidden, seq_start, partial);
-  }
+  auto launch = [&](auto type, auto fused, auto streamed) {
+    using T = decltype(type);
+    constexpr bool F = decltype(fused)::value, N = decltype(streamed)::value;
+    if (rows == 8) importance_short_rows_kernel<T, F, N, 32><<<grid, kImpThreads, 0, st>>>(a);
+    else if (rows == 4) importance_short_rows_kernel<T, F, N, 64><<<grid, kImpThreads, 0, st>>>(a);
+    else importance_partial_kernel<T, F, N><<<grid, kImpThreads, 0, st>>>(a);
+  };
+  auto pick = [&](auto type) {
+    if (nt) launch(type, std::true_type{}, std::true_type{});
+    else if (fuse) launch(type, std::true_type{}, std::false_type{});
+    else launch(type, std::false_type{}, std::false_type{});
+  };
+  if (dt == SQA_F32) pick(float{}); else pick(bf16_t{});
   SQA_HIP_CHECK(hipGetLastError());
   static_assert(kImpMaxBlocks <= 4 * kImpThreads, "partial sums per thread of the final kernel");
-  importance_final_kernel<<<n_layers * n_seq, nblk <= 4 * SQA_WAVE ? SQA_WAVE : kImpThreads, 0, st>>>(partial, nblk, n_tokens, seq_start, n_seq, cos_out);
+  if (nblk > 1) importance_final_kernel<<<n_layers * n_seq, nblk <= 4 * SQA_WAVE ? SQA_WAVE : kImpThreads, 0, st>>>(a, nblk, n_seq);
   SQA_HIP_CHECK(hipGetLastError());
   return SQA_OK;
 }

@@ -77,6 +77,35 @@ def test_residual_add_importance(sqa, dtype, L, T, d, inplace):
         assert np.array_equal(alone.view(np.uint32), cos.astype(np.float32).view(np.uint32))
 
 
+@pytest.mark.parametrize("dtype,d", [("f32", 8), ("bf16", 8), ("f32", 128), ("bf16", 256), ("bf16", 264), ("f32", 256), ("bf16", 512),
+                                     ("bf16", 520), ("f32", 264)])
+@pytest.mark.parametrize("T", [1, 3, 31, 32, 33, 96, 97, 128, 129, 1030])
+def test_importance_of_short_rows(sqa, dtype, d, T):
+    """Rows of up to 1 KiB share a wave (32 or 64 lanes each; 32 or 64 rows' cosines are worked out together), one workgroup's
+    result needs no second kernel: around those numbers of rows, pieces per row and workgroups, alone, inside the residual add
+    (in place too) and per sequence.  fp32 products over at most 520 elements."""
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator().manual_seed(T * 1000 + d)
+    a, r = (torch.randn(2, T, d, generator=gen).to(tdt).to(DEV) for _ in range(2))
+    h = torch.empty_like(a)
+    cos = sqa.residual_add_importance(a, r, h)
+    assert torch.equal(h, a + r)
+    ref = O.layer_importance(np64(a), np64(h))
+    assert _cos_rel(cos.cpu().numpy().astype(np.float64), ref) < 1e-5
+    assert torch.equal(cos, sqa.layer_importance(a, h))
+    for inplace in ("h_in", "attn_out"):
+        x, y = a.clone(), r.clone()
+        z = x if inplace == "h_in" else y
+        assert torch.equal(cos, sqa.residual_add_importance(x, y, z)) and torch.equal(z, h)
+    cut = [0, T // 3, T // 3, T]
+    per = sqa.layer_importance_seq(a, h, torch.tensor(cut, dtype=torch.int32, device=DEV)).cpu().numpy().astype(np.float64)
+    for i in range(3):
+        if cut[i] == cut[i + 1]:
+            assert np.all(per[:, i] == 0.0)
+        else:
+            assert _cos_rel(per[:, i], O.layer_importance(np64(a[:, cut[i]:cut[i + 1]]), np64(h[:, cut[i]:cut[i + 1]]))) < 1e-5
+
+
 @pytest.mark.parametrize("L,T,d", [(2, 1021, 64), (1, 1025, 128), (1, 4099, 64),      # 256, 257 and 1024 partial sums
                                    (1, 32768, 4096), (2, 16383, 4096)])                # h_out of 256 MiB, and just below
 def test_residual_add_importance_store_forms(sqa, L, T, d):
