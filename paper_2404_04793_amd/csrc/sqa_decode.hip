@@ -340,9 +340,9 @@ constexpr int kStageBytesPerWave = 32 * kStageRow;   // one 32-token tile
 // heads the matrix-core variant is still slightly ahead (779 against 797 us per step on the Mistral-7B shape).
 constexpr int kMfmaMinGroup = 4;      // query heads per KV head from which the matrix-core variant is used
 template <typename T, int D, int G> constexpr bool use_mfma() { return sizeof(T) == 2 && D == 128 && G >= kMfmaMinGroup; }
-// 8 heads at D = 64, and in fp32 under H2O: matrix cores in 32-bit precision (section 1X).  50 drawn calls, on the vector
-// ALUs and so: 1.04 to 2.16 times as fast, 1.40 on average (17 layers of 56 units of 93 and 935 slots, fp32, D = 128, H2O
-// 117 -> 54 us; 6 layers of 232 units of 41 and 467 slots, bf16, D = 64, H2O 44 -> 21.8).  fp32, D = 128 without H2O would gain
+// 8 heads at D = 64, and in fp32 under H2O: matrix cores in 32-bit precision (section 1X).  46 drawn calls, on the vector
+// ALUs and so: 1.12 to 2.56 times as fast, 1.53 on average (17 layers of 56 units of 93 and 935 slots, fp32, D = 128, H2O
+// 118 -> 46 us; 6 layers of 232 units of 41 and 467 slots, bf16, D = 64, H2O 44.8 -> 21.2).  fp32, D = 128 without H2O would gain
 // too (1.2 to 1.4), but its instructions on the vector ALUs are pinned by a test.  4 heads: nothing in bf16 (192.8 and 192.6
 // us), slower in fp32 (13 layers of 1168 units of 33 and 355 slots 169 -> 189; D = 64 99 -> 128): three quarters of a product's
 // columns would be empty.
