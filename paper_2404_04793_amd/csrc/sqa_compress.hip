@@ -28,6 +28,12 @@ constexpr int64_t kCmpFill = 384;         // workgroups that a call with few uni
 constexpr int64_t kCmpCUs = 256;
 constexpr int64_t kCmpManyUnits = 2048, kCmpManyRows = 128;   // launches of more units than run at once, with fewer rows each: see launch_compress
 constexpr int64_t kCmpMaxParts = 256;         // workgroups per unit
+// The rows are stored non-temporally (the next reader is a decode step, which streams the whole cache that way), and read so
+// too in launches that move at least as much as the Infinity Cache holds; below, the prompt's rows may still be found there.
+// us, plain, stores only, both: 7B shape (3.4 GB) 654, 640, 618; 40 layers of a joining sequence, fp32, D = 64 (282 MB) 81.7,
+// 78.5, 76.1; 12 layers of 160 units, fp32, D = 64 (236 MB) 53.6, 46.8, 48.8; one sequence joining (93 MB) 39.8, 34.3, 36.8;
+// 22 layers (34 MB) 13.3, 12.9, 15.7.
+constexpr int64_t kCmpStreamBytes = (int64_t)256 << 20;
 constexpr int kKeysInLdsMax = 16384;     // scores staged in LDS up to this many candidates
 
 __device__ __forceinline__ uint32_t score_key(float s) {
@@ -94,7 +100,8 @@ static_assert(SQA_MAX_LAYERS <= 256, "CompressBatch::layer holds a layer index i
 
 // MANY: many short units, where what counts is how little each one does (one workgroup per unit, two rows in flight
 // per thread); otherwise a unit may be shared out, four rows are in flight, and many candidates are listed in runs.
-template <typename T, int D, bool MANY>
+// NT: rows are read non-temporally.
+template <typename T, int D, bool MANY, bool NT>
 __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
     const CompressBatch batch, int P /*prompt rows per unit in memory*/, int policy, int n_sink, int lds_words /*dynamic LDS of the launch, in 32-bit words*/) {
   const int li = blockIdx.y;              // slot of this launch: a layer
@@ -290,15 +297,17 @@ __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
 #pragma unroll
     for (int x = 0; x < R; ++x) {
       const int64_t src = source(j + x * GROUPS < j_hi ? j + x * GROUPS : j);
-      kr[x] = ld16(reinterpret_cast<const char*>(Ku) + src * ROWB + c * 16);
-      vr[x] = ld16(reinterpret_cast<const char*>(Vu) + src * ROWB + c * 16);
+      const char* kp = reinterpret_cast<const char*>(Ku) + src * ROWB + c * 16;
+      const char* vp = reinterpret_cast<const char*>(Vu) + src * ROWB + c * 16;
+      kr[x] = NT ? ld16_nt(kp) : ld16(kp);
+      vr[x] = NT ? ld16_nt(vp) : ld16(vp);
     }
 #pragma unroll
     for (int x = 0; x < R; ++x)
       if (j + x * GROUPS < j_hi) {
         const int64_t dst = row_of(j + x * GROUPS);
-        st16(Kc + dst * ROWB + c * 16, kr[x]);
-        st16(Vc + dst * ROWB + c * 16, vr[x]);
+        st16_nt(Kc + dst * ROWB + c * 16, kr[x]);
+        st16_nt(Vc + dst * ROWB + c * 16, vr[x]);
       }
   };
   int j = j_lo + grp;
@@ -370,7 +379,9 @@ static hipError_t launch_compress(CompressBatch& batch, int n, int P, int policy
   // 91 / 94, of 168 152.6 / 152.6; 8192 of 98, fp32, D = 64 179 / 182; 65536 of 55 772 / 784; 8192 of 409 667 / 662;
   // 16 layers, 1024 units of 98 28.1 / 27.3.
   const bool many = (int64_t)units * n >= kCmpManyUnits && rows < kCmpManyRows * units * n;
-  auto fn = many ? prefill_compress_kernel<T, D, true> : prefill_compress_kernel<T, D, false>;
+  const bool stream = rows * (4 * D * (int64_t)sizeof(T)) >= kCmpStreamBytes;       // K and V, read and written
+  auto fn = many ? (stream ? prefill_compress_kernel<T, D, true, true> : prefill_compress_kernel<T, D, true, false>)
+                 : (stream ? prefill_compress_kernel<T, D, false, true> : prefill_compress_kernel<T, D, false, false>);
   if (lds > 48 * 1024) {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(fn), lds);
     if (e != hipSuccess) return e;
