@@ -28,12 +28,12 @@ constexpr int64_t kCmpFill = 384;         // workgroups that a call with few uni
 constexpr int64_t kCmpCUs = 256;
 constexpr int64_t kCmpManyUnits = 2048, kCmpManyRows = 128;   // launches of more units than run at once, with fewer rows each: see launch_compress
 constexpr int64_t kCmpMaxParts = 256;         // workgroups per unit
-// The rows are stored non-temporally (the next reader is a decode step, which streams the whole cache that way), and read so
-// too in launches that move at least as much as the Infinity Cache holds; below, the prompt's rows may still be found there.
-// us, plain, stores only, both: 7B shape (3.4 GB) 654, 640, 618; 40 layers of a joining sequence, fp32, D = 64 (282 MB) 81.7,
-// 78.5, 76.1; 12 layers of 160 units, fp32, D = 64 (236 MB) 53.6, 46.8, 48.8; one sequence joining (93 MB) 39.8, 34.3, 36.8;
-// 22 layers (34 MB) 13.3, 12.9, 15.7.
-constexpr int64_t kCmpStreamBytes = (int64_t)256 << 20;
+// Caches that the Infinity Cache (256 MB) does not hold: rows are stored non-temporally, and in launches that move as much as
+// it holds they are read so too.  us, plain, stores only, both: 7B shape (3.4 GB moved) 654, 640, 618; 40 units of 32 layers of
+// 512 tokens 807, 787, 772; one sequence joining a 600 MB cache (93 MB moved) 39.8, 34.3, 36.8, and with the decode step that
+// follows, which has the plain stores to write back, 232 and 207 (stores only).  A smaller cache is found in the Infinity Cache
+// by that step after plain stores: 12 layers of 160 units, fp32, D = 64 (118 MB) 53.5 and 50.2, with the step 65.2 and 72.5.
+constexpr int64_t kCmpCacheBytes = (int64_t)320 << 20, kCmpStreamBytes = (int64_t)256 << 20;
 constexpr int kKeysInLdsMax = 16384;     // scores staged in LDS up to this many candidates
 
 __device__ __forceinline__ uint32_t score_key(float s) {
@@ -100,8 +100,8 @@ static_assert(SQA_MAX_LAYERS <= 256, "CompressBatch::layer holds a layer index i
 
 // MANY: many short units, where what counts is how little each one does (one workgroup per unit, two rows in flight
 // per thread); otherwise a unit may be shared out, four rows are in flight, and many candidates are listed in runs.
-// NT: rows are read non-temporally.
-template <typename T, int D, bool MANY, bool NT>
+// NT: rows are stored (1), or read and stored (2) non-temporally.
+template <typename T, int D, bool MANY, int NT>
 __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
     const CompressBatch batch, int P /*prompt rows per unit in memory*/, int policy, int n_sink, int lds_words /*dynamic LDS of the launch, in 32-bit words*/) {
   const int li = blockIdx.y;              // slot of this launch: a layer
@@ -299,15 +299,20 @@ __global__ __launch_bounds__(kCmpThreads) void prefill_compress_kernel(
       const int64_t src = source(j + x * GROUPS < j_hi ? j + x * GROUPS : j);
       const char* kp = reinterpret_cast<const char*>(Ku) + src * ROWB + c * 16;
       const char* vp = reinterpret_cast<const char*>(Vu) + src * ROWB + c * 16;
-      kr[x] = NT ? ld16_nt(kp) : ld16(kp);
-      vr[x] = NT ? ld16_nt(vp) : ld16(vp);
+      kr[x] = NT == 2 ? ld16_nt(kp) : ld16(kp);
+      vr[x] = NT == 2 ? ld16_nt(vp) : ld16(vp);
     }
 #pragma unroll
     for (int x = 0; x < R; ++x)
       if (j + x * GROUPS < j_hi) {
         const int64_t dst = row_of(j + x * GROUPS);
-        st16_nt(Kc + dst * ROWB + c * 16, kr[x]);
-        st16_nt(Vc + dst * ROWB + c * 16, vr[x]);
+        if constexpr (NT != 0) {
+          st16_nt(Kc + dst * ROWB + c * 16, kr[x]);
+          st16_nt(Vc + dst * ROWB + c * 16, vr[x]);
+        } else {
+          st16(Kc + dst * ROWB + c * 16, kr[x]);
+          st16(Vc + dst * ROWB + c * 16, vr[x]);
+        }
       }
   };
   int j = j_lo + grp;
@@ -351,7 +356,7 @@ __global__ __launch_bounds__(kCmpThreads) void kept_idx_sorted_kernel(sqa_layer_
 
 template <typename T, int D>
 static hipError_t launch_compress(CompressBatch& batch, int n, int P, int policy, int n_sink,
-                                   unsigned units, size_t lds, hipStream_t st) {
+                                   unsigned units, int64_t cache_bytes /*K and V of the call's layers*/, size_t lds, hipStream_t st) {
   // A unit's rows are shared out among workgroups where one per unit leaves CUs idle (fewer units than CUs) or busy for
   // long after the others (fewer than two per CU, and the longest has more than 1.5 times a CU's share of the rows):
   // as many pieces as bring the launch to 384 equal workgroups, of at least one trip of the copy loop each.  One
@@ -379,9 +384,13 @@ static hipError_t launch_compress(CompressBatch& batch, int n, int P, int policy
   // 91 / 94, of 168 152.6 / 152.6; 8192 of 98, fp32, D = 64 179 / 182; 65536 of 55 772 / 784; 8192 of 409 667 / 662;
   // 16 layers, 1024 units of 98 28.1 / 27.3.
   const bool many = (int64_t)units * n >= kCmpManyUnits && rows < kCmpManyRows * units * n;
-  const bool stream = rows * (4 * D * (int64_t)sizeof(T)) >= kCmpStreamBytes;       // K and V, read and written
-  auto fn = many ? (stream ? prefill_compress_kernel<T, D, true, true> : prefill_compress_kernel<T, D, true, false>)
-                 : (stream ? prefill_compress_kernel<T, D, false, true> : prefill_compress_kernel<T, D, false, false>);
+  auto pick = [&](auto many_tag) {
+    constexpr bool M = decltype(many_tag)::value;
+    if (cache_bytes < kCmpCacheBytes) return prefill_compress_kernel<T, D, M, 0>;
+    const bool stream = rows * (4 * D * (int64_t)sizeof(T)) >= kCmpStreamBytes;     // K and V, read and written
+    return stream ? prefill_compress_kernel<T, D, M, 2> : prefill_compress_kernel<T, D, M, 1>;
+  };
+  auto fn = many ? pick(std::true_type{}) : pick(std::false_type{});
   if (lds > 48 * 1024) {
     const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(fn), lds);
     if (e != hipSuccess) return e;
@@ -463,6 +472,11 @@ extern "C" sqa_status sqa_prefill_compress_layers_ex(const void* const* K, const
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   const unsigned units = (unsigned)(B * Hkv);
+  // (blocks: the pools, which hold all sequences; packed units: at most so much)
+  int64_t cache_bytes = 0;
+  for (int i = 0; i < n_layers; ++i)
+    cache_bytes += (layers[i].block_table ? (int64_t)layers[i].n_blocks * SQA_BLOCK_SLOTS : (int64_t)units * layers[i].capacity) *
+                   (2 * D * (kv_dt == SQA_F32 ? 4 : 2));
   for (int l0 = 0; l0 < n_layers; l0 += kCmpBatch) {
     const int n = n_layers - l0 < kCmpBatch ? n_layers - l0 : kCmpBatch;
     CompressBatch batch;
@@ -488,11 +502,11 @@ extern "C" sqa_status sqa_prefill_compress_layers_ex(const void* const* K, const
     for (int i = n; i < kCmpBatch; ++i) { batch.L[i] = layers[l0]; batch.K[i] = nullptr; batch.V[i] = nullptr; batch.scores[i] = nullptr; batch.layer[i] = 0; }
     hipError_t e;
     if (kv_dt == SQA_F32) {
-      if (D == 64) e = launch_compress<float, 64>(batch, n, P, policy, n_sink, units, lds, st);
-      else e = launch_compress<float, 128>(batch, n, P, policy, n_sink, units, lds, st);
+      if (D == 64) e = launch_compress<float, 64>(batch, n, P, policy, n_sink, units, cache_bytes, lds, st);
+      else e = launch_compress<float, 128>(batch, n, P, policy, n_sink, units, cache_bytes, lds, st);
     } else {
-      if (D == 64) e = launch_compress<bf16_t, 64>(batch, n, P, policy, n_sink, units, lds, st);
-      else e = launch_compress<bf16_t, 128>(batch, n, P, policy, n_sink, units, lds, st);
+      if (D == 64) e = launch_compress<bf16_t, 64>(batch, n, P, policy, n_sink, units, cache_bytes, lds, st);
+      else e = launch_compress<bf16_t, 128>(batch, n, P, policy, n_sink, units, cache_bytes, lds, st);
     }
     SQA_HIP_CHECK(e);
   }

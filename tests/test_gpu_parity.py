@@ -13,7 +13,7 @@ from oracle import sqa_oracle as O
 from oracle import pipeline as OP
 from paper_2404_04793_amd import workloads as W
 from tests.harness import (TOL, check_scores_after_run, check_step_scores, clustering_margin, export_state, import_state,
-                           near_tie_swap, np64, oracle_view, rel_err, round_scores_f32, uses_matrix_cores)
+                           near_tie_swap, np64, oracle_view, rel_err, round_scores_f32, unit_kv, uses_matrix_cores)
 
 pytestmark = pytest.mark.gpu
 
@@ -540,6 +540,43 @@ def test_prefill_compress_of_many_short_units(sqa, dtype, D, B, b):
         got = export_state(caches, 0, x, h)
         assert got["pos"].tolist() == want["pos"].tolist(), (x, h)
         assert all(np.array_equal(got[f], want[f]) for f in ("K", "V", "score")), (x, h)
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("policy,units,P,b,blocked", [("h2o", 6, 500, 211, True),           # stores: a pool of 320 MiB, little of it written
+                                                      ("sliding", 1100, 70, 33, True),       # ... in many short units
+                                                      ("h2o", 64, 4096, 4100, False)])       # stores and loads: 256 MiB moved
+def test_prefill_compress_into_caches_beyond_the_infinity_cache(sqa, dtype, D, policy, units, P, b, blocked):
+    """Caches of 320 MiB and more have their rows stored non-temporally (launches that move 256 MiB read them so too): the same
+    rows, scores and positions as in a cache just below that size."""
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device=DEV).manual_seed(units)
+    L = 2
+    Ks, Vs = ([torch.randn(units, 1, P, D, device=DEV, generator=gen).to(tdt) for _ in range(L)] for _ in range(2))
+    Ss = [torch.rand(units, 1, P, device=DEV, generator=gen) for _ in range(L)]
+    limit = (320 << 20) // (L * 2 * D * Ks[0].element_size())          # slots of a layer
+    got = []
+    for big in (False, True):
+        if blocked:
+            own = units * ((b + 15) // 16)
+            caches = sqa.LayerCaches([b] * L, [b] * L, units, 1, D, tdt, DEV, True, blocked=True,
+                                     spare_blocks=(limit // 16 if big else min(limit // 16 - 1, own + 3)) - own)
+        else:
+            caches = sqa.LayerCaches([b] * L, [(limit + units - 1) // units if big else P] * L, units, 1, D, tdt, DEV, True)
+        sqa.prefill_compress_layers(Ks, Vs, Ss, policy, 4, caches)
+        n = min(P, b)
+        rows = [unit_kv(caches, l, u, 0, n) for l in range(L) for u in (0, units // 2, units - 1)]
+        got.append((rows, [[x[l].view(units, -1)[:, :n].cpu() for x in (caches.pos, caches.score)] for l in range(L)],
+                    [s.cpu() for s in caches.state]))
+    for (k0, v0), (k1, v1) in zip(got[0][0], got[1][0]):
+        assert np.array_equal(k0, k1) and np.array_equal(v0, v1)
+    for x, y in zip(got[0][1], got[1][1]):
+        assert torch.equal(x[0], y[0]) and torch.equal(x[1], y[1])
+    for x, y in zip(got[0][2], got[1][2]):
+        assert torch.equal(x, y)
+    keep = O.select_keep(np.arange(P), Ss[1][units - 1, 0].cpu().numpy(), b, policy)
+    assert np.array_equal(np.sort(got[1][1][1][0][units - 1].numpy()), np.sort(keep))
+    assert np.array_equal(got[1][0][-1][0], np64(Ks[1][units - 1, 0])[got[1][1][1][0][units - 1].numpy()])
 
 
 def test_prefill_compress_layers_matches_single_layer_calls(sqa):
