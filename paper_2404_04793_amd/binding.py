@@ -7,7 +7,9 @@ if the library is missing, importing this module raises.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
+from array import array
 from typing import List, Optional, Sequence, Tuple
 
 import torch
@@ -92,17 +94,16 @@ _lib.sqa_prefill_compress_layers.restype = _i
 _lib.sqa_prefill_compress_layers.argtypes = [C.POINTER(_vp), C.POINTER(_vp), _i, C.POINTER(_vp), _i, _i, _i, _i, _i, _i,
                                              _LCp, _i, _vp]
 _lib.sqa_prefill_compress_layers_ex.restype = _i
-_lib.sqa_prefill_compress_layers_ex.argtypes = [C.POINTER(_vp), C.POINTER(_vp), _i, C.POINTER(_vp), _i, _i, _i, _i, _i,
-                                                _i, _LCp, _i, _vp, _BOp]
+_lib.sqa_prefill_compress_layers_ex.argtypes = [_vp, _vp, _i, _vp, _i, _i, _i, _i, _i, _i, _vp, _i, _vp, _BOp]
 _lib.sqa_decode_workspace_bytes.restype = _sz
 _lib.sqa_decode_workspace_bytes.argtypes = [_LCp, _i, _i, _i, _i, _i, _i]
 _lib.sqa_decode_workspace_init.restype = _i
 _lib.sqa_decode_workspace_init.argtypes = [_vp, _sz, _vp]
 _lib.sqa_decode_step.restype = _i
-_lib.sqa_decode_step.argtypes = [_vp, _vp, _vp, _i, _i, _i, _i, _i, C.c_int32, _i, _i, _LCp, _vp, _i,
+_lib.sqa_decode_step.argtypes = [_vp, _vp, _vp, _i, _i, _i, _i, _i, C.c_int32, _i, _i, _vp, _vp, _i,
                                  _vp, _vp, _sz, _vp]
 _lib.sqa_decode_step_ex.restype = _i
-_lib.sqa_decode_step_ex.argtypes = [_vp, _vp, _vp, _i, _i, _i, _i, _i, C.c_int32, _i, _i, _LCp, _vp, _i,
+_lib.sqa_decode_step_ex.argtypes = [_vp, _vp, _vp, _i, _i, _i, _i, _i, C.c_int32, _i, _i, _vp, _vp, _i,
                                     _vp, _vp, _sz, _vp, _BOp]
 _lib.sqa_decode_step_static.restype = _i
 _lib.sqa_decode_step_static.argtypes = [_vp, _vp, _vp, _i, _i, _i, _i, _i, C.c_int32, _i, _i, _LCp, _vp, _i,
@@ -126,12 +127,12 @@ _lib.sqa_block_pool_take.argtypes = [_vp, C.c_int32, C.POINTER(C.c_int32)]
 _lib.sqa_block_pool_give.argtypes = [_vp, C.POINTER(C.c_int32), C.c_int32]
 
 
+_DT = {torch.float32: SQA_F32, torch.bfloat16: SQA_BF16}
+_LC_BYTES = C.sizeof(LayerCacheStruct)
+
+
 def _dt(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return SQA_F32
-    if t.dtype == torch.bfloat16:
-        return SQA_BF16
-    return -1
+    return _DT.get(t.dtype, -1)
 
 
 def _ptr(t: Optional[torch.Tensor]):
@@ -141,12 +142,13 @@ def _ptr(t: Optional[torch.Tensor]):
 # The current stream's handle without a torch.cuda.Stream object around it: 0.3 instead of 2.8 us, a fifth of what the
 # host spends on a small call (torch's own compiled code asks for it this way; a build of torch without it: the long way).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_get_device = getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device)
 
 
 def _stream():
     if _raw_stream is None:
         return torch.cuda.current_stream().cuda_stream
-    return _raw_stream(torch.cuda.current_device())
+    return _raw_stream(_get_device())
 
 
 def batch_opts(prompt_len: Optional[torch.Tensor] = None, budget_seq: Optional[torch.Tensor] = None,
@@ -157,6 +159,10 @@ def batch_opts(prompt_len: Optional[torch.Tensor] = None, budget_seq: Optional[t
         if t is not None and (t.dtype != torch.int32 or not t.is_contiguous()):
             raise TypeError("per-sequence arrays are contiguous int32 tensors")
     return BatchOptsStruct(_ptr(prompt_len), _ptr(budget_seq), _ptr(new_pos_seq), _ptr(status), ORDER[order])
+
+
+# (a pure function of the shape; asked for anew it is 1 to 5 us of host arithmetic, a small call's 12 in all)
+_scores_workspace_bytes = functools.lru_cache(maxsize=256)(_lib.sqa_prefill_scores_workspace_bytes)
 
 
 def _opts(o: Optional[BatchOptsStruct]):
@@ -176,8 +182,8 @@ def layer_importance(h_in: torch.Tensor, h_out: torch.Tensor, cos_out: Optional[
     L, T, d = h_in.shape
     if cos_out is None:
         cos_out = torch.empty(L, dtype=torch.float32, device=h_in.device)
-    need = _lib.sqa_layer_importance_workspace_bytes(L, T, d)
     if workspace is None:
+        need = _lib.sqa_layer_importance_workspace_bytes(L, T, d)
         workspace = torch.empty(max(need, 8), dtype=torch.uint8, device=h_in.device)
     _check(_lib.sqa_layer_importance(_ptr(h_in), _ptr(h_out), _dt(h_in), L, T, d, _ptr(cos_out),
                                      _ptr(workspace), workspace.numel(), _stream()), "sqa_layer_importance")
@@ -192,8 +198,8 @@ def residual_add_importance(h_in: torch.Tensor, attn_out: torch.Tensor, h_out: t
     L, T, d = h_in.shape
     if cos_out is None:
         cos_out = torch.empty(L, dtype=torch.float32, device=h_in.device)
-    need = _lib.sqa_layer_importance_workspace_bytes(L, T, d)
     if workspace is None:
+        need = _lib.sqa_layer_importance_workspace_bytes(L, T, d)
         workspace = torch.empty(max(need, 8), dtype=torch.uint8, device=h_in.device)
     _check(_lib.sqa_residual_add_importance(_ptr(h_in), _ptr(attn_out), _ptr(h_out), _dt(h_in), L, T, d,
                                             _ptr(cos_out), _ptr(workspace), workspace.numel(), _stream()),
@@ -233,8 +239,7 @@ def prefill_scores(Q: torch.Tensor, K: torch.Tensor, scores_out: Optional[torch.
     Hkv = K.shape[1]
     if scores_out is None:
         scores_out = torch.empty(B, Hkv, P, dtype=torch.float32, device=Q.device)
-    need = _lib.sqa_prefill_scores_workspace_bytes(B, Hq, Hkv, P, D)
-    ws = torch.empty(max(need, 8), dtype=torch.uint8, device=Q.device)
+    ws = torch.empty(max(_scores_workspace_bytes(B, Hq, Hkv, P, D), 8), dtype=torch.uint8, device=Q.device)
     if row_lse is None:
         _check(_lib.sqa_prefill_scores_ex(_ptr(Q), _ptr(K), _dt(Q), B, Hq, Hkv, P, D, _ptr(scores_out), _ptr(ws),
                                           ws.numel(), _stream(), _opts(opts)), "sqa_prefill_scores")
@@ -433,6 +438,11 @@ def prefill_compress(K: torch.Tensor, V: torch.Tensor, attn_scores: Optional[tor
                                      n_sink, caches.struct_ptr(layer), _stream()), "sqa_prefill_compress")
 
 
+def _addresses(tensors: Sequence[torch.Tensor]) -> array:
+    """Their device addresses, one after the other (the caller keeps the array for the length of the call)."""
+    return array("Q", map(torch.Tensor.data_ptr, tensors))
+
+
 def prefill_compress_layers(K: Sequence[torch.Tensor], V: Sequence[torch.Tensor],
                             attn_scores: Optional[Sequence[Optional[torch.Tensor]]], policy: str, n_sink: int,
                             caches: LayerCaches, layer0: int = 0, opts: Optional[BatchOptsStruct] = None,
@@ -441,12 +451,12 @@ def prefill_compress_layers(K: Sequence[torch.Tensor], V: Sequence[torch.Tensor]
     table: sqa_layer_cache records to use instead of the caches' own (LayerCaches.sequence_table)."""
     n = len(K)
     B, Hkv, P, D = K[0].shape
-    Ks = (_vp * n)(*[t.data_ptr() for t in K])
-    Vs = (_vp * n)(*[t.data_ptr() for t in V])
-    Ss = None if attn_scores is None or attn_scores[0] is None else (_vp * n)(*[t.data_ptr() for t in attn_scores])
-    layers = caches.struct_ptr(layer0) if table is None else C.cast(C.byref(table, layer0 * C.sizeof(LayerCacheStruct)), _LCp)
-    _check(_lib.sqa_prefill_compress_layers_ex(Ks, Vs, _dt(K[0]), Ss, B, Hkv, P, D, POLICY[policy], n_sink,
-                                               layers, n, _stream(), _opts(opts)),
+    Ks, Vs = _addresses(K), _addresses(V)
+    Ss = None if attn_scores is None or attn_scores[0] is None else _addresses(attn_scores)
+    layers = C.addressof(caches.table if table is None else table) + layer0 * _LC_BYTES
+    _check(_lib.sqa_prefill_compress_layers_ex(Ks.buffer_info()[0], Vs.buffer_info()[0], _dt(K[0]),
+                                               None if Ss is None else Ss.buffer_info()[0], B, Hkv, P, D, POLICY[policy],
+                                               n_sink, layers, n, _stream(), _opts(opts)),
            "sqa_prefill_compress_layers")
 
 
@@ -468,20 +478,18 @@ def decode_step(q: torch.Tensor, k_new: torch.Tensor, v_new: torch.Tensor, new_p
                 layer0: int = 0, n_layers: Optional[int] = None, use_dev_table: bool = True,
                 opts: Optional[BatchOptsStruct] = None) -> torch.Tensor:
     """q [n_layers, B, Hq, D], k_new / v_new [n_layers, B, Hkv, D] -> out like q."""
-    n_layers = caches.L - layer0 if n_layers is None else n_layers
-    B, Hq, D = q.shape[-3:]
-    Hkv = k_new.shape[-2]
+    # (kept short: in a model that calls this once per layer, the host's part is as long as a small layer's kernel)
+    shape, at = q.shape, layer0 * _LC_BYTES
+    args = (q.data_ptr(), k_new.data_ptr(), _ptr(v_new), _DT.get(q.dtype, -1), shape[-3], shape[-2], k_new.shape[-2], shape[-1],
+            int(new_pos), POLICY[policy], n_sink, C.addressof(caches.table) + at,
+            caches.table_dev.data_ptr() + at if use_dev_table else None, caches.L - layer0 if n_layers is None else n_layers,
+            _ptr(out), workspace.data_ptr(), workspace.numel(), _stream())
     if opts is None:
-        _check(_lib.sqa_decode_step(_ptr(q), _ptr(k_new), _ptr(v_new), _dt(q), B, Hq, Hkv, D, int(new_pos),
-                                    POLICY[policy], n_sink, caches.struct_ptr(layer0),
-                                    caches.dev_ptr(layer0) if use_dev_table else None, n_layers, _ptr(out),
-                                    _ptr(workspace), workspace.numel(), _stream()), "sqa_decode_step")
+        code, where = _lib.sqa_decode_step(*args), "sqa_decode_step"
     else:
-        _check(_lib.sqa_decode_step_ex(_ptr(q), _ptr(k_new), _ptr(v_new), _dt(q), B, Hq, Hkv, D, int(new_pos),
-                                       POLICY[policy], n_sink, caches.struct_ptr(layer0),
-                                       caches.dev_ptr(layer0) if use_dev_table else None, n_layers, _ptr(out),
-                                       _ptr(workspace), workspace.numel(), _stream(), C.byref(opts)),
-               "sqa_decode_step_ex")
+        code, where = _lib.sqa_decode_step_ex(*args, C.byref(opts)), "sqa_decode_step_ex"
+    if code != SQA_OK:
+        raise SqaError(code, where)
     return out
 
 

@@ -322,7 +322,8 @@ static sqa_status launch_importance(const void* h_in, const void* other, void* h
   const dim3 grid(nblk, n_layers, n_seq);
   // h_out is stored non-temporally where it is larger than the 256 MB Infinity Cache: nothing of it would be found
   // there again (16 layers of 4096 x 4096 bf16, 537 MB: 304 us, 285 so); below that plain stores are absorbed by the
-  // cache and found by the next kernel (16384 x 4096, 134 MB: 68 us, 74 so).
+  // cache and found by the next kernel (16384 x 4096, 134 MB: 68 us, 74 so.  From inputs that lie in memory 79 and 75, but
+  // with a norm of h_out after it 132 and 151).
   const bool nt = fuse && (int64_t)n_layers * n_tokens * hidden * (dt == SQA_F32 ? 4 : 2) >= ((int64_t)256 << 20);
   auto launch = [&](auto type, auto fused, auto streamed) {
     using T = decltype(type);
