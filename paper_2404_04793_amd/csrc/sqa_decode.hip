@@ -354,14 +354,32 @@ template <typename T, int D, int G, bool H2O> constexpr bool exact_mfma() { retu
 template <typename T, int D, int G, bool H2O, bool MF, bool PG>
 __global__ __launch_bounds__(kDecThreads, MF ? kMfWavesPerSimd : 1) void decode_unit_kernel(const DecodeArgs a) {
   constexpr int NW = kDecWaves;
+  constexpr bool NTR = false;     // rows of step 4 with ordinary stores
 #include "sqa_decode_unit.inc"
 }
 // The same with more than 4 waves per workgroup (WIDE in the body), for calls that have no more work items than CUs.
 template <typename T, int D, int G, bool H2O, bool PG, int NW>
 __global__ __launch_bounds__(NW * SQA_WAVE) void decode_wide_kernel(const DecodeArgs a) {
-  constexpr bool MF = use_mfma<T, D, G>();
+  constexpr bool MF = use_mfma<T, D, G>(), NTR = false;
 #include "sqa_decode_unit.inc"
 }
+// decode_unit_kernel for MHA calls over very large caches: the moved and the new K/V rows of step 4 are stored
+// non-temporally.  A step writes each unit's rows once and reads them a whole pass later, when a cache of this size has long
+// pushed them out; until then the dirty lines are in the way of the rows that stream through.  A kernel of its own, because
+// a switch inside costs the others: with it, 32 layers of 2048 units of 20 to 40 slots 160 -> 163 us.
+template <typename T, int D, bool H2O, bool PG>
+__global__ __launch_bounds__(kDecThreads) void decode_large_kernel(const DecodeArgs a) {
+  constexpr int NW = kDecWaves, G = 1;
+  constexpr bool MF = false, NTR = true;
+#include "sqa_decode_unit.inc"
+}
+// From how many bytes of K and V (the call's layers together, at their budgets): measured per call, plain -> non-temporal,
+// bf16, H2O, D = 128 unless said otherwise: 1.7 GB of 40-slot units 313 -> 319 us, 3.4 GB (80 slots) 599 -> 607, 4.2 GB
+// 603 -> 605, 6.7 GB 949 -> 952 / 10 GB 1449 -> 1427, 11 GB (160 slots) 1953 -> 1920, 13.4 GB (40 slots) 3474 -> 3353,
+// 15 GB (35 to 571 slots) 2233 -> 2170, 24 GB (571 slots) 4153 -> 4080; D = 64, 11 GB 2072 -> 2016; fp32, 12 GB 2054 -> 2031.
+// What is written counts against what is read: long units gain little (1024 slots 3572 -> 3562, 143 to 2271 slots
+// 1768 -> 1772), 2 and more heads per KV head nothing (2061 -> 2061).
+constexpr int64_t kLargeBytes = (int64_t)8 << 30;
 
 typedef void (*decode_fn)(const DecodeArgs);
 
@@ -375,27 +393,27 @@ template <typename T, int D, bool H2O, bool PG> decode_fn pick_wide(int g) {
   }
   return nullptr;
 }
-template <typename T, int D, bool H2O, bool PG> decode_fn pick_g(int g, int waves) {
+template <typename T, int D, bool H2O, bool PG> decode_fn pick_g(int g, int waves, bool large) {
   if (waves > kDecWaves) return pick_wide<T, D, H2O, PG>(g);
   switch (g) {
-    case 1: return decode_unit_kernel<T, D, 1, H2O, false, PG>;
+    case 1: return large ? decode_large_kernel<T, D, H2O, PG> : decode_unit_kernel<T, D, 1, H2O, false, PG>;
     case 2: return decode_unit_kernel<T, D, 2, H2O, false, PG>;
     case 4: return decode_unit_kernel<T, D, 4, H2O, use_mfma<T, D, 4>(), PG>;
     case 8: return decode_unit_kernel<T, D, 8, H2O, use_mfma<T, D, 8>(), PG>;
   }
   return nullptr;
 }
-template <typename T, bool H2O, bool PG> decode_fn pick_d(int d, int g, int waves) {
-  if (d == 64) return pick_g<T, 64, H2O, PG>(g, waves);
-  if (d == 128) return pick_g<T, 128, H2O, PG>(g, waves);
+template <typename T, bool H2O, bool PG> decode_fn pick_d(int d, int g, int waves, bool large) {
+  if (d == 64) return pick_g<T, 64, H2O, PG>(g, waves, large);
+  if (d == 128) return pick_g<T, 128, H2O, PG>(g, waves, large);
   return nullptr;
 }
-template <typename T, bool H2O> decode_fn pick_p(int d, int g, bool paged, int waves) {
-  return paged ? pick_d<T, H2O, true>(d, g, waves) : pick_d<T, H2O, false>(d, g, waves);
+template <typename T, bool H2O> decode_fn pick_p(int d, int g, bool paged, int waves, bool large) {
+  return paged ? pick_d<T, H2O, true>(d, g, waves, large) : pick_d<T, H2O, false>(d, g, waves, large);
 }
-static decode_fn pick(sqa_dtype dt, int d, int g, bool h2o, bool paged, int waves = kDecWaves) {
-  if (dt == SQA_F32) return h2o ? pick_p<float, true>(d, g, paged, waves) : pick_p<float, false>(d, g, paged, waves);
-  return h2o ? pick_p<bf16_t, true>(d, g, paged, waves) : pick_p<bf16_t, false>(d, g, paged, waves);
+static decode_fn pick(sqa_dtype dt, int d, int g, bool h2o, bool paged, int waves = kDecWaves, bool large = false) {
+  if (dt == SQA_F32) return h2o ? pick_p<float, true>(d, g, paged, waves, large) : pick_p<float, false>(d, g, paged, waves, large);
+  return h2o ? pick_p<bf16_t, true>(d, g, paged, waves, large) : pick_p<bf16_t, false>(d, g, paged, waves, large);
 }
 
 constexpr size_t kStatusBytes = 256;
@@ -767,7 +785,10 @@ static sqa_status decode_launch(sqa_dtype dt, const DecodePlan& plan, size_t lds
                                 int B, int Hq, int Hkv, int D, int32_t new_pos, sqa_policy policy, int n_sink,
                                 const sqa_layer_cache* layers, const sqa_layer_cache* layers_dev, int n_layers,
                                 void* out, hipStream_t st, const sqa_batch_opts* opts) {
-  const decode_fn fn = pick(dt, D, Hq / Hkv, policy == SQA_H2O, layers[0].block_table != nullptr, plan.waves);
+  int64_t kv_bytes = 0;
+  for (int i = 0; i < n_layers; ++i)
+    kv_bytes += (int64_t)B * Hkv * (layers[i].budget < layers[i].capacity ? layers[i].budget : layers[i].capacity) * 2 * D * (dt == SQA_F32 ? 4 : 2);
+  const decode_fn fn = pick(dt, D, Hq / Hkv, policy == SQA_H2O, layers[0].block_table != nullptr, plan.waves, kv_bytes >= kLargeBytes);
   if (lds > 64 * 1024) SQA_HIP_CHECK(allow_dynamic_lds(reinterpret_cast<const void*>(fn), lds));
   DecodeArgs a;
   a.q = q; a.k_new = k_new; a.v_new = v_new; a.out = out;
