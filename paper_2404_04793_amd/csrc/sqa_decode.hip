@@ -374,12 +374,12 @@ __global__ __launch_bounds__(kDecThreads) void decode_large_kernel(const DecodeA
 #include "sqa_decode_unit.inc"
 }
 // From how many bytes of K and V (the call's layers together, at their budgets): measured per call, plain -> non-temporal,
-// bf16, H2O, D = 128 unless said otherwise: 1.7 GB of 40-slot units 313 -> 319 us, 3.4 GB (80 slots) 599 -> 607, 4.2 GB
-// 603 -> 605, 6.7 GB 949 -> 952 / 10 GB 1449 -> 1427, 11 GB (160 slots) 1953 -> 1920, 13.4 GB (40 slots) 3474 -> 3353,
-// 15 GB (35 to 571 slots) 2233 -> 2170, 24 GB (571 slots) 4153 -> 4080; D = 64, 11 GB 2072 -> 2016; fp32, 12 GB 2054 -> 2031.
-// What is written counts against what is read: long units gain little (1024 slots 3572 -> 3562, 143 to 2271 slots
-// 1768 -> 1772), 2 and more heads per KV head nothing (2061 -> 2061).
-constexpr int64_t kLargeBytes = (int64_t)8 << 30;
+// bf16, H2O, D = 128 unless said otherwise: 1.7 GB of 40-slot units 313 -> 319 us, 3.4 GB (80 slots) 599 -> 607, 5.3 GB (35 to
+// 571 slots) 949 -> 952, 6.7 GB (160 slots) 1173 -> 1174 / 8.0 GB (35 to 571) 1449 -> 1427, 10.9 GB (160 slots) 1953 -> 1920,
+// 12 GB (35 to 571) 2233 -> 2170, 16.8 GB (40 slots) 3474 -> 3353, 24 GB (571 slots) 4153 -> 4080; D = 64, 10.9 GB 2072 -> 2016;
+// fp32, 11.7 GB 2054 -> 2031.  What is written counts against what is read: long units gain little (1024 slots 3572 -> 3562,
+// 143 to 2271 slots 1768 -> 1772), 2 and more heads per KV head nothing (2061 -> 2061).
+constexpr int64_t kLargeBytes = (int64_t)7 << 30;
 
 typedef void (*decode_fn)(const DecodeArgs);
 
