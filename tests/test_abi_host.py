@@ -330,3 +330,44 @@ int main() {
         assert parts[0] == "0"
         got = [tuple(int(v) for v in x.split(":")) for x in parts[1:]]
         assert [b for b, _ in got] == want[0] and [g for _, g in got] == want[1]
+
+
+def test_compression_lists_of_another_length(monkeypatch):
+    """The library reads len(K) addresses from each of the three lists, and as many records of the table.  A shorter list
+    reaches it filled up with NULLs (which it refuses where it needs them), never with what lies behind the list; a longer
+    one, and layers outside the table, do not reach it."""
+    import torch
+    monkeypatch.setattr(sqa, "_stream", lambda: None)
+    caches = sqa.LayerCaches([8] * 4, [8] * 4, 1, 1, 64, torch.float32, "cpu", True)
+    rows, scores = [torch.zeros(1, 1, 12, 64) for _ in range(8)], [torch.zeros(1, 1, 12) for _ in range(4)]
+    call = lambda k, v, s, policy="h2o", **kw: sqa.prefill_compress_layers(rows[:k], rows[4:4 + v], s, policy, 4, caches, **kw)
+    for k, v, s, policy in [(3, 1, scores[:3], "h2o"), (3, 2, None, "sliding"), (1, 0, None, "sliding"), (3, 3, scores[:1], "h2o")]:
+        with pytest.raises(sqa.SqaError) as e:
+            call(k, v, s, policy)
+        assert e.value.code == 1
+    seen = []
+
+    def library(K, V, dt, S, B, Hkv, P, D, policy, n_sink, layers, n, stream, opts):
+        read = lambda a: None if a is None else list((C.c_uint64 * n).from_address(a))
+        seen.append((read(K), read(V), read(S), layers, n))
+        return 0
+    monkeypatch.setattr(sqa._lib, "sqa_prefill_compress_layers_ex", library)
+    one = caches.sequence_table(0)
+    for k, v, s in [(3, 4, scores[:3]), (3, 3, scores), (2, 3, scores[:3])]:
+        with pytest.raises(IndexError):
+            call(k, v, s)
+    for k, kw in [(4, dict(layer0=1)), (1, dict(layer0=4)), (1, dict(layer0=-1)), (2, dict(layer0=3, table=one))]:
+        with pytest.raises(IndexError):
+            call(k, k, scores[:k], **kw)
+    with pytest.raises(AttributeError):
+        call(2, 2, [scores[0], None])
+    assert not seen
+    at = lambda ts, n: [t.data_ptr() for t in ts] + [0] * (n - len(ts))
+    call(3, 3, scores[1:], layer0=1)
+    call(4, 4, None, table=one)
+    call(1, 1, [None], table=one[2])                      # (a record alone)
+    call(4, 1, scores[:2], "sliding")
+    table = C.addressof(caches.table)
+    assert seen[0] == (at(rows[:3], 3), at(rows[4:7], 3), at(scores[1:], 3), table + C.sizeof(sqa.LayerCacheStruct), 3)
+    assert seen[1] == (at(rows[:4], 4), at(rows[4:], 4), None, C.addressof(one), 4) and seen[2][2] is None and seen[2][4] == 1
+    assert seen[3] == (at(rows[:4], 4), at(rows[4:5], 4), at(scores[:2], 4), table, 4)
