@@ -23,6 +23,11 @@ namespace sqa {
 constexpr int kImpThreads = 256;
 constexpr int kImpWaves = kImpThreads / SQA_WAVE;
 constexpr int kImpMaxBlocks = 1024;   // partial sums per layer
+// A workgroup that has at most 3 turns takes them all and needs no second kernel, as long as what it does alone is short: 16-byte
+// pieces of a row times further turns.  One layer, us on the device (replayed graphs), two kernels and one: 5 rows of
+// 4096 bf16 (512) 3.9 and 3.0, 12 of 2048 (512) 3.6 and 3.4 / 12 of 4096 (1024) 3.9 and 6.2, 12 of 8192 fp32 (4096) 8.6 and
+// 17.5, 12 of 16384 (8192) 13.5 and 32.1; back to back from the host, which two launches hold up for 6.8, up to 512 4.0 to 4.8.
+constexpr int kImpOnePieces = 512;
 
 template <typename T> struct Dots;
 template <> struct Dots<float> {
@@ -309,11 +314,11 @@ static sqa_status launch_importance(const void* h_in, const void* other, void* h
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int pieces = hidden / (dt == SQA_F32 ? 4 : 8);
   const int rows = pieces <= 32 ? 8 : (pieces <= 64 ? 4 : 1);      // of a wave at a time
-  // (several sequences, whose lengths are not known here: twice what the average one needs; up to 3 turns of a workgroup: one,
+  // (several sequences, whose lengths are not known here: twice what the average one needs; up to 3 turns of a workgroup, if short: one,
   // which needs no second kernel: 23 layers of 20 rows of 256 bf16 9.2 -> 6.0 us)
   const int64_t share = n_seq == 1 ? n_tokens : (2 * n_tokens + n_seq - 1) / n_seq;
   int nblk = imp_blocks((share + rows - 1) / rows);
-  nblk = nblk <= 3 ? 1 : nblk;
+  nblk = nblk <= 3 && (nblk - 1) * pieces <= kImpOnePieces ? 1 : nblk;
   ImpArgs a;
   a.h_in = h_in; a.other = other; a.h_out_w = h_out_w;
   a.n_tokens = n_tokens; a.hidden = hidden; a.seq_start = seq_start;
