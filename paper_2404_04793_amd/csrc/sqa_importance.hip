@@ -2,9 +2,9 @@
 // equation of Sec. 3.  A pure streaming reduction (each hidden-state element is
 // read once), so the only roofline is HBM bandwidth.
 //
-// Mapping: grid = (blocks per layer, layers, sequences); a workgroup has 4 waves; a wave
+// Mapping: grid = (blocks per layer, layers); a workgroup has 4 waves; a wave
 // owns whole token rows (row = wave id, stepping by the number of waves of the
-// layer) and its 64 lanes read the row in 16-byte pieces, 1 KiB per wave load.
+// layer; several sequences: see imp_share) and its 64 lanes read the row in 16-byte pieces, 1 KiB per wave load.
 // The three dot products accumulate in fp32 per lane, are summed over the wave,
 // and lane 0 adds the row's cosine to a per-wave fp64 sum.  Partial sums go to
 // the workspace and a second tiny kernel adds them in a fixed order: no atomics,
@@ -23,6 +23,7 @@ namespace sqa {
 constexpr int kImpThreads = 256;
 constexpr int kImpWaves = kImpThreads / SQA_WAVE;
 constexpr int kImpMaxBlocks = 1024;   // partial sums per layer
+constexpr int kImpMaxPieces = 2 * kImpMaxBlocks;      // the same of several sequences (the workspace holds kImpMaxBlocks for each)
 // A workgroup that has at most 3 turns takes them all and needs no second kernel, as long as what it does alone is short: 16-byte
 // pieces of a row times further turns.  One layer, us on the device (replayed graphs), two kernels and one: 5 rows of
 // 4096 bf16 (512) 3.9 and 3.0, 12 of 2048 (512) 3.6 and 3.4 / 12 of 4096 (1024) 3.9 and 6.2, 12 of 8192 fp32 (4096) 8.6 and
@@ -72,10 +73,13 @@ struct ImpArgs {
   void* h_out_w;                 // may be h_in or other
   int64_t n_tokens;
   int hidden;
-  const int32_t* seq_start;      // [gridDim.z + 1] or NULL
-  double* partial;               // [layers][gridDim.z][gridDim.x]
-  float* cos_out;
+  const int32_t* seq_start;      // [n_seq + 1] or NULL
+  int n_seq;
+  int piece;                     // see imp_share
+  double* partial;               // [layers][gridDim.x]
+  float* cos_out;                // [layers][n_seq]
 };
+enum { kImpAll = -2, kImpWhole = -1 };   // ImpArgs::piece: a layer's rows in turns; a sequence per workgroup; else log2 of a piece's rows
 
 template <int CTRL> __device__ __forceinline__ float imp_dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
@@ -97,32 +101,84 @@ template <int W> __device__ __forceinline__ float lanes_sum(float v) {
   return v;
 }
 
-__device__ __forceinline__ int64_t imp_rows(const ImpArgs& a, int seq, int64_t& lo) {
+// rows [lo, hi) of a sequence: all of the layer's unless the tokens are segmented
+__device__ __forceinline__ void imp_rows(const ImpArgs& a, int seq, int64_t& lo, int64_t& hi) {
   lo = 0;
-  int64_t hi = a.n_tokens;            // all of the layer's rows unless the tokens are segmented
+  hi = a.n_tokens;
   if (a.seq_start) {
     lo = a.seq_start[seq];
     hi = a.seq_start[seq + 1];
     lo = lo < 0 ? 0 : lo;
     hi = hi > a.n_tokens ? a.n_tokens : hi;
   }
-  return hi;
+}
+
+// Which rows a workgroup takes.  One sequence: all of them, in turns with the layer's other workgroups.  Several, together no
+// more than one workgroup is given: a workgroup each.  Otherwise the layer's rows are cut into pieces of 2^piece, and again
+// where a sequence ends, so that the work is shared out evenly whatever the lengths: the part of sequence s in piece j belongs
+// to workgroup j + s, which grows by at least one from each part to the next.  Every wave finds the s of its workgroup from
+// the sequences' starts, 64 at a time (one round for up to 63 sequences).  us per call on the device, one layer, rows of 4096
+// bf16, with 1024 workgroups for each sequence / with as many as twice the average length needs / so: 4096 rows and 32 of one
+// row 23.2 / 34.0 / 15.4; 4000 and 1000 of one 326 / 1660 / 18.6; 8192 and 100 of 20 60 / 79 / 32; 16 of 1000 45.4 / 44.4 / 45.6,
+// 1000 of 10 361 / 29 / 31; 11 layers, 9 of 1000 rows of 256 56.2 / 20.0 / 20.4.  (Where a workgroup per sequence was enough by the
+// average length, the second kernel comes on top: 64 of 30 rows of 256 14.8 / 3.6 / 6.1.)
+struct ImpShare {
+  int64_t row, hi, step;          // of a wave with `rows` rows at a time
+  int seq;
+};
+template <bool SEQS /*there may be several*/> __device__ __forceinline__ ImpShare imp_share(const ImpArgs& a, int wave, int rows) {
+  ImpShare r;
+  int64_t lo;
+  r.seq = 0;
+  r.step = (int64_t)kImpWaves * rows;
+  int64_t first = 0;
+  if (!SEQS || a.piece == kImpAll) {
+    first = blockIdx.x * r.step;
+    r.step *= gridDim.x;
+    imp_rows(a, 0, lo, r.hi);
+  } else if (a.piece == kImpWhole) {
+    r.seq = blockIdx.x;
+    imp_rows(a, r.seq, lo, r.hi);
+  } else {
+    const int w = blockIdx.x, lane = threadIdx.x & (SQA_WAVE - 1);
+    int base = 0, n = a.n_seq, at = 0;
+    auto count = [&](int every) {                 // samples of base, base + every, .. below base + n that are at w or before
+      at = a.seq_start[base + min(lane * every, n)];
+      return __popcll(__ballot(lane * every < n && (max(at, 0) >> a.piece) + base + lane * every <= w));
+    };
+    while (n >= SQA_WAVE) {
+      const int every = (n + SQA_WAVE - 1) / SQA_WAVE, skip = max(count(every) - 1, 0) * every;
+      base += skip;
+      n = min(every, n - skip);
+    }
+    const int s = max(count(1) - 1, 0);           // (before the first sequence: its part of that piece is empty)
+    r.seq = base + s;
+    lo = max(__builtin_amdgcn_readlane(at, s), 0);
+    r.hi = min((int64_t)__builtin_amdgcn_readlane(at, s + 1), a.n_tokens);
+    const int64_t from = (int64_t)(w - r.seq) << a.piece;
+    lo = max(lo, from);
+    r.hi = min(r.hi, from + ((int64_t)1 << a.piece));
+  }
+  r.row = lo + first + wave * rows;
+  return r;
 }
 
 // the cosine of a (layer, sequence) from the sum over its rows
-__device__ __forceinline__ void imp_store(const ImpArgs& a, int64_t item, int seq, double sum) {
-  int64_t lo;
-  const int64_t rows = imp_rows(a, seq, lo) - lo;
+__device__ __forceinline__ void imp_store(const ImpArgs& a, int64_t item, int64_t rows, double sum) {
   a.cos_out[item] = rows > 0 ? (float)(sum / (double)rows) : 0.f;
 }
 
-// a workgroup's sum, or (if there is only one) the result
-__device__ __forceinline__ void imp_put(const ImpArgs& a, const double* waves) {
+// a workgroup's sum, or (if it had all rows of the sequence) the result
+__device__ __forceinline__ void imp_put(const ImpArgs& a, int seq, const double* waves) {
   double s = 0.0;
   for (int w = 0; w < kImpWaves; ++w) s += waves[w];
-  const int64_t item = (int64_t)blockIdx.y * gridDim.z + blockIdx.z;
-  if (gridDim.x == 1) imp_store(a, item, blockIdx.z, s);
-  else a.partial[item * gridDim.x + blockIdx.x] = s;
+  if (a.piece == kImpWhole) {
+    int64_t lo, hi;
+    imp_rows(a, seq, lo, hi);
+    imp_store(a, (int64_t)blockIdx.y * a.n_seq + seq, hi - lo, s);
+  } else {
+    a.partial[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
+  }
 }
 
 // FUSE = false: h_out is read.  FUSE = true: `other` is attn_out and h_out is written (NT: non-temporally).
@@ -137,13 +193,10 @@ __global__ __launch_bounds__(kImpThreads) void importance_partial_kernel(const I
   const char* A = static_cast<const char*>(args.h_in) + layer * layer_bytes;
   const char* Bp = static_cast<const char*>(args.other) + layer * layer_bytes;
   char* Wp = FUSE ? static_cast<char*>(args.h_out_w) + layer * layer_bytes : nullptr;
-  const int64_t stride = (int64_t)gridDim.x * kImpWaves;
-
-  int64_t row_lo;
-  const int64_t row_hi = imp_rows(args, blockIdx.z, row_lo);
+  const ImpShare mine = imp_share<!FUSE>(args, wave, 1);
   auto put = [](char* p, const uint4& v) { if constexpr (NT) st16_nt(p, v); else st16(p, v); };
   double wave_cos = 0.0;
-  for (int64_t row = row_lo + (int64_t)blockIdx.x * kImpWaves + wave; row < row_hi; row += stride) {
+  for (int64_t row = mine.row; row < mine.hi; row += mine.step) {
     const char* a = A + row * row_bytes;
     const char* b = Bp + row * row_bytes;
     char* w = FUSE ? Wp + row * row_bytes : nullptr;
@@ -191,7 +244,7 @@ __global__ __launch_bounds__(kImpThreads) void importance_partial_kernel(const I
   __shared__ double s_part[kImpWaves];
   if (lane == 0) s_part[wave] = wave_cos;
   __syncthreads();
-  if (threadIdx.x == 0) imp_put(args, s_part);
+  if (threadIdx.x == 0) imp_put(args, mine.seq, s_part);
 }
 
 // Rows of up to 1 KiB: W lanes share a row and hold one 16-byte piece of it, a wave takes 64 / W rows side by side and 4 such
@@ -210,8 +263,7 @@ __global__ __launch_bounds__(kImpThreads) void importance_short_rows_kernel(cons
   const char* A = static_cast<const char*>(args.h_in) + blockIdx.y * layer_bytes;
   const char* B = static_cast<const char*>(args.other) + blockIdx.y * layer_bytes;
   char* O = FUSE ? static_cast<char*>(args.h_out_w) + blockIdx.y * layer_bytes : nullptr;
-  int64_t row_lo;
-  const int64_t row_hi = imp_rows(args, blockIdx.z, row_lo);
+  const ImpShare mine = imp_share<!FUSE>(args, wave, ROWS);
   double cosines = 0.0;
   float k_ab = 0.f, k_aa = 0.f, k_bb = 0.f;      // the sums of the row that this lane keeps
   int kept = 0;                                  // rows kept per lane group
@@ -221,8 +273,8 @@ __global__ __launch_bounds__(kImpThreads) void importance_short_rows_kernel(cons
     k_ab = k_aa = k_bb = 0.f;
     kept = 0;
   };
-  for (int64_t row0 = row_lo + ((int64_t)blockIdx.x * kImpWaves + wave) * ROWS; row0 < row_hi; row0 += (int64_t)gridDim.x * kImpWaves * ROWS) {
-    const int there = (int)min(row_hi - row0, (int64_t)ROWS);      // rows of this turn
+  for (int64_t row0 = mine.row; row0 < mine.hi; row0 += mine.step) {
+    const int there = (int)min(mine.hi - row0, (int64_t)ROWS);      // rows of this turn
     uint4 x[4], y[4];
     uint32_t off[4];
 #pragma unroll
@@ -233,13 +285,13 @@ __global__ __launch_bounds__(kImpThreads) void importance_short_rows_kernel(cons
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const bool mine = i * SIDE + side < there && lw < chunks;
+      const bool own = i * SIDE + side < there && lw < chunks;
       if (FUSE) {
         y[i] = Residual<T>::add(x[i], y[i]);
         char* o = O + row0 * row_bytes + off[i];
-        if (mine) { if constexpr (NT) st16_nt(o, y[i]); else st16(o, y[i]); }
+        if (own) { if constexpr (NT) st16_nt(o, y[i]); else st16(o, y[i]); }
       }
-      if (!mine) x[i] = y[i] = make_uint4(0, 0, 0, 0);
+      if (!own) x[i] = y[i] = make_uint4(0, 0, 0, 0);
       float ab = 0.f, aa = 0.f, bb = 0.f;
       Dots<T>::acc(x[i], y[i], ab, aa, bb);
       ab = lanes_sum<W>(ab); aa = lanes_sum<W>(aa); bb = lanes_sum<W>(bb);
@@ -252,25 +304,34 @@ __global__ __launch_bounds__(kImpThreads) void importance_short_rows_kernel(cons
   cosines = wave_sum(cosines);
   if (lane == 0) s_part[wave] = cosines;
   __syncthreads();
-  if (threadIdx.x == 0) imp_put(args, s_part);
+  if (threadIdx.x == 0) imp_put(args, mine.seq, s_part);
 }
 
-// one workgroup per (layer, sequence): blockIdx.x = layer * n_seq + sequence.  All of its partial sums are requested
+// one workgroup per (sequence, layer).  All of its partial sums are requested
 // at once and added in a fixed order (one wave that took 16 turns for 1024 of them: 5.8 us; 16384 rows of 4096 bf16
 // in one layer, both kernels: 45.9 -> 42.3 us, inside the residual add 71.5 -> 68.0).  64 threads for up to 256.
 // (The last workgroup to arrive adding them instead was slower: its round trips -- stores acknowledged, arrivals counted, sums
 // fetched -- take longer than a launch: 2048 rows of 4096 13.4 -> 17.2, 300 8.8 -> 11.0.)
-__global__ __launch_bounds__(kImpThreads) void importance_final_kernel(
-    const ImpArgs a, int n_part, int n_seq) {
-  const int item = blockIdx.x;
+template <bool SEQS /*pieces of several sequences, see imp_share*/>
+__global__ __launch_bounds__(kImpThreads) void importance_final_kernel(const ImpArgs a, int per_layer /*partial sums*/) {
+  const int seq = SEQS ? blockIdx.x : 0, layer = blockIdx.y;
   const int lane = threadIdx.x & (SQA_WAVE - 1);
-  constexpr int N = 4;                            // >= n_part / threads
+  int64_t lo = 0, hi = 0;
+  int first = 0, n = per_layer;
+  if constexpr (SEQS) {
+    imp_rows(a, seq, lo, hi);
+    first = min((int)(lo >> a.piece) + seq, per_layer - 1);
+    n = hi > lo ? (int)(((hi - 1) >> a.piece) - (lo >> a.piece)) + 1 : 0;
+  }
+  constexpr int N = SEQS ? 8 : 4;                 // >= n / threads
   double v[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const int at = threadIdx.x + i * blockDim.x;
-    v[i] = a.partial[(int64_t)item * n_part + min(at, n_part - 1)];
-    v[i] = at < n_part ? v[i] : 0.0;
+    v[i] = 0.0;
+    if (SEQS && i >= N / 2 && n <= (int)blockDim.x * (N / 2)) continue;
+    v[i] = a.partial[(int64_t)layer * per_layer + first + max(min(at, n - 1), 0)];
+    v[i] = at < n ? v[i] : 0.0;
   }
   double s = 0.0;
 #pragma unroll
@@ -283,7 +344,10 @@ __global__ __launch_bounds__(kImpThreads) void importance_final_kernel(
     s = 0.0;
     for (int w = 0; w < kImpWaves; ++w) s += s_wave[w];
   }
-  if (threadIdx.x == 0) imp_store(a, item, item % n_seq, s);
+  if (threadIdx.x == 0) {
+    if (!SEQS) imp_rows(a, 0, lo, hi);
+    imp_store(a, (int64_t)layer * a.n_seq + seq, hi - lo, s);
+  }
 }
 
 static int imp_blocks(int64_t n_tokens) {
@@ -314,17 +378,22 @@ static sqa_status launch_importance(const void* h_in, const void* other, void* h
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int pieces = hidden / (dt == SQA_F32 ? 4 : 8);
   const int rows = pieces <= 32 ? 8 : (pieces <= 64 ? 4 : 1);      // of a wave at a time
-  // (several sequences, whose lengths are not known here: twice what the average one needs; up to 3 turns of a workgroup, if short: one,
-  // which needs no second kernel: 23 layers of 20 rows of 256 bf16 9.2 -> 6.0 us)
-  const int64_t share = n_seq == 1 ? n_tokens : (2 * n_tokens + n_seq - 1) / n_seq;
-  int nblk = imp_blocks((share + rows - 1) / rows);
-  nblk = nblk <= 3 && (nblk - 1) * pieces <= kImpOnePieces ? 1 : nblk;
+  int nblk = imp_blocks((n_tokens + rows - 1) / rows);
+  // (one workgroup, or one per sequence, needs no second kernel: 23 layers of 20 rows of 256 bf16 9.2 -> 6.0 us)
+  int piece = nblk <= 3 && (nblk - 1) * pieces <= kImpOnePieces ? kImpWhole : kImpAll;
+  if (piece == kImpWhole) {
+    nblk = n_seq;
+  } else if (n_seq > 1) {
+    for (piece = 0; (1 << piece) < kImpWaves * rows || (n_tokens - 1) >> piece >= kImpMaxPieces - 1; ++piece) {}
+    nblk = (int)((n_tokens - 1) >> piece) + n_seq;
+  }
   ImpArgs a;
   a.h_in = h_in; a.other = other; a.h_out_w = h_out_w;
   a.n_tokens = n_tokens; a.hidden = hidden; a.seq_start = seq_start;
+  a.n_seq = n_seq; a.piece = piece;
   a.partial = static_cast<double*>(workspace);
   a.cos_out = cos_out;
-  const dim3 grid(nblk, n_layers, n_seq);
+  const dim3 grid(nblk, n_layers);
   // h_out is stored non-temporally where it is larger than the 256 MB Infinity Cache: nothing of it would be found
   // there again (16 layers of 4096 x 4096 bf16, 537 MB: 304 us, 285 so); below that plain stores are absorbed by the
   // cache and found by the next kernel (16384 x 4096, 134 MB: 68 us, 74 so.  From inputs that lie in memory 79 and 75, but
@@ -344,8 +413,14 @@ static sqa_status launch_importance(const void* h_in, const void* other, void* h
   };
   if (dt == SQA_F32) pick(float{}); else pick(bf16_t{});
   SQA_HIP_CHECK(hipGetLastError());
-  static_assert(kImpMaxBlocks <= 4 * kImpThreads, "partial sums per thread of the final kernel");
-  if (nblk > 1) importance_final_kernel<<<n_layers * n_seq, nblk <= 4 * SQA_WAVE ? SQA_WAVE : kImpThreads, 0, st>>>(a, nblk, n_seq);
+  static_assert(kImpMaxPieces <= 8 * kImpThreads, "partial sums per thread of the final kernel");
+  if (piece != kImpWhole) {
+    const int most = nblk - (n_seq - 1);          // partial sums of a sequence
+    const dim3 items(n_seq, n_layers);
+    const int threads = most <= 4 * SQA_WAVE ? SQA_WAVE : kImpThreads;
+    if (piece == kImpAll) importance_final_kernel<false><<<items, threads, 0, st>>>(a, nblk);
+    else importance_final_kernel<true><<<items, threads, 0, st>>>(a, nblk);
+  }
   SQA_HIP_CHECK(hipGetLastError());
   return SQA_OK;
 }

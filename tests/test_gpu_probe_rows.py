@@ -45,3 +45,39 @@ def test_few_long_rows(sqa, dtype, d, T):
     out = torch.empty_like(a)
     _whole(sqa.residual_add_importance(a, r, out), T, want)
     assert torch.equal(out, h)
+
+
+def _lens(name):
+    gen = torch.Generator().manual_seed(3)
+    return {
+        "one long": [1] * 16 + [4096] + [1] * 16,
+        "ends on pieces": [0, 32, 16, 4, 1, 0, 0, 64, 8, 3, 128, 0, 31, 33, 0],
+        "around 64": [5, 0, 700] + [2] * 60 + [9],         # 64 sequences: one more than a round of the search holds
+        "two rounds": torch.randint(0, 9, (1000,), generator=gen).tolist(),
+        "three rounds": torch.randint(0, 3, (5000,), generator=gen).tolist(),
+        "few rows": [2, 0, 1],
+        "few and empty": [0, 3, 0, 0, 5],
+        "longer pieces": [0, 3, 30000, 1, 100, 40001, 17, 0],
+    }[name]
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 8), ("f32", 64), ("bf16", 512), ("f32", 264)])
+@pytest.mark.parametrize("before,after", [(0, 0), (5, 3)])
+@pytest.mark.parametrize("name", ["one long", "ends on pieces", "around 64", "two rounds", "three rounds", "few rows",
+                                  "few and empty", "longer pieces"])
+def test_uneven_sequences(sqa, dtype, d, name, before, after):
+    """Rows are shared out in pieces that end where a sequence ends: empty, short and long ones in one batch, rows before the
+    first and after the last (which count for none), from one round of the search for a workgroup's sequence to three."""
+    lens = _lens(name)
+    if name == "longer pieces" and d > 64:
+        lens = [n // 4 for n in lens]
+    L, T = 2, before + sum(lens) + after
+    a, _, h, cos = _rows(L, T, d, dtype, T)
+    start = torch.tensor([before] + lens, device=DEV).cumsum(0)
+    upto = torch.nn.functional.pad(cos, (1, 0)).cumsum(1)
+    want = upto[:, start[1:]] - upto[:, start[:-1]]
+    got = sqa.layer_importance_seq(a, h, start.to(torch.int32))
+    _whole(got, torch.tensor(lens, device=DEV), want)
+    assert bool((got[:, torch.tensor(lens, device=DEV) == 0] == 0).all())
+    again = sqa.layer_importance_seq(a, h, start.to(torch.int32))
+    assert torch.equal(got, again)
