@@ -25,8 +25,6 @@ def sqa():
 @pytest.mark.parametrize("g", [1, 2, 4, 8])
 @pytest.mark.parametrize("dtype,D", KINDS)
 def test_unwritten_slots_count_nothing(sqa, dtype, D, g, order, policy, blocked):
-    if (dtype, D) == ("bf16", 128) and g >= 4:
-        pytest.skip("on the matrix cores")
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
     gen = torch.Generator(DEV)
     mk = lambda *shape: torch.randn(*shape, generator=gen, device=DEV).to(tdt)
