@@ -28,11 +28,14 @@ constexpr int64_t kCmpFill = 384;         // workgroups that a call with few uni
 constexpr int64_t kCmpCUs = 256;
 constexpr int64_t kCmpManyUnits = 2048, kCmpManyRows = 128;   // launches of more units than run at once, with fewer rows each: see launch_compress
 constexpr int64_t kCmpMaxParts = 256;         // workgroups per unit
-// Caches that the Infinity Cache (256 MB) does not hold: rows are stored non-temporally, and in launches that move as much as
-// it holds they are read so too.  us, plain, stores only, both: 7B shape (3.4 GB moved) 654, 640, 618; 40 units of 32 layers of
-// 512 tokens 807, 787, 772; one sequence joining a 600 MB cache (93 MB moved) 39.8, 34.3, 36.8, and with the decode step that
-// follows, which has the plain stores to write back, 232 and 207 (stores only).  A smaller cache is found in the Infinity Cache
-// by that step after plain stores: 12 layers of 160 units, fp32, D = 64 (118 MB) 53.5 and 50.2, with the step 65.2 and 72.5.
+// Calls whose layers' caches the Infinity Cache (256 MB) does not hold: rows are stored non-temporally, and in launches that
+// move as much as it holds they are read so too.  us, plain, stores only, both: 7B shape (3.4 GB moved) 654, 640, 618; 40 units of
+// 32 layers of 512 tokens 807, 787, 772; one sequence joining a 600 MB cache in blocks (93 MB moved) 39.8, 34.3, 36.8, and with the
+// decode step that follows, which has the plain stores to write back, 232 and 207 (stores only).  A smaller cache is found in the
+// Infinity Cache by that step after plain stores: 12 layers of 160 units, fp32, D = 64 (118 MB) 53.5 and 50.2, with the
+// step 65.2 and 72.5.  (These are calls in turn; the first one on prompt tensors just filled takes as long either way.)
+// What counts is what that step reads, as far as the host knows it (cached_rows): a call over one layer, and a sequence that joins a
+// dense cache, are counted alone and keep plain stores.
 constexpr int64_t kCmpCacheBytes = (int64_t)320 << 20, kCmpStreamBytes = (int64_t)256 << 20;
 constexpr int kKeysInLdsMax = 16384;     // scores staged in LDS up to this many candidates
 
@@ -354,9 +357,23 @@ __global__ __launch_bounds__(kCmpThreads) void kept_idx_sorted_kernel(sqa_layer_
   }
 }
 
+// Rows of a layer's cache that the decode step after the call reads: those that the call leaves, not what there is room for (118
+// MB in a cache of 472, compression and step, plain and non-temporal stores: 66.0 and 73.5 us).  Where the units differ and
+// only the device knows how much (packed units, budgets per sequence) none, which means plain stores (118 MB that would count as
+// 492 at the largest budget 81.7 and 86.4; 535 as 2517 338 and 335).  In blocks a call that leaves less than half of the pool
+// is taken for some sequences of many, whose rows fill the rest.
+static int64_t cached_rows(const sqa_layer_cache& L, int64_t units, int P, bool per_sequence) {
+  const int64_t left = units * std::min(P, std::min(L.budget, L.capacity));
+  if (L.block_table) {
+    const int64_t pool = (int64_t)L.n_blocks * SQA_BLOCK_SLOTS;
+    return 2 * left < pool ? pool : std::min(left, pool);
+  }
+  return L.unit_offset || per_sequence ? 0 : left;
+}
+
 template <typename T, int D>
 static hipError_t launch_compress(CompressBatch& batch, int n, int P, int policy, int n_sink,
-                                   unsigned units, int64_t cache_bytes /*K and V of the call's layers*/, size_t lds, hipStream_t st) {
+                                   unsigned units, int64_t cache_bytes /*K and V of the call's layers, see cached_rows*/, size_t lds, hipStream_t st) {
   // A unit's rows are shared out among workgroups where one per unit leaves CUs idle (fewer units than CUs) or busy for
   // long after the others (fewer than two per CU, and the longest has more than 1.5 times a CU's share of the rows):
   // as many pieces as bring the launch to 384 equal workgroups, of at least one trip of the copy loop each.  One
@@ -472,11 +489,9 @@ extern "C" sqa_status sqa_prefill_compress_layers_ex(const void* const* K, const
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
   const unsigned units = (unsigned)(B * Hkv);
-  // (blocks: the pools, which hold all sequences; packed units: at most so much)
   int64_t cache_bytes = 0;
   for (int i = 0; i < n_layers; ++i)
-    cache_bytes += (layers[i].block_table ? (int64_t)layers[i].n_blocks * SQA_BLOCK_SLOTS : (int64_t)units * layers[i].capacity) *
-                   (2 * D * (kv_dt == SQA_F32 ? 4 : 2));
+    cache_bytes += cached_rows(layers[i], units, P, opts && opts->budget_seq) * (2 * D * (kv_dt == SQA_F32 ? 4 : 2));
   for (int l0 = 0; l0 < n_layers; l0 += kCmpBatch) {
     const int n = n_layers - l0 < kCmpBatch ? n_layers - l0 : kCmpBatch;
     CompressBatch batch;

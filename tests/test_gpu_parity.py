@@ -545,10 +545,11 @@ def test_prefill_compress_of_many_short_units(sqa, dtype, D, B, b):
 @pytest.mark.parametrize("dtype,D", [("bf16", 128), ("f32", 64)])
 @pytest.mark.parametrize("policy,units,P,b,blocked", [("h2o", 6, 500, 211, True),           # stores: a pool of 320 MiB, little of it written
                                                       ("sliding", 1100, 70, 33, True),       # ... in many short units
-                                                      ("h2o", 64, 4096, 4100, False)])       # stores and loads: 256 MiB moved
+                                                      ("h2o", 80, 4096, 4100, False)])       # stores and loads: 320 MiB left, twice that moved
 def test_prefill_compress_into_caches_beyond_the_infinity_cache(sqa, dtype, D, policy, units, P, b, blocked):
-    """Caches of 320 MiB and more have their rows stored non-temporally (launches that move 256 MiB read them so too): the same
-    rows, scores and positions as in a cache just below that size."""
+    """Calls over caches of 320 MiB and more (in blocks: pools; dense: the rows that the call leaves) store rows
+    non-temporally, and launches that move 256 MiB read them so too: the same rows, scores and positions as in a pool just below
+    that size, or with a call per layer."""
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
     gen = torch.Generator(device=DEV).manual_seed(units)
     L = 2
@@ -562,8 +563,13 @@ def test_prefill_compress_into_caches_beyond_the_infinity_cache(sqa, dtype, D, p
             caches = sqa.LayerCaches([b] * L, [b] * L, units, 1, D, tdt, DEV, True, blocked=True,
                                      spare_blocks=(limit // 16 if big else min(limit // 16 - 1, own + 3)) - own)
         else:
-            caches = sqa.LayerCaches([b] * L, [(limit + units - 1) // units if big else P] * L, units, 1, D, tdt, DEV, True)
-        sqa.prefill_compress_layers(Ks, Vs, Ss, policy, 4, caches)
+            assert units * min(P, b) >= limit
+            caches = sqa.LayerCaches([b] * L, [P] * L, units, 1, D, tdt, DEV, True)
+        if blocked or big:
+            sqa.prefill_compress_layers(Ks, Vs, Ss, policy, 4, caches)
+        else:
+            for l in range(L):
+                sqa.prefill_compress_layers(Ks[l:l + 1], Vs[l:l + 1], Ss[l:l + 1], policy, 4, caches, layer0=l)
         n = min(P, b)
         rows = [unit_kv(caches, l, u, 0, n) for l in range(L) for u in (0, units // 2, units - 1)]
         got.append((rows, [[x[l].view(units, -1)[:, :n].cpu() for x in (caches.pos, caches.score)] for l in range(L)],
