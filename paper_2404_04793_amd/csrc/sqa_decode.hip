@@ -34,6 +34,7 @@
 // in step 3 with the scores and positions requested at the start, the decision costs
 // one barrier, and the rows of step 4 are written by one wave meanwhile.
 #include "sqa_common.h"
+#include <algorithm>
 #include <cstring>
 #include <type_traits>
 
@@ -378,8 +379,23 @@ __global__ __launch_bounds__(kDecThreads) void decode_large_kernel(const DecodeA
 // 571 slots) 949 -> 952, 6.7 GB (160 slots) 1173 -> 1174 / 8.0 GB (35 to 571) 1449 -> 1427, 10.9 GB (160 slots) 1953 -> 1920,
 // 12 GB (35 to 571) 2233 -> 2170, 16.8 GB (40 slots) 3474 -> 3353, 24 GB (571 slots) 4153 -> 4080; D = 64, 10.9 GB 2072 -> 2016;
 // fp32, 11.7 GB 2054 -> 2031.  What is written counts against what is read: long units gain little (1024 slots 3572 -> 3562,
-// 143 to 2271 slots 1768 -> 1772), 2 and more heads per KV head nothing (2061 -> 2061).
+// 143 to 2271 slots 1768 -> 1772), 2 and more heads per KV head nothing (2061 -> 2061).  (Calls of the same shape differ by up to
+// 3 % with the place of their buffers; these were taken in turn on the same ones.)  The size is the call's: a cache of any
+// size that is stepped layer by layer keeps the ordinary kernel, and units that are not full count as if they were (240 slots, 60
+// filled: 2.0 GB counted as 8.1 448 -> 453).  Where units differ and only the device knows how much (packed units, budgets per
+// sequence; not in blocks, whose pools bound it) the ordinary kernel stays: 2.4 GB packed that would count as 8.1 446 -> 455.
 constexpr int64_t kLargeBytes = (int64_t)7 << 30;
+static int64_t known_kv_bytes(const sqa_layer_cache* layers, int n_layers, int64_t units, int64_t row_bytes /*K and V*/, bool per_sequence) {
+  int64_t rows = 0;
+  for (int i = 0; i < n_layers; ++i) {
+    const sqa_layer_cache& L = layers[i];
+    int64_t all = units * std::min(L.budget, L.capacity);
+    if (L.block_table) all = std::min(all, (int64_t)L.n_blocks * SQA_BLOCK_SLOTS);
+    else if (L.unit_offset || per_sequence) all = 0;
+    rows += all;
+  }
+  return rows * row_bytes;
+}
 
 typedef void (*decode_fn)(const DecodeArgs);
 
@@ -785,9 +801,7 @@ static sqa_status decode_launch(sqa_dtype dt, const DecodePlan& plan, size_t lds
                                 int B, int Hq, int Hkv, int D, int32_t new_pos, sqa_policy policy, int n_sink,
                                 const sqa_layer_cache* layers, const sqa_layer_cache* layers_dev, int n_layers,
                                 void* out, hipStream_t st, const sqa_batch_opts* opts) {
-  int64_t kv_bytes = 0;
-  for (int i = 0; i < n_layers; ++i)
-    kv_bytes += (int64_t)B * Hkv * (layers[i].budget < layers[i].capacity ? layers[i].budget : layers[i].capacity) * 2 * D * (dt == SQA_F32 ? 4 : 2);
+  const int64_t kv_bytes = known_kv_bytes(layers, n_layers, (int64_t)B * Hkv, 2 * D * (dt == SQA_F32 ? 4 : 2), opts && opts->budget_seq);
   const decode_fn fn = pick(dt, D, Hq / Hkv, policy == SQA_H2O, layers[0].block_table != nullptr, plan.waves, kv_bytes >= kLargeBytes);
   if (lds > 64 * 1024) SQA_HIP_CHECK(allow_dynamic_lds(reinterpret_cast<const void*>(fn), lds));
   DecodeArgs a;
