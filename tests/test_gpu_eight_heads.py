@@ -56,3 +56,20 @@ def test_nothing_beyond_the_end_of_a_unit_counts(sqa, dtype, D, b, n, order):
             sqa.decode_step(q, k, v, n + t, "h2o", 4, caches, out, ws, opts=sqa.batch_opts(order=order))
         got.append(out.clone())
     assert torch.isfinite(got[1].float()).all() and torch.equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("order", ["evict_then_attend", "attend_then_evict"])
+@pytest.mark.parametrize("dtype,D", KINDS)
+def test_scores_use_the_exponents_that_were_summed(sqa, dtype, D, order):
+    """A token alone has the probability 1 under each of the 8 heads, however large its logit (here up to 300): the exponential
+    that its score adds has to be the one its normaliser holds.  Each is off by at most the reciprocal's and the product's
+    rounding, 2^-22 together; a logit rounded in between would be off by 2^-24 of itself."""
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(DEV).manual_seed(D)
+    B, H = 16, 4
+    mk = lambda *shape: (8 * torch.randn(*shape, generator=gen, device=DEV)).to(tdt)
+    caches = sqa.LayerCaches([40], [40], B, H, D, tdt, DEV, True)
+    q, k, v = mk(1, B, 8 * H, D), mk(1, B, H, D), mk(1, B, H, D)
+    out, ws = torch.empty_like(q), sqa.decode_workspace(caches, 8 * H, "h2o")
+    sqa.decode_step(q, k, v, 0, "h2o", 4, caches, out, ws, opts=sqa.batch_opts(order=order))
+    assert float((caches.score[0][..., 0].double() - 8).abs().max()) <= 8 * 2.0 ** -22
