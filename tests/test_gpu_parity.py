@@ -81,9 +81,9 @@ def test_residual_add_importance(sqa, dtype, L, T, d, inplace):
                                      ("bf16", 520), ("f32", 264)])
 @pytest.mark.parametrize("T", [1, 3, 31, 32, 33, 96, 97, 128, 129, 1030])
 def test_importance_of_short_rows(sqa, dtype, d, T):
-    """Rows of up to 1 KiB share a wave (32 or 64 lanes each; 32 or 64 rows' cosines are worked out together), one workgroup's
-    result needs no second kernel: around those numbers of rows, pieces per row and workgroups, alone, inside the residual add
-    (in place too) and per sequence.  fp32 products over at most 520 elements."""
+    """Rows of up to 1 KiB share a wave (32 or 64 lanes each), one workgroup's result needs no second kernel: around those
+    numbers of rows, pieces per row and workgroups, alone, inside the residual add (in place too) and per sequence.  (The rows
+    at which cosines are worked out inside the loop: test_gpu_probe_rows.py.)  fp32 products over at most 520 elements."""
     tdt = torch.float32 if dtype == "f32" else torch.bfloat16
     gen = torch.Generator().manual_seed(T * 1000 + d)
     a, r = (torch.randn(2, T, d, generator=gen).to(tdt).to(DEV) for _ in range(2))
@@ -106,7 +106,9 @@ def test_importance_of_short_rows(sqa, dtype, d, T):
             assert _cos_rel(per[:, i], O.layer_importance(np64(a[:, cut[i]:cut[i + 1]]), np64(h[:, cut[i]:cut[i + 1]]))) < 1e-5
 
 
-@pytest.mark.parametrize("L,T,d", [(2, 1021, 64), (1, 1025, 128), (1, 4099, 64),      # 256, 257 and 1024 partial sums
+@pytest.mark.parametrize("L,T,d", [(2, 1021, 520), (1, 1025, 520), (1, 4099, 520),    # 256, 257 and 1024 partial sums
+                                   (2, 1021, 64), (1, 1025, 128), (1, 4099, 64),      # short rows: 32, 33 and 129 of them
+                                   (1, 8192, 128), (1, 8193, 128),                    # ... 256 and 257
                                    (1, 32768, 4096), (2, 16383, 4096)])                # h_out of 256 MiB, and just below
 def test_residual_add_importance_store_forms(sqa, L, T, d):
     """Stored sums bit for bit, and the same cosines as the probe of the stored values, around the number of partial

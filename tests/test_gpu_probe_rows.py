@@ -1,6 +1,6 @@
 """Every row of the probe counts once, whichever kernel, workgroup and turn it falls to.  Rows that go in and come out as
-they are, negated or zero have the cosines 1, -1 and 0 (zero rows: 0) without rounding, so the sum over a layer's or a
-sequence's rows is a whole number: one row lost, counted twice or credited to a neighbour shows in it."""
+they are, negated or zero have the cosines 1, -1 and 0, so the sum over a layer's or a sequence's rows is a whole number: one
+row lost, counted twice or credited to a neighbour shows in it."""
 import pytest
 import torch
 
@@ -28,10 +28,12 @@ def _rows(L, T, d, dtype, seed):
 
 
 def _whole(cos, counts, want):
-    """The sums that the means stand for.  cos is rounded to fp32 once, at most 2^-24 of |mean| <= 1: 2^-24 of a row per row,
-    0.018 for 300000; the cosine of a row alone is off by a few 2^-53."""
+    """The sums that the means stand for; a row is 1.  A mean is rounded to fp32 (2^-24 of it).  The products of a row with
+    itself and with its opposite go through the same sums and may round differently (two bf16 products added at once do): over
+    a row of up to 1 KiB at most 4 additions in a lane and 6 over the lanes, 10 * 2^-23 of it, 0.31 over 262144 rows if
+    all were off in one direction; a row of 8 elements 4, 0.25 over 530000; longer rows are few here (20000 of 264 elements, 14 each: 0.04)."""
     got = cos.double() * counts
-    assert float((got - want).abs().max()) < 0.02, (got - want).abs().max()
+    assert float((got - want).abs().max()) < 0.35, (got - want).abs().max()
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 520), ("bf16", 2048), ("f32", 1032), ("bf16", 4096), ("f32", 2056), ("f32", 16384)])
@@ -45,6 +47,19 @@ def test_few_long_rows(sqa, dtype, d, T):
     out = torch.empty_like(a)
     _whole(sqa.residual_add_importance(a, r, out), T, want)
     assert torch.equal(out, h)
+
+
+@pytest.mark.parametrize("dtype,d,T", [("bf16", 8, 262143), ("bf16", 8, 262144), ("f32", 8, 262145), ("f32", 128, 294913), ("bf16", 8, 530000),
+                                       ("bf16", 264, 262144), ("f32", 136, 262145), ("bf16", 512, 278529)])
+def test_many_short_rows(sqa, dtype, d, T):
+    """A lane keeps the sums of one row, and when all lanes of a row have one (32 or 64) their cosines are worked out together:
+    around and after the 262144 rows at which that comes up inside the loop (1024 workgroups of 4 waves, 8 turns of 8 rows or 16
+    of 4), alone and inside the residual add."""
+    a, r, h, cos = _rows(1, T, d, dtype, T)
+    want = cos.sum(1)
+    _whole(sqa.layer_importance(a, h), T, want)
+    _whole(sqa.residual_add_importance(a, r, a), T, want)
+    assert torch.equal(a, h)
 
 
 def _lens(name):

@@ -35,6 +35,16 @@ def test_no_decode_kernel_spills(res):
         assert v["ScratchSize"] == 0 and v["VGPRs Spill"] == 0, k
 
 
+def test_no_kernel_of_the_other_forms_spills(res):
+    """The decode kernels with 8 waves per workgroup and for very large caches, the probe of short rows, and what adds up."""
+    for name, n in [("decode_wide_kernel", 52), ("decode_large_kernel", 16), ("importance_short_rows_kernel", 12),
+                    ("importance_final_kernel", 2)]:
+        hits = {k: v for k, v in res.items() if name in k}
+        assert len(hits) == n, (name, len(hits))
+        for k, v in hits.items():
+            assert v["ScratchSize"] == 0 and v["VGPRs Spill"] == 0, k
+
+
 def test_decode_kernels_keep_their_waves(res):
     # bf16, D = 128, one query head per KV head: the headline kernel (H2O) and its policy-free sibling
     # (the last template argument: 0 = dense, 1 = K and V in blocks named by a block table)
