@@ -87,7 +87,8 @@ enum { SQA_ST_LEN = 0, SQA_ST_RING_HEAD = 1, SQA_ST_EVICT_HINT = 2, SQA_ST_WORDS
  * sqa_decode_step keeps it.
  */
 typedef struct sqa_layer_cache {
-  void* K;             /* [B][Hkv][capacity][D], element type = the call's dtype   */
+  void* K;             /* [B][Hkv][capacity][D], element type = the call's dtype.  Here and in V,
+                          score_acc and pos, slots that hold no token may hold anything */
   void* V;             /* [B][Hkv][capacity][D]                                    */
   float* score_acc;    /* [B][Hkv][capacity] accumulated attention (H2O; else may be NULL) */
   int32_t* pos;        /* [B][Hkv][capacity] token position per slot = kept_idx    */
@@ -385,7 +386,9 @@ typedef struct sqa_decode_plan_info {
   int64_t workgroups;       /* grid of the one launch, 64 x sqa_decode_plan_waves threads each            */
   int64_t workspace_bytes;  /* what the call uses of its workspace (<= sqa_decode_workspace_bytes)        */
   int32_t lds_bytes;        /* dynamic LDS per workgroup                                                  */
-  int32_t matrix_cores;     /* 1: the MFMA variant runs (bf16, D = 128, 4 or 8 query heads per KV head)   */
+  int32_t matrix_cores;     /* 1: the variant with probabilities in bf16 runs (bf16, D = 128, 4 or 8 query heads per
+                               KV head).  0: probabilities in 32 bits -- on the matrix cores too under 8 query heads
+                               per KV head in fp32 (at D = 128 only with H2O) and in bf16 at D = 64            */
   int32_t wide_tail;        /* 1: so few workgroups (up to 512) that a long unit's score walk keeps all waves
                                (0: only that of units over 768 tokens does, up to 2048 workgroups; with 8
                                waves per workgroup off the matrix cores any unit's does)                   */
@@ -405,7 +408,7 @@ sqa_status sqa_decode_plan(const sqa_layer_cache* layers, int n_layers, int B, i
                            sqa_dtype dt, sqa_policy policy, sqa_decode_plan_info* info,
                            sqa_decode_layer_plan* per_layer);
 /* Waves of 64 threads per workgroup of that launch: 8 where it has at most 256 workgroups (one per CU; not for 8
- * query heads per KV head off the matrix cores), else 4.  0 where sqa_decode_plan returns an error. */
+ * query heads per KV head unless matrix_cores is 1), else 4.  0 where sqa_decode_plan returns an error. */
 int32_t sqa_decode_plan_waves(const sqa_layer_cache* layers, int n_layers, int B, int Hq, int Hkv, int D,
                               sqa_dtype dt, sqa_policy policy);
 

@@ -438,14 +438,17 @@ def prefill_compress(K: torch.Tensor, V: torch.Tensor, attn_scores: Optional[tor
                                      n_sink, caches.struct_ptr(layer), _stream()), "sqa_prefill_compress")
 
 
-def _addresses(tensors: Sequence[torch.Tensor], n: int) -> array:
-    """Their n device addresses, one after the other (the caller keeps the array for the length of the call).  The library
-    reads n of them whatever the list holds: a shorter list ends in NULLs, which it refuses where it needs them."""
-    a = array("Q", [t.data_ptr() for t in tensors])
+def _addresses(tensors: Sequence[torch.Tensor]) -> array:
+    """Their device addresses, one after the other (the caller keeps the array for the length of the call)."""
+    return array("Q", [t.data_ptr() for t in tensors])
+
+
+def _filled(a: array, n: int) -> array:
+    """n addresses: the library reads as many whatever the list holds.  A shorter one ends in NULLs, which it refuses where it
+    needs them."""
     if len(a) > n:
         raise IndexError("%d tensors for %d layers" % (len(a), n))
-    if len(a) < n:
-        a.frombytes(bytes(a.itemsize * (n - len(a))))
+    a.frombytes(bytes(a.itemsize * (n - len(a))))
     return a
 
 
@@ -457,12 +460,19 @@ def prefill_compress_layers(K: Sequence[torch.Tensor], V: Sequence[torch.Tensor]
     table: sqa_layer_cache records to use instead of the caches' own (LayerCaches.sequence_table)."""
     n = len(K)
     B, Hkv, P, D = K[0].shape
-    Ks, Vs = _addresses(K, n), _addresses(V, n)
-    Ss = None if attn_scores is None or attn_scores[0] is None else _addresses(attn_scores, n)
-    records = caches.table if table is None else table
-    if layer0 < 0 or (layer0 + n) * _LC_BYTES > C.sizeof(records):
+    Ks, Vs = _addresses(K), _addresses(V)
+    Ss = None if attn_scores is None or attn_scores[0] is None else _addresses(attn_scores)
+    if len(Vs) != n:
+        Vs = _filled(Vs, n)
+    if Ss is not None and len(Ss) != n:
+        Ss = _filled(Ss, n)
+    if table is None:
+        table, there = caches.table, caches.L
+    else:
+        there = C.sizeof(table) // _LC_BYTES
+    if layer0 < 0 or layer0 + n > there:
         raise IndexError("layers outside the table")
-    layers = C.addressof(records) + layer0 * _LC_BYTES
+    layers = C.addressof(table) + layer0 * _LC_BYTES
     _check(_lib.sqa_prefill_compress_layers_ex(Ks.buffer_info()[0], Vs.buffer_info()[0], _dt(K[0]),
                                                None if Ss is None else Ss.buffer_info()[0], B, Hkv, P, D, POLICY[policy],
                                                n_sink, layers, n, _stream(), _opts(opts)),

@@ -1,5 +1,5 @@
 """Slots that hold no token count nothing, whatever lies there: a cache handed over as it was allocated, with NaN in every
-slot of K, V and the scores, gives the outputs and scores of one filled with zeros, bit for bit, while the units fill up
+slot of K, V and the scores (and any positions), gives the outputs and scores of one filled with zeros, bit for bit, while the units fill up
 from nothing and from a prompt, short of their capacity and beyond it.  Every kernel reads rows before it knows the unit's
 length, or fills up a tile with them, and counts them with weight 0 -- which is not enough for NaN."""
 import pytest
@@ -36,6 +36,8 @@ def test_unwritten_slots_count_nothing(sqa, dtype, D, g, order, policy, blocked)
                 caches = sqa.LayerCaches([b], [b + spare], B, H, D, tdt, DEV, True, blocked=blocked)
                 for x in (caches.K[0], caches.V[0], caches.score[0]):
                     x.fill_(fill)
+                if fill != 0.0:
+                    caches.pos[0].fill_(1 << 30)
                 if n > 0:
                     scores = torch.rand(B, H, n, generator=gen, device=DEV)
                     sqa.prefill_compress_layers([mk(B, H, n, D)], [mk(B, H, n, D)], [scores], policy, 4, caches)
