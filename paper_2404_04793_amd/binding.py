@@ -473,10 +473,11 @@ def prefill_compress_layers(K: Sequence[torch.Tensor], V: Sequence[torch.Tensor]
     if layer0 < 0 or layer0 + n > there:
         raise IndexError("layers outside the table")
     layers = C.addressof(table) + layer0 * _LC_BYTES
-    _check(_lib.sqa_prefill_compress_layers_ex(Ks.buffer_info()[0], Vs.buffer_info()[0], _dt(K[0]),
+    code = _lib.sqa_prefill_compress_layers_ex(Ks.buffer_info()[0], Vs.buffer_info()[0], _DT.get(K[0].dtype, -1),
                                                None if Ss is None else Ss.buffer_info()[0], B, Hkv, P, D, POLICY[policy],
-                                               n_sink, layers, n, _stream(), _opts(opts)),
-           "sqa_prefill_compress_layers")
+                                               n_sink, layers, n, _stream(), None if opts is None else C.byref(opts))
+    if code != SQA_OK:
+        raise SqaError(code, "sqa_prefill_compress_layers")
 
 
 def decode_workspace(caches: "LayerCaches", Hq: int, policy: str, layer0: int = 0,

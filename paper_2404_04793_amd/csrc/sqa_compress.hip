@@ -359,16 +359,15 @@ __global__ __launch_bounds__(kCmpThreads) void kept_idx_sorted_kernel(sqa_layer_
 
 // Rows of a layer's cache that the decode step after the call reads: those that the call leaves, not what there is room for (118
 // MB in a cache of 472, compression and step, plain and non-temporal stores: 66.0 and 73.5 us).  Where the units differ and
-// only the device knows how much (packed units, budgets per sequence) none, which means plain stores (118 MB that would count as
-// 492 at the largest budget 81.7 and 86.4; 535 as 2517 338 and 335).  In blocks a call that leaves less than half of the pool
-// is taken for some sequences of many, whose rows fill the rest.
-static int64_t cached_rows(const sqa_layer_cache& L, int64_t units, int P, bool per_sequence) {
+// only the device knows how much (packed units, budgets per sequence) they count at the layer's largest: right for lengths
+// within a factor of two (535 MB that count as 2517 338 and 335), too much for a few long ones among many short (118 MB that
+// count as 492 81.7 and 86.4).  In blocks a call that leaves less than half of the pool is taken for some sequences of many,
+// whose rows fill the rest.
+static int64_t cached_rows(const sqa_layer_cache& L, int64_t units, int P) {
   const int64_t left = units * std::min(P, std::min(L.budget, L.capacity));
-  if (L.block_table) {
-    const int64_t pool = (int64_t)L.n_blocks * SQA_BLOCK_SLOTS;
-    return 2 * left < pool ? pool : std::min(left, pool);
-  }
-  return L.unit_offset || per_sequence ? 0 : left;
+  if (!L.block_table) return left;
+  const int64_t pool = (int64_t)L.n_blocks * SQA_BLOCK_SLOTS;
+  return 2 * left < pool ? pool : std::min(left, pool);
 }
 
 template <typename T, int D>
@@ -491,7 +490,7 @@ extern "C" sqa_status sqa_prefill_compress_layers_ex(const void* const* K, const
   const unsigned units = (unsigned)(B * Hkv);
   int64_t cache_bytes = 0;
   for (int i = 0; i < n_layers; ++i)
-    cache_bytes += cached_rows(layers[i], units, P, opts && opts->budget_seq) * (2 * D * (kv_dt == SQA_F32 ? 4 : 2));
+    cache_bytes += cached_rows(layers[i], units, P) * (2 * D * (kv_dt == SQA_F32 ? 4 : 2));
   for (int l0 = 0; l0 < n_layers; l0 += kCmpBatch) {
     const int n = n_layers - l0 < kCmpBatch ? n_layers - l0 : kCmpBatch;
     CompressBatch batch;

@@ -383,16 +383,14 @@ __global__ __launch_bounds__(kDecThreads) void decode_large_kernel(const DecodeA
 // 3 % with the place of their buffers; these were taken in turn on the same ones.)  The size is the call's: a cache of any
 // size that is stepped layer by layer keeps the ordinary kernel, and units that are not full count as if they were (240 slots, 60
 // filled: 2.0 GB counted as 8.1 448 -> 453).  Where units differ and only the device knows how much (packed units, budgets per
-// sequence; not in blocks, whose pools bound it) the ordinary kernel stays: 2.4 GB packed that would count as 8.1 446 -> 455.
+// sequence) they count at the layer's largest, in blocks at most as the pools: 6.2 GB packed, streaming, that count as 8.1, 1067 ->
+// 1015; a few long among many short lose by it (2.4 GB that count as 8.1 446 -> 455).
 constexpr int64_t kLargeBytes = (int64_t)7 << 30;
-static int64_t known_kv_bytes(const sqa_layer_cache* layers, int n_layers, int64_t units, int64_t row_bytes /*K and V*/, bool per_sequence) {
+static int64_t counted_kv_bytes(const sqa_layer_cache* layers, int n_layers, int64_t units, int64_t row_bytes /*K and V*/) {
   int64_t rows = 0;
   for (int i = 0; i < n_layers; ++i) {
-    const sqa_layer_cache& L = layers[i];
-    int64_t all = units * std::min(L.budget, L.capacity);
-    if (L.block_table) all = std::min(all, (int64_t)L.n_blocks * SQA_BLOCK_SLOTS);
-    else if (L.unit_offset || per_sequence) all = 0;
-    rows += all;
+    const int64_t all = units * std::min(layers[i].budget, layers[i].capacity);
+    rows += layers[i].block_table ? std::min(all, (int64_t)layers[i].n_blocks * SQA_BLOCK_SLOTS) : all;
   }
   return rows * row_bytes;
 }
@@ -801,7 +799,7 @@ static sqa_status decode_launch(sqa_dtype dt, const DecodePlan& plan, size_t lds
                                 int B, int Hq, int Hkv, int D, int32_t new_pos, sqa_policy policy, int n_sink,
                                 const sqa_layer_cache* layers, const sqa_layer_cache* layers_dev, int n_layers,
                                 void* out, hipStream_t st, const sqa_batch_opts* opts) {
-  const int64_t kv_bytes = known_kv_bytes(layers, n_layers, (int64_t)B * Hkv, 2 * D * (dt == SQA_F32 ? 4 : 2), opts && opts->budget_seq);
+  const int64_t kv_bytes = counted_kv_bytes(layers, n_layers, (int64_t)B * Hkv, 2 * D * (dt == SQA_F32 ? 4 : 2));
   const decode_fn fn = pick(dt, D, Hq / Hkv, policy == SQA_H2O, layers[0].block_table != nullptr, plan.waves, kv_bytes >= kLargeBytes);
   if (lds > 64 * 1024) SQA_HIP_CHECK(allow_dynamic_lds(reinterpret_cast<const void*>(fn), lds));
   DecodeArgs a;
